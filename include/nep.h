@@ -387,7 +387,9 @@ nep_status snes_run(nep_ctx ctx, nep_dataset ds, int n_par, int n_pop, float* m_
 
 /* Replace the positions of a dataset's atoms (pos_dev [3][sum N] float64 on
  * the device, same order and structures as at creation), wrap them into their
- * cells and rebuild the lists.  NEP_EOVERFLOW if a list outgrows its capacity. */
+ * cells and rebuild the lists.  NEP_EOVERFLOW if a list outgrows its capacity.
+ * The operands of the population calls follow here once such a call has used
+ * the dataset, else with the first one. */
 nep_status nep_dataset_set_positions(nep_ctx ctx, nep_dataset ds, const double* pos_dev);
 
 /* Copy the dataset's current (wrapped) positions to pos_dev [3][sum N]. */

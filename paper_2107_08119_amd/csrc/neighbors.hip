@@ -544,61 +544,25 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
     scan(std::false_type{});
 }
 
-// One 64-lane wave per atom (4 atoms per block): every atom j and every image
-// m in [-k, k]^3 of the wrapped frame (boxes thinner than three cut-off
-// widths).  Candidate c = j (2k+1)^3 + image (m2 fastest) is tested by lane
-// c mod 64; a ballot and a population count give each kept entry the slot of
-// the serial order (angular-range entries first, then the radial-only ones).
-__global__ __launch_bounds__(256) void k_build_all_pairs(
+// Boxes thinner than three cut-off widths: one wave per atom over every atom
+// and lattice image (scan_images), blockDim.x / 64 atoms per block.
+__global__ __launch_bounds__(64 * kImageWaves) void k_build_all_pairs(
     int n, int cap, const double* __restrict__ pos, Box box, int k0, int k1, int k2,
     const int* __restrict__ wrap, double rc2_r, double rc2_a, uint32_t* __restrict__ nl,
-    int* __restrict__ cnt_r, int* __restrict__ cnt_a, int* __restrict__ flags) {
-  const int lane = (int)threadIdx.x % 64;
-  const int i = (int)blockIdx.x * 4 + (int)threadIdx.x / 64;
+    uint32_t* __restrict__ nl_rm, int* __restrict__ cnt_r, int* __restrict__ cnt_a,
+    int* __restrict__ flags) {
+  __shared__ uint32_t stash[kImageWaves][kImageStash];
+  const int w = (int)threadIdx.x / 64;
+  const int i = (int)(blockIdx.x * (blockDim.x / 64)) + w;
   if (i >= n) return;  // whole waves leave together
-  const double xi = pos[i], yi = pos[n + i], zi = pos[2 * n + i];
-  const int wi0 = wrap[i], wi1 = wrap[n + i], wi2 = wrap[2 * n + i];
-  const int d1 = 2 * k1 + 1, d2 = 2 * k2 + 1;
-  const int nimg = (2 * k0 + 1) * d1 * d2;
-  const long long total = (long long)n * nimg;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  int count = 0;
-  bool overflow = false, bad_image = false;
-  for (int pass = 0; pass < 2; ++pass) {
-    for (long long base = 0; base < total; base += 64) {
-      const long long c = base + lane;
-      bool keep = false;
-      uint32_t entry = 0;
-      if (c < total) {
-        const int j = (int)(c / nimg), im = (int)(c % nimg);
-        const int m0 = im / (d1 * d2) - k0, m1 = (im / d2) % d1 - k1, m2 = im % d2 - k2;
-        const int n0 = m0 + wi0 - wrap[j], n1 = m1 + wi1 - wrap[n + j], n2 = m2 + wi2 - wrap[2 * n + j];
-        if (!(j == i && n0 == 0 && n1 == 0 && n2 == 0)) {
-          const double r2 = list_r2(pos[j], pos[n + j], pos[2 * n + j], xi, yi, zi, n0, n1, n2, box.h);
-          const bool in_a = r2 < rc2_a;
-          keep = pass == 0 ? in_a : (!in_a && r2 < rc2_r);
-          if (keep && (n0 < -3 || n0 > 3 || n1 < -3 || n1 > 3 || n2 < -3 || n2 > 3)) {
-            bad_image = true;
-            keep = false;
-          }
-          entry = pack_entry(j, n0, n1, n2);
-        }
-      }
-      const unsigned long long b = __ballot(keep);
-      if (keep) {
-        const int slot = count + __popcll(b & below);
-        if (slot < cap)
-          nl[(size_t)slot * n + i] = entry;
-        else
-          overflow = true;
-      }
-      count += __popcll(b);
-    }
-    if (pass == 0 && lane == 0) cnt_a[i] = min(count, cap);
+  const ImageList l = scan_images(n, cap, i, 0, n, pos, wrap, box.h, box.hinv, k0, k1, k2, rc2_r,
+                                  rc2_a, 0.f, 0.f, nl, nl_rm, stash[w]);
+  if ((threadIdx.x & 63) == 0) {
+    cnt_a[i] = min(l.na, cap);
+    cnt_r[i] = min(l.na + l.nr, cap);
   }
-  if (lane == 0) cnt_r[i] = min(count, cap);
-  if (overflow) flags[kFlagOverflow] = 1;
-  if (bad_image) flags[kFlagImage] = 1;
+  if (l.overflow) flags[kFlagOverflow] = 1;
+  if (l.bad_image) flags[kFlagImage] = 1;
 }
 
 // Slot of the reverse entry (i, -n) in atom j's list, for every entry (j, n)
@@ -736,12 +700,12 @@ inline unsigned blocks_for(size_t work, int block) { return (unsigned)((work + b
 
 }  // namespace
 
-void launch_reverse(nep_ctx ctx, int n, int cap, const uint32_t* nl, const int* cnt_r,
-                    const int* cnt_a, int* rev) {
+void launch_reverse(nep_ctx ctx, int n, int cap, const uint32_t* nl, const uint32_t* nl_rm,
+                    const int* cnt_r, const int* cnt_a, int* rev) {
   const size_t ncap = (size_t)n * cap;
   if (ncap == 0) return;
   launch_kernel(ctx, false, false, k_reverse, dim3(blocks_for((size_t)n, kReverseAtoms)),
-                dim3(kBlock), n, cap, nl, (const uint32_t*)nullptr, cnt_r, cnt_a, rev,
+                dim3(kBlock), n, cap, nl, nl_rm, cnt_r, cnt_a, rev,
                 ctx->flags.ptr);
 }
 
@@ -893,13 +857,17 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel) {
                   (const CellRec*)s.cell_rec.ptr, rc2_r, rc2_a, s.nl.ptr, s.nl_rm.ptr, s.cnt_r.ptr,
                   s.cnt_a.ptr, ctx->flags.ptr);
   } else {
+    // (a fixed workspace may have no room for the per-atom copy)
+    if (!(s.nl_rm.view && !s.nl_rm.ptr) && (e = s.nl_rm.ensure(ncap)) != hipSuccess)
+      return check_hip(ctx, e, "allocating neighbour lists");
     launch_kernel(ctx, true, false, k_bin, dim3(blocks_for(n, kBlock)), blk, n, s.pos_s.ptr, s.box,
                   1, 1, 1, 0, wrap_in_place ? 1 : 0, s.wrap.ptr, (int*)nullptr, (int*)nullptr,
                   s.pos_ref.ptr);
-    launch_kernel(ctx, false, false, k_build_all_pairs, dim3(blocks_for(n, 4)), dim3(256), n,
-                  s.cap, (const double*)s.pos_s.ptr, s.box, s.kimg[0], s.kimg[1], s.kimg[2],
-                  (const int*)s.wrap.ptr, rc2_r, rc2_a, s.nl.ptr, s.cnt_r.ptr, s.cnt_a.ptr,
-                  ctx->flags.ptr);
+    const int waves = image_waves(n);
+    launch_kernel(ctx, false, false, k_build_all_pairs, dim3(blocks_for(n, waves)),
+                  dim3(64 * waves), n, s.cap, (const double*)s.pos_s.ptr, s.box, s.kimg[0],
+                  s.kimg[1], s.kimg[2], (const int*)s.wrap.ptr, rc2_r, rc2_a, s.nl.ptr,
+                  s.nl_rm.ptr, s.cnt_r.ptr, s.cnt_a.ptr, ctx->flags.ptr);
   }
   // caller index -> internal index, for the coalesced copies back (the cell
   // path's k_rank_permute writes it)
@@ -908,7 +876,7 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel) {
                   (const int*)s.perm.ptr, s.iperm.ptr);
   launch_kernel(ctx, false, true, k_reverse, dim3(blocks_for((size_t)n, kReverseAtoms)), blk, n,
                 s.cap, (const uint32_t*)s.nl.ptr,
-                s.use_cells ? (const uint32_t*)s.nl_rm.ptr : (const uint32_t*)nullptr,
+                (const uint32_t*)s.nl_rm.ptr,
                 (const int*)s.cnt_r.ptr, (const int*)s.cnt_a.ptr, s.rev.ptr, ctx->flags.ptr);
   return check_hip(ctx, hipGetLastError(), "launching neighbour kernels");
 }

@@ -77,6 +77,34 @@ hipError_t evaluate_internal(nep_ctx ctx, bool vel, double* out, int mode, doubl
   });
 }
 
+nep_status synchronize_flags(nep_ctx ctx, unsigned long long* pairs) {
+  DeviceGuard guard(ctx->device);
+  int h[kFlagWords];
+  nep_status st = check_hip(ctx,
+                            hipMemcpyAsync(h, ctx->flags.ptr, sizeof(h), hipMemcpyDeviceToHost,
+                                           ctx->stream),
+                            "reading device flags");
+  if (st != NEP_OK) return st;
+  st = check_hip(ctx, hipStreamSynchronize(ctx->stream), "synchronizing");
+  if (st != NEP_OK) return st;
+  if (pairs) std::memcpy(pairs, h + kPairTotals, 2 * sizeof(*pairs));
+  int any = 0;
+  for (int k = 0; k < kNumFlags; ++k) any |= h[k];
+  if (any) {
+    st = check_hip(ctx, hipMemset(ctx->flags.ptr, 0, sizeof(int) * kNumFlags), "clearing device flags");
+    if (st != NEP_OK) return st;
+  }
+  if (h[kFlagOverflow]) return fail(ctx, NEP_EOVERFLOW, "an atom has more than max_neighbors neighbours");
+  if (h[kFlagImage]) return fail(ctx, NEP_EIMAGE, "a neighbour needs a lattice image beyond +-3 cells");
+  if (h[kFlagReverse]) return fail(ctx, NEP_EDEVICE, "neighbour list is not symmetric");
+  if (h[kFlagNonFinite]) return fail(ctx, NEP_ENONFINITE, "non-finite energy, virial or heat current");
+  if (h[kFlagSkin])
+    return fail(ctx, NEP_ESKIN,
+                "an atom moved more than skin/2 since its neighbour list was built (rebuild "
+                "more often or use a larger skin)");
+  return NEP_OK;
+}
+
 nep_status check_box(nep_ctx ctx, const double* box_host, double skin, System& probe) {
   if (!box_host) return fail(ctx, NEP_EINVAL, "box_host is NULL");
   if (!(skin >= 0.0) || !std::isfinite(skin)) return fail(ctx, NEP_EINVAL, "skin must be >= 0");
@@ -109,8 +137,8 @@ nep_status nep_create(nep_ctx* out, int device, void* hip_stream) {
   ctx->device = device;
   ctx->stream = (hipStream_t)hip_stream;
   hipError_t e;
-  if ((e = ctx->flags.ensure(kNumFlags)) != hipSuccess || (e = ctx->totals.ensure(16)) != hipSuccess ||
-      (e = hipMemset(ctx->flags.ptr, 0, sizeof(int) * kNumFlags)) != hipSuccess) {
+  if ((e = ctx->flags.ensure(kFlagWords)) != hipSuccess || (e = ctx->totals.ensure(16)) != hipSuccess ||
+      (e = hipMemset(ctx->flags.ptr, 0, sizeof(int) * kFlagWords)) != hipSuccess) {
     nep_destroy(ctx);
     return e == hipErrorOutOfMemory ? NEP_ENOMEM : NEP_EDEVICE;
   }
@@ -153,28 +181,7 @@ nep_status nep_set_stream(nep_ctx ctx, void* hip_stream) {
 
 nep_status nep_synchronize(nep_ctx ctx) {
   if (!ctx) return NEP_EINVAL;
-  DeviceGuard guard(ctx->device);
-  nep_status st = check_hip(ctx, hipStreamSynchronize(ctx->stream), "synchronizing");
-  if (st != NEP_OK) return st;
-  int h[kNumFlags];
-  st = check_hip(ctx, hipMemcpy(h, ctx->flags.ptr, sizeof(h), hipMemcpyDeviceToHost),
-                 "reading device flags");
-  if (st != NEP_OK) return st;
-  int any = 0;
-  for (int k = 0; k < kNumFlags; ++k) any |= h[k];
-  if (any) {
-    st = check_hip(ctx, hipMemset(ctx->flags.ptr, 0, sizeof(h)), "clearing device flags");
-    if (st != NEP_OK) return st;
-  }
-  if (h[kFlagOverflow]) return fail(ctx, NEP_EOVERFLOW, "an atom has more than max_neighbors neighbours");
-  if (h[kFlagImage]) return fail(ctx, NEP_EIMAGE, "a neighbour needs a lattice image beyond +-3 cells");
-  if (h[kFlagReverse]) return fail(ctx, NEP_EDEVICE, "neighbour list is not symmetric");
-  if (h[kFlagNonFinite]) return fail(ctx, NEP_ENONFINITE, "non-finite energy, virial or heat current");
-  if (h[kFlagSkin])
-    return fail(ctx, NEP_ESKIN,
-                "an atom moved more than skin/2 since its neighbour list was built (rebuild "
-                "more often or use a larger skin)");
-  return NEP_OK;
+  return synchronize_flags(ctx, nullptr);
 }
 
 int nep_num_descriptors(const nep_hyper* hyper) {

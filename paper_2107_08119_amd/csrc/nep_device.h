@@ -263,6 +263,180 @@ __device__ __forceinline__ double list_r2_shifted(double xj, double yj, double z
   return (dx * dx + dy * dy) + dz * dz;
 }
 
+// ------------------------------------------------- small periodic systems
+// The list of atom i over the atoms [j0, j0 + nj) of its cell and their
+// lattice images, by one wave.  The list is that of a serial loop over
+// (j, m0, m1, m2), m_a in [-K_a, K_a] the image of the wrapped frame, with the
+// exact predicate of list_r2: entries inside rc2_a first, then the rest inside
+// rc2_r.
+//
+// Bound: latency of the position loads and the scan over j.  The lanes take 64
+// atoms j at a time and each tests only the images that can reach atom i: the
+// fractional distance along cell vector a is ds_a + m_a, the atoms' distance
+// is at least |ds_a + m_a| times the cell's width along a, so m_a lies within
+// rc / width_a of -ds_a (one or two values unless the cell is thin).  The
+// reach is widened by 1e-6 and by 64 roundings of the atom's own coordinate
+// (only atoms within three cells of each other make entries), so the exact
+// test sees every image it would keep.  Testing all
+// (2K+1)^3 images in two passes, one per list part, took 97 us on the 216-atom
+// cell (now 9.6 us), 419 us on 64 structures of 8-256 atoms (now 36 us) and
+// 3.2 ms on 128 structures of 64-512 atoms (now 0.18 ms).
+//
+// stash: kImageStash words of LDS of this wave, where radial-only entries wait
+// for the number of angular ones; an atom with more of them scans once more.
+// nl_rm (may be NULL) receives the same entries per atom.  n_in, n_ang: pairs
+// inside the cutoffs rcr2, rca2 by their float32 distance (rcr2 = 0: not
+// counted).
+constexpr int kImageStash = 128;
+// Waves (atoms) per block: one for small systems, whose waves then spread over
+// all compute units.
+constexpr int kImageWaves = 4;
+inline int image_waves(int n) { return n < 4096 ? 1 : kImageWaves; }
+struct ImageList {
+  int na, nr;         // angular entries, radial-only entries
+  int n_ang, n_in;    // counts of the lane (to be summed over the wave)
+  bool overflow, bad_image;
+};
+__device__ __forceinline__ ImageList scan_images(
+    int n, int cap, int i, int j0, int nj, const double* __restrict__ pos,
+    const int* __restrict__ wrap, const double* h, const double* hi, int k0, int k1, int k2,
+    double rc2_r, double rc2_a, float rcr2, float rca2, uint32_t* __restrict__ nl,
+    uint32_t* __restrict__ nl_rm, uint32_t* stash) {
+  const int lane = threadIdx.x & 63;
+  const int K[3] = {k0, k1, k2};
+  const double xi = pos[i], yi = pos[n + i], zi = pos[2 * n + i];
+  const int wi[3] = {wrap[i], wrap[n + i], wrap[2 * n + i]};
+  double si[3], reach[3];
+  const double rc = sqrt(rc2_r);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const double raw = xi * hi[a] + yi * hi[3 + a] + zi * hi[6 + a];
+    si[a] = raw - (double)wi[a];
+    reach[a] = rc * sqrt(hi[a] * hi[a] + hi[3 + a] * hi[3 + a] + hi[6 + a] * hi[6 + a]) *
+                   (1.0 + 1e-6) +
+               1e-6 + 0x1p-46 * (fabs(xi * hi[a]) + fabs(yi * hi[3 + a]) + fabs(zi * hi[6 + a]));
+  }
+  ImageList out{0, 0, 0, 0, false, false};
+  // radial: 0 = one scan for both parts, 1 = the second scan of the radial part
+  auto scan = [&](int radial) {
+    int na = 0, nr = 0;
+    double nx, ny, nz;
+    int nw[3];
+    auto request = [&](int t) {  // the positions of the lane's next atom
+      const int j = j0 + (t < nj ? t : 0);
+      nx = pos[j];
+      ny = pos[n + j];
+      nz = pos[2 * n + j];
+      nw[0] = wrap[j];
+      nw[1] = wrap[n + j];
+      nw[2] = wrap[2 * n + j];
+    };
+    request(lane);
+    for (int base = 0; base < nj; base += 64) {
+      const int t = base + lane;
+      const int j = j0 + t;
+      const double xj = nx, yj = ny, zj = nz;
+      const int wj[3] = {nw[0], nw[1], nw[2]};
+      if (base + 64 < nj) request(t + 64);
+      int lo[3], hi3[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const double ds = ((xj * hi[a] + yj * hi[3 + a] + zj * hi[6 + a]) - (double)wj[a]) - si[a];
+        lo[a] = (int)fmax(-(double)K[a], ceil(-ds - reach[a]));
+        hi3[a] = (int)fmin((double)K[a], floor(reach[a] - ds));
+      }
+      if (t >= nj) hi3[0] = lo[0] - 1;
+      const int d0 = wi[0] - wj[0], d1 = wi[1] - wj[1], d2 = wi[2] - wj[2];
+      // visit(entry, r2, n0, n1, n2) for every image inside the radial cutoff
+      auto images = [&](auto&& visit) {
+        for (int m0 = lo[0]; m0 <= hi3[0]; ++m0)
+          for (int m1 = lo[1]; m1 <= hi3[1]; ++m1)
+            for (int m2 = lo[2]; m2 <= hi3[2]; ++m2) {
+              const int n0 = m0 + d0, n1 = m1 + d1, n2 = m2 + d2;
+              if (j == i && n0 == 0 && n1 == 0 && n2 == 0) continue;
+              const double r2 = list_r2(xj, yj, zj, xi, yi, zi, n0, n1, n2, h);
+              if (!(r2 < rc2_r)) continue;
+              if (n0 < -3 || n0 > 3 || n1 < -3 || n1 > 3 || n2 < -3 || n2 > 3) {
+                out.bad_image = true;
+                continue;
+              }
+              visit(pack_entry(j, n0, n1, n2), r2 < rc2_a);
+            }
+      };
+      int ca = 0, cr = 0;  // the lane's entries of each part
+      images([&](uint32_t e, bool in_a) {
+        ca += in_a ? 1 : 0;
+        cr += in_a ? 0 : 1;
+        if (rcr2 > 0.f && radial == 0) {
+          float dx, dy, dz;
+          image_displacement(e, xj, yj, zj, xi, yi, zi, h, dx, dy, dz);
+          const float r2f = pair_r2(dx, dy, dz);
+          const bool ang = in_a && r2f < rca2;
+          out.n_ang += ang ? 1 : 0;
+          out.n_in += ang || r2f < rcr2 ? 1 : 0;
+        }
+      });
+      // entries of the lanes before this one (both parts in one word) and in all
+      const int own = ca | (cr << 16);
+      int sum = own;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(sum, d, 64);
+        if (lane >= d) sum += y;
+      }
+      const int total = __shfl(sum, 63, 64);
+      int sa = na + ((sum - own) & 0xFFFF), sr = nr + ((sum - own) >> 16);
+      if (own)
+        images([&](uint32_t e, bool in_a) {
+          if (in_a) {
+            if (radial == 0) {
+              if (sa < cap) {
+                nl[(size_t)sa * n + i] = e;
+                if (nl_rm) nl_rm[(size_t)i * cap + sa] = e;
+              } else {
+                out.overflow = true;
+              }
+            }
+            ++sa;
+          } else {
+            if (radial == 0) {
+              if (sr < kImageStash) stash[sr] = e;
+            } else if (out.na + sr < cap) {
+              nl[(size_t)(out.na + sr) * n + i] = e;
+              if (nl_rm) nl_rm[(size_t)i * cap + out.na + sr] = e;
+            } else {
+              out.overflow = true;
+            }
+            ++sr;
+          }
+        });
+      na += total & 0xFFFF;
+      nr += total >> 16;
+    }
+    out.na = na;
+    out.nr = nr;
+  };
+  scan(0);
+  if (out.nr > kImageStash) {
+    scan(1);
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int t = lane; t < out.nr; t += 64) {
+      const int slot = out.na + t;
+      if (slot < cap) {
+        const uint32_t e = stash[t];
+        nl[(size_t)slot * n + i] = e;
+        if (nl_rm) nl_rm[(size_t)i * cap + slot] = e;
+      } else {
+        out.overflow = true;
+      }
+    }
+  }
+  return out;
+}
+
 // Sum of NQ doubles over a block in a fixed order: shuffle tree inside each
 // wave, then waves in index order.  The result is valid in threads < NQ
 // (thread q holds quantity q).

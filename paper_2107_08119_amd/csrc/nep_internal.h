@@ -100,6 +100,9 @@ enum Flag {
   kFlagSkin = 4,  // an evaluation saw an atom more than skin/2 from its list-build position
   kNumFlags = 5
 };
+// Words of the flag buffer; the 64-bit totals of a dataset's pairs lie at word
+// kPairTotals, so that one copy brings both to the host.
+constexpr int kPairTotals = 8, kFlagWords = 12;
 
 // 1 eV/A acting on 1 amu, in A/fs^2; and 1 amu A^2/fs^2 in eV.
 constexpr double kAccel = 1.602176634e-19 / 1.66053906660e-27 * 1.0e-10;
@@ -240,7 +243,7 @@ struct nep_ctx_s {
   nep::DevBuf<double> species_wd;  // [n] the same in float64 (descriptor sums)
   nep::DevBuf<double> masses;     // [n] amu
   nep::DevBuf<double> totals;     // [16]
-  nep::DevBuf<int> flags;         // [kNumFlags]
+  nep::DevBuf<int> flags;         // [kFlagWords]: kNumFlags flags, two 64-bit pair totals
   // molecular dynamics state
   bool md_forces_valid = false;
   const double* md_pos = nullptr;
@@ -298,6 +301,8 @@ struct nep_dataset_s {
   nep::DevBuf<float2> pnorm;     // [N] largest row 1-norm of the force rows, of the virial rows
   nep::DevBuf<float2> tbound;    // [T] fixed-point bound factors of forces and virials
   int n_tiles = 0, tile_max = 0;
+  bool geometry_stale = false;   // positions replaced since the geometry cache was prepared
+  bool population_used = false;  // a population call has run: set_positions prepares the cache
   long long pairs_r = 0, pairs_a = 0;  // pairs inside r_c^R, inside r_c^A (geometry cache)
   int tile_kc = 0;               // individuals per contraction launch the tiles were sized for
   int pop_variant = 1;         // network kernel shape: 0, 1, 2 = 16, 32, 64 atoms per wave
@@ -370,8 +375,9 @@ void prepare_system_geometry(System& s, const double* box_host, double rc_r, dou
 // Expand the list into the caller's numbering (see nep_get_neighbors).
 hipError_t unpack_neighbors(nep_ctx ctx, int* nbr, int* img, int* cnt_r, int* cnt_a, int* rev);
 // Reverse slots of a list (any system, global atom indices).
-void launch_reverse(nep_ctx ctx, int n, int cap, const uint32_t* nl, const int* cnt_r,
-                    const int* cnt_a, int* rev);
+// nl_rm: the same entries per atom, [n][cap].
+void launch_reverse(nep_ctx ctx, int n, int cap, const uint32_t* nl, const uint32_t* nl_rm,
+                    const int* cnt_r, const int* cnt_a, int* rev);
 
 // force.hip
 bool have_force_variant(const nep_hyper& h);
@@ -469,6 +475,11 @@ struct DeviceGuard {
 // helpers (nep_api.hip)
 nep_status fail(nep_ctx ctx, nep_status code, const std::string& msg);
 nep_status check_hip(nep_ctx ctx, hipError_t e, const char* what);
+// nep_synchronize; pairs (may be NULL) receives the two pair totals.
+nep_status synchronize_flags(nep_ctx ctx, unsigned long long* pairs);
+inline unsigned long long* pair_totals(nep_ctx ctx) {
+  return reinterpret_cast<unsigned long long*>(ctx->flags.ptr + kPairTotals);
+}
 int n_des_of(const nep_hyper& h);
 // One force evaluation of the internal state (positions sys.pos_s, velocities
 // sys.vel_s when vel is true): pass 1 and pass 2 into the internal U, F, W, J,

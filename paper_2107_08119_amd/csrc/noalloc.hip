@@ -81,7 +81,14 @@ bool carve(char* base, const System& geo, int n, int cap, System& s, nep_ctx_s& 
   k.take(c.J, n3);
   k.take(c.partials, gather_blocks(n) * 16 + 16);
   *used = k.off;
-  return k.ok;
+  const bool fits = k.ok;
+  // without cells the per-atom copy of the list only speeds the reverse search
+  // up: it is used where the workspace has room left for it
+  if (fits && !geo.use_cells) {
+    k.take(s.nl_rm, ncap);
+    if (!k.ok) s.nl_rm.set_view(nullptr, 0);
+  }
+  return fits;
 }
 
 // The context's own system, buffers and species, put back on every return.

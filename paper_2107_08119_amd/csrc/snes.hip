@@ -9,6 +9,7 @@
 // (atom, individual) pair; a population gather turns the partials into per-
 // atom loss terms; float64 sums over each structure and then over structures
 // give the loss components of each individual, in a fixed order.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -48,70 +49,58 @@ __global__ void k_ds_wrap(int N, double* __restrict__ pos, const double* __restr
     wrap[a * N + i] = (int)floor(r[0] * Hi[a] + r[1] * Hi[3 + a] + r[2] * Hi[6 + a]);
 }
 
-// One wave per atom: every atom j of the same structure and every image m in
-// [-K, K]^3 of the wrapped frame, numbered in (j, m0, m1, m2) order; 64 such
-// candidates are tested at a time and a ballot keeps the serial order.  The
-// angular-range entries come first (first pass), then the rest.
-__global__ __launch_bounds__(256) void k_ds_build(
+// One wave per atom over the atoms of its structure and their lattice images
+// (scan_images), with the pairs inside the cutoffs counted per atom as
+// k_pair_classes does.  Also clears the two pair totals.
+__global__ __launch_bounds__(64 * kImageWaves) void k_ds_build(
     int N, int cap, const double* __restrict__ pos, const double* __restrict__ boxes,
-    const int* __restrict__ struct_of, const int* __restrict__ off, const int* __restrict__ kimg,
-    const int* __restrict__ wrap, double rc2_r, double rc2_a, uint32_t* __restrict__ nl,
-    int* __restrict__ cnt_r, int* __restrict__ cnt_a, int* __restrict__ flags) {
-  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = gid / 64;
-  const int k = gid % 64;
+    const double* __restrict__ boxinv, const int* __restrict__ struct_of,
+    const int* __restrict__ off, const int* __restrict__ kimg, const int* __restrict__ wrap,
+    double rc2_r, double rc2_a, float rcr2, float rca2, uint32_t* __restrict__ nl,
+    uint32_t* __restrict__ nl_rm, int* __restrict__ cnt_r, int* __restrict__ cnt_a,
+    int* __restrict__ n_in, int* __restrict__ n_ang, unsigned long long* __restrict__ totals,
+    int* __restrict__ flags) {
+  __shared__ uint32_t stash[kImageWaves][kImageStash];
+  const int w = (int)threadIdx.x / 64;
+  const int i = (int)(blockIdx.x * (blockDim.x / 64)) + w;
+  if (blockIdx.x == 0 && threadIdx.x < 2) totals[threadIdx.x] = 0;
   if (i >= N) return;  // whole waves leave together
-  const unsigned long long below = (1ull << k) - 1ull;
   const int s = struct_of[i];
-  const double* H = boxes + 9 * (size_t)s;
-  const int j0 = off[s], nj = off[s + 1] - off[s];
-  const int K0 = kimg[3 * s], K1 = kimg[3 * s + 1], K2 = kimg[3 * s + 2];
-  const int w1n = 2 * K1 + 1, w2n = 2 * K2 + 1;
-  const int nimg = (2 * K0 + 1) * w1n * w2n;
-  const int total = nj * nimg;
-  const double xi = pos[i], yi = pos[N + i], zi = pos[2 * N + i];
-  const int wi0 = wrap[i], wi1 = wrap[N + i], wi2 = wrap[2 * N + i];
-  int count = 0;
-  bool overflow = false, bad_image = false;
-  for (int pass = 0; pass < 2; ++pass) {
-    for (int base = 0; base < total; base += 64) {
-      const int c = base + k;
-      bool keep = false;
-      uint32_t entry = 0;
-      if (c < total) {
-        const int j = j0 + c / nimg;
-        const int mi = c % nimg;
-        const int m0 = mi / (w1n * w2n) - K0;
-        const int m1 = (mi / w2n) % w1n - K1;
-        const int m2 = mi % w2n - K2;
-        const int n0 = m0 + wi0 - wrap[j], n1 = m1 + wi1 - wrap[N + j], n2 = m2 + wi2 - wrap[2 * N + j];
-        if (!(j == i && n0 == 0 && n1 == 0 && n2 == 0)) {
-          const double r2 =
-              list_r2(pos[j], pos[N + j], pos[2 * N + j], xi, yi, zi, n0, n1, n2, H);
-          const bool in_a = r2 < rc2_a;
-          keep = pass == 0 ? in_a : (!in_a && r2 < rc2_r);
-          if (keep && (n0 < -3 || n0 > 3 || n1 < -3 || n1 > 3 || n2 < -3 || n2 > 3)) {
-            bad_image = true;
-            keep = false;
-          }
-          entry = pack_entry(j, n0, n1, n2);
-        }
-      }
-      const unsigned long long ball = __ballot(keep);
-      if (keep) {
-        const int slot = count + __popcll(ball & below);
-        if (slot < cap)
-          nl[(size_t)slot * N + i] = entry;
-        else
-          overflow = true;
-      }
-      count += __popcll(ball);
-    }
-    if (pass == 0 && k == 0) cnt_a[i] = min(count, cap);
+  ImageList l = scan_images(N, cap, i, off[s], off[s + 1] - off[s], pos, wrap,
+                            boxes + 9 * (size_t)s, boxinv + 9 * (size_t)s, kimg[3 * s],
+                            kimg[3 * s + 1], kimg[3 * s + 2], rc2_r, rc2_a, rcr2, rca2, nl, nl_rm,
+                            stash[w]);
+  for (int d = 32; d > 0; d >>= 1) {
+    l.n_in += __shfl_xor(l.n_in, d, 64);
+    l.n_ang += __shfl_xor(l.n_ang, d, 64);
   }
-  if (k == 0) cnt_r[i] = min(count, cap);
-  if (overflow) flags[kFlagOverflow] = 1;
-  if (bad_image) flags[kFlagImage] = 1;
+  if ((threadIdx.x & 63) == 0) {
+    cnt_a[i] = min(l.na, cap);
+    cnt_r[i] = min(l.na + l.nr, cap);
+    n_in[i] = l.n_in;
+    n_ang[i] = l.n_ang;
+  }
+  if (l.overflow) flags[kFlagOverflow] = 1;
+  if (l.bad_image) flags[kFlagImage] = 1;
+}
+
+// totals += the sums of n_in and n_ang (whole numbers: any order).
+__global__ __launch_bounds__(kBlock) void k_ds_pair_totals(int N, const int* __restrict__ n_in,
+                                                           const int* __restrict__ n_ang,
+                                                           unsigned long long* __restrict__ totals) {
+  unsigned long long a = 0, b = 0;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < N; i += gridDim.x * blockDim.x) {
+    a += (unsigned long long)n_in[i];
+    b += (unsigned long long)n_ang[i];
+  }
+  for (int d = 32; d > 0; d >>= 1) {
+    a += __shfl_xor(a, d, 64);
+    b += __shfl_xor(b, d, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(&totals[0], a);
+    atomicAdd(&totals[1], b);
+  }
 }
 
 // ------------------------------------------------- population loss terms
@@ -393,21 +382,38 @@ void invert_box(const double* H, double* Hi) {
   Hi[8] = (a * e - b * d) / det;
 }
 
-// Wrap the dataset's positions and build its lists and reverse slots.
+// Wrap the dataset's positions and build its lists and reverse slots.  The
+// row-major list copy of the reverse search lies in pcidx, which the geometry
+// cache fills afterwards.
 hipError_t build_dataset_lists(nep_ctx ctx, nep_dataset ds) {
   const int N = ds->N;
   hipStream_t st = ctx->stream;
+  hipError_t e = ds->pcidx.ensure((size_t)N * ds->cap);
+  if (e == hipSuccess) e = ds->pn_ang.ensure(N);
+  if (e == hipSuccess) e = ds->pn_in.ensure(N);
+  if (e != hipSuccess) return e;
+  const float rca = (float)ds->rc_a, rcr = (float)ds->rc_r;
+  uint32_t* nl_rm = reinterpret_cast<uint32_t*>(ds->pcidx.ptr);
   k_ds_wrap<<<blocks_for(N, kBlock), kBlock, 0, st>>>(N, ds->pos.ptr, ds->boxes.ptr,
                                                       ds->boxinv.ptr, ds->struct_of.ptr,
                                                       ds->wrap.ptr);
-  k_ds_build<<<blocks_for((size_t)N * 64, 256), 256, 0, st>>>(
-      N, ds->cap, ds->pos.ptr, ds->boxes.ptr, ds->struct_of.ptr, ds->off.ptr, ds->kimg.ptr,
-      ds->wrap.ptr, ds->rc_r * ds->rc_r, ds->rc_a * ds->rc_a, ds->nl.ptr, ds->cnt_r.ptr,
-      ds->cnt_a.ptr, ctx->flags.ptr);
-  launch_reverse(ctx, N, ds->cap, ds->nl.ptr, ds->cnt_r.ptr, ds->cnt_a.ptr, ds->rev.ptr);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return prepare_dataset_geometry(ctx, ds);
+  const int waves = image_waves(N);
+  k_ds_build<<<blocks_for(N, waves), 64 * waves, 0, st>>>(
+      N, ds->cap, ds->pos.ptr, ds->boxes.ptr, ds->boxinv.ptr, ds->struct_of.ptr, ds->off.ptr,
+      ds->kimg.ptr, ds->wrap.ptr, ds->rc_r * ds->rc_r, ds->rc_a * ds->rc_a, rcr * rcr, rca * rca,
+      ds->nl.ptr, nl_rm, ds->cnt_r.ptr, ds->cnt_a.ptr, ds->pn_in.ptr, ds->pn_ang.ptr,
+      pair_totals(ctx), ctx->flags.ptr);
+  launch_reverse(ctx, N, ds->cap, ds->nl.ptr, nl_rm, ds->cnt_r.ptr, ds->cnt_a.ptr, ds->rev.ptr);
+  ds->geometry_stale = true;
+  return hipGetLastError();
+}
+
+// The geometry cache of the population kernels for the current positions.
+hipError_t ensure_geometry(nep_ctx ctx, nep_dataset ds) {
+  if (!ds->geometry_stale) return hipSuccess;
+  hipError_t e = prepare_dataset_geometry(ctx, ds);
+  if (e == hipSuccess) ds->geometry_stale = false;
+  return e;
 }
 
 nep_status check_dataset(nep_ctx ctx, nep_dataset ds) {
@@ -555,6 +561,7 @@ nep_status nep_dataset_create(nep_ctx ctx, int n_struct, const int* n_atoms_host
   up(ds->w_tar.ptr, virial_host, sizeof(double) * 6 * S);
   up(ds->has_v.ptr, hv.data(), sizeof(int) * S);
   if (e == hipSuccess) e = build_dataset_lists(ctx, ds);
+  if (e == hipSuccess) e = ensure_geometry(ctx, ds);
   if (e != hipSuccess) {
     nep_dataset_destroy(ds);
     return check_hip(ctx, e, "creating the dataset");
@@ -618,8 +625,24 @@ nep_status nep_dataset_set_positions(nep_ctx ctx, nep_dataset ds, const double* 
   hipError_t e = hipMemcpyAsync(ds->pos.ptr, pos_dev, sizeof(double) * 3 * ds->N,
                                 hipMemcpyDeviceToDevice, ctx->stream);
   if (e == hipSuccess) e = build_dataset_lists(ctx, ds);
+  if (e == hipSuccess && ds->population_used) {
+    e = ensure_geometry(ctx, ds);
+    if (e == hipSuccess) return nep_synchronize(ctx);
+  }
   if (e != hipSuccess) return check_hip(ctx, e, "rebuilding dataset lists");
-  return nep_synchronize(ctx);
+  // A dataset that no population call has used (differentiation at moving
+  // positions) needs the pair totals only: preparing the population operands
+  // took 0.35 ms of the 1.1 ms of an energy-and-gradient call at new positions
+  // of 64 structures.
+  k_ds_pair_totals<<<std::min(64u, blocks_for(ds->N, kBlock)), kBlock, 0, ctx->stream>>>(
+      ds->N, ds->pn_in.ptr, ds->pn_ang.ptr, pair_totals(ctx));
+  unsigned long long pairs[2] = {0, 0};
+  const nep_status st = synchronize_flags(ctx, pairs);
+  if (st != NEP_EDEVICE) {
+    ds->pairs_r = (long long)pairs[0];
+    ds->pairs_a = (long long)pairs[1];
+  }
+  return st;
 }
 
 nep_status nep_dataset_get_positions(nep_ctx ctx, nep_dataset ds, double* pos_dev) {
@@ -692,7 +715,9 @@ nep_status snes_eval_population(nep_ctx ctx, nep_dataset ds, int n_pop, const fl
   if (!population_fits(ds))
     return fail(ctx, NEP_EINVAL, "a structure has more atoms than the population kernels hold");
   DeviceGuard guard(ctx->device);
-  hipError_t e = ensure_population(ds, n_pop);
+  hipError_t e = ensure_geometry(ctx, ds);
+  ds->population_used = true;
+  if (e == hipSuccess) e = ensure_population(ds, n_pop);
   if (e != hipSuccess) return check_hip(ctx, e, "allocating population workspace");
   e = timed(ctx, 0, [&] {
     return enqueue_population_loss(ctx, ds, n_pop, Z_dev, lambda_host, loss_dev, ds->pop_variant);
@@ -748,7 +773,9 @@ nep_status snes_autotune(nep_ctx ctx, nep_dataset ds, int n_pop, const float* Z_
   if (!population_fits(ds))
     return fail(ctx, NEP_EINVAL, "a structure has more atoms than the population kernels hold");
   DeviceGuard guard(ctx->device);
-  hipError_t e = ensure_population(ds, n_pop);
+  hipError_t e = ensure_geometry(ctx, ds);
+  ds->population_used = true;
+  if (e == hipSuccess) e = ensure_population(ds, n_pop);
   if (e != hipSuccess) return check_hip(ctx, e, "allocating population workspace");
   const bool timing = ctx->timer.on;
   ctx->timer.on = false;
@@ -814,7 +841,9 @@ nep_status snes_run(nep_ctx ctx, nep_dataset ds, int n_par, int n_pop, float* m_
   if (!(eta_m > 0.0)) eta_m = 1.0;
   if (!(eta_s > 0.0)) eta_s = (3.0 + std::log((double)n_par)) / (5.0 * std::sqrt((double)n_par));
   DeviceGuard guard(ctx->device);
-  hipError_t e = ensure_population(ds, n_pop);
+  hipError_t e = ensure_geometry(ctx, ds);
+  ds->population_used = true;
+  if (e == hipSuccess) e = ensure_population(ds, n_pop);
   if (e == hipSuccess) e = ctx->gen_counter.ensure(2);
   if (e != hipSuccess) return check_hip(ctx, e, "allocating SNES workspace");
   SnesGraph& G = ctx->snes_graph;
