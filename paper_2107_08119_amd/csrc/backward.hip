@@ -14,9 +14,11 @@
 //
 // k_grad_atoms evaluates q and delta q per atom (lanes split the neighbour
 // slots, as in the force kernel; delta q uses the same factorised angular
-// form) and writes (alpha, s, beta, q, delta q, g) per atom.  k_grad_blocks
-// contracts them over blocks of atoms into float64 partial gradients, and
-// k_grad_final adds the blocks in order.
+// form) and writes (alpha, s, beta, q, delta q, g) per atom.  k_grad_contract
+// sums them over the atoms of each wave in float64 on the matrix cores, and
+// k_grad_final adds the blocks in order and applies the factors w2.
+#include <algorithm>
+
 #include "nep_device.h"
 
 namespace nep {
@@ -25,7 +27,10 @@ namespace {
 inline unsigned blocks_for(size_t work, int block) { return (unsigned)((work + block - 1) / block); }
 
 constexpr int kLanes = 4;
-constexpr int kChunk = 64;  // atoms per block in the contraction
+constexpr int kChunk = 16;      // atoms per step of a wave in the contraction
+constexpr int kMaxBlocks = 256;  // its blocks: one per compute unit
+// rows of the per-atom record: padded so that 16 atoms are read as float4
+inline int rec_stride(int n) { return (n + kChunk - 1) / kChunk * kChunk; }
 
 template <int NR, int NA, int LMAX, int NNEU>
 struct GradLayout {
@@ -45,7 +50,8 @@ __global__ __launch_bounds__(kBlock) void k_grad_atoms(
     const int* __restrict__ cnt_r, const int* __restrict__ cnt_a,
     const double* __restrict__ boxes, const int* __restrict__ struct_of,
     const float* __restrict__ zpar, float rc_r, float rc_a, const double* __restrict__ gE,
-    const float* __restrict__ gF, float* __restrict__ rec) {
+    const float* __restrict__ gF, const float* __restrict__ F, double* __restrict__ gpos, int ld,
+    float* __restrict__ rec) {
   using Lay = GradLayout<NR, NA, LMAX, NNEU>;
   constexpr int NLM = (LMAX + 1) * (LMAX + 1) - 1;
   constexpr int NDES = Lay::NDES;
@@ -166,6 +172,10 @@ __global__ __launch_bounds__(kBlock) void k_grad_atoms(
   const float* w1 = sz;
   const float* b1 = sz + NNEU * NDES;
   const float ga = (active && gE) ? (float)gE[struct_of[i]] : 0.f;
+  if (gpos && active && lane < 3) {  // energy part of the position gradient, -gE F
+    const size_t t = (size_t)lane * n + i;
+    gpos[t] = gE ? -gE[struct_of[i]] * (double)F[t] : 0.0;
+  }
   if (active) {
     for (int mu = lane; mu < NNEU; mu += L) {
       float act = -b1[mu], t = 0.f;
@@ -178,74 +188,154 @@ __global__ __launch_bounds__(kBlock) void k_grad_atoms(
       const float inv = __builtin_amdgcn_rcpf(1.f + ea);
       const float xm = copysignf((1.f - ea) * inv, act);
       const float sm = 4.f * ea * inv * inv;
-      rec[(size_t)(Lay::ALPHA + mu) * n + i] = sm * (ga + 2.f * xm * t);
-      rec[(size_t)(Lay::S + mu) * n + i] = sm;
-      rec[(size_t)(Lay::BETA + mu) * n + i] = ga * xm - sm * t;
+      rec[(size_t)(Lay::ALPHA + mu) * ld + i] = sm * (ga + 2.f * xm * t);
+      rec[(size_t)(Lay::S + mu) * ld + i] = sm;
+      rec[(size_t)(Lay::BETA + mu) * ld + i] = ga * xm - sm * t;
     }
     for (int v = lane; v < NDES; v += L) {
-      rec[(size_t)(Lay::Q + v) * n + i] = q[v];
-      rec[(size_t)(Lay::DQ + v) * n + i] = dq[v];
+      rec[(size_t)(Lay::Q + v) * ld + i] = q[v];
+      rec[(size_t)(Lay::DQ + v) * ld + i] = dq[v];
     }
-    if (lane == 0) rec[(size_t)Lay::G * n + i] = ga;
+    if (lane == 0) rec[(size_t)Lay::G * ld + i] = ga;
   }
 }
 
-// Block b contracts atoms [b*kChunk, (b+1)*kChunk) into out[b][N_par] (float64).
+// out[block][N_par] = sums over the block's atoms, float64:
+//   w1 (mu, k): alpha_mu q_k - s_mu dq_k;  b1: alpha_mu;  w2: beta_mu;  b2: g.
+// Bound: the read of the records (596 bytes per atom).  The w1 sums are two
+// products of 30 x atoms and atoms x 29 matrices, done by 16x16x4 float64
+// MFMA steps: a lane reads four consecutive atoms of its row as one float4
+// (the K step e takes atom 4 (l/16) + e), converts them, and keeps 2 x 2 tiles
+// for all its atoms; column 29 of the second operand is 1, so that it collects
+// the b1 sums.  The grid is at most one block per compute unit, each striding
+// over the atoms, so k_grad_final adds 256 partial gradients at most.  With
+// one thread per parameter over 64-atom blocks and 576 partial gradients this
+// took 59 us, and adding them in one chain per parameter 145 us, on 36,863
+// atoms; now 11 and 4 us.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <int NR, int NA, int LMAX, int NNEU>
-__global__ __launch_bounds__(kBlock) void k_grad_blocks(int n, const float* __restrict__ rec,
-                                                         const float* __restrict__ zpar,
-                                                         double* __restrict__ out) {
+__global__ __launch_bounds__(kBlock) void k_grad_contract(int n, int ld,
+                                                          const float* __restrict__ rec,
+                                                          double* __restrict__ out) {
   using Lay = GradLayout<NR, NA, LMAX, NNEU>;
   constexpr int NDES = Lay::NDES;
   constexpr int NPAR = (NDES + 2) * NNEU + 1;
-  __shared__ float sr[Lay::FIELDS][kChunk];
-  const int a0 = blockIdx.x * kChunk;
-  const int na = min(kChunk, n - a0);
-  for (int t = threadIdx.x; t < Lay::FIELDS * kChunk; t += blockDim.x) {
-    const int f = t / kChunk, a = t % kChunk;
-    sr[f][a] = a < na ? rec[(size_t)f * n + a0 + a] : 0.f;
+  static_assert(NNEU <= 32 && NDES < 32, "two 16-wide tiles, one column spare");
+  constexpr int kW = kBlock / 64;
+  __shared__ double tile[kW][32][33];
+  __shared__ double side[kW][33];  // beta sums per neuron, then the g sum
+  const int w = threadIdx.x / 64, l = threadIdx.x & 63, col = l & 15, h = l >> 4;
+  f64x4 acc[2][2];
+  double beta[2] = {0.0, 0.0}, gsum = 0.0;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) acc[t][u] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const int chunks = (n + kChunk - 1) / kChunk;
+  for (int c = blockIdx.x * kW + w; c < chunks; c += gridDim.x * kW) {
+    const int a0 = c * kChunk + 4 * h;  // the lane's four atoms
+    auto rows = [&](int field, int row, int last) {
+      return *reinterpret_cast<const float4*>(rec + (size_t)(field + min(row, last)) * ld + a0);
+    };
+    float4 v[2][5];
+    const float4 g4 = rows(Lay::G, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int r = 16 * t + col;  // neuron row and descriptor column of the lane
+      v[t][0] = rows(Lay::ALPHA, r, NNEU - 1);
+      v[t][1] = rows(Lay::S, r, NNEU - 1);
+      v[t][2] = rows(Lay::BETA, r, NNEU - 1);
+      v[t][3] = rows(Lay::Q, r, NDES - 1);
+      v[t][4] = rows(Lay::DQ, r, NDES - 1);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = a0 + e < n;  // the padding of the rows is never written
+      auto at = [&](const float4& x) {
+        const float y = e == 0 ? x.x : (e == 1 ? x.y : (e == 2 ? x.z : x.w));
+        return in ? (double)y : 0.0;
+      };
+      double alpha[2], s[2], q[2], dq[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int k = 16 * t + col;
+        alpha[t] = at(v[t][0]);
+        s[t] = -at(v[t][1]);
+        beta[t] += at(v[t][2]);
+        q[t] = k < NDES ? at(v[t][3]) : (k == NDES && in ? 1.0 : 0.0);
+        dq[t] = k < NDES ? at(v[t][4]) : 0.0;
+      }
+      gsum += at(g4);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(alpha[t], q[u], acc[t][u], 0, 0, 0);
+          acc[t][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(s[t], dq[u], acc[t][u], 0, 0, 0);
+        }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) tile[w][16 * t + 4 * r + h][16 * u + col] = acc[t][u][r];
+#pragma unroll
+  for (int d = 16; d < 64; d <<= 1) {  // the four atom groups of the wave
+    beta[0] += __shfl_xor(beta[0], d, 64);
+    beta[1] += __shfl_xor(beta[1], d, 64);
+    gsum += __shfl_xor(gsum, d, 64);
+  }
+  if (h == 0) {
+    side[w][col] = beta[0];
+    side[w][16 + col] = beta[1];
+    if (col == 0) side[w][32] = gsum;
   }
   __syncthreads();
-  const float* w2 = zpar + NNEU * NDES + NNEU;
-  for (int p = threadIdx.x; p < NPAR; p += blockDim.x) {
-    double acc = 0.0;
-    if (p < NNEU * NDES) {
-      const int mu = p / NDES, k = p % NDES;
-      for (int a = 0; a < na; ++a)
-        acc += (double)(sr[Lay::ALPHA + mu][a] * sr[Lay::Q + k][a] -
-                        sr[Lay::S + mu][a] * sr[Lay::DQ + k][a]);
-      acc *= (double)w2[mu];
-    } else if (p < NNEU * NDES + NNEU) {
-      const int mu = p - NNEU * NDES;
-      for (int a = 0; a < na; ++a) acc += (double)sr[Lay::ALPHA + mu][a];
-      acc *= -(double)w2[mu];
-    } else if (p < NNEU * NDES + 2 * NNEU) {
-      const int mu = p - NNEU * NDES - NNEU;
-      for (int a = 0; a < na; ++a) acc += (double)sr[Lay::BETA + mu][a];
-    } else {
-      for (int a = 0; a < na; ++a) acc -= (double)sr[Lay::G][a];
+  for (int p = threadIdx.x; p < NPAR; p += kBlock) {
+    double s = 0.0;
+    for (int u = 0; u < kW; ++u) {
+      if (p < NNEU * NDES)
+        s += tile[u][p / NDES][p % NDES];
+      else if (p < NNEU * (NDES + 1))
+        s += tile[u][p - NNEU * NDES][NDES];
+      else
+        s += p < NPAR - 1 ? side[u][p - NNEU * (NDES + 1)] : side[u][32];
     }
-    out[(size_t)blockIdx.x * NPAR + p] = acc;
+    out[(size_t)blockIdx.x * NPAR + p] = s;
   }
 }
 
-__global__ void k_grad_final(int nblocks, int npar, const double* __restrict__ part,
-                             double* __restrict__ grad, float* __restrict__ grad32) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= npar) return;
+// grad[p] = factor_p sum_b part[b][p]: 64 parameters per block, 16 threads per
+// parameter over consecutive runs of partial gradients, then the runs in order.
+template <int NDES, int NNEU>
+__global__ __launch_bounds__(1024) void k_grad_final(int nblocks, const float* __restrict__ zpar,
+                                                     const double* __restrict__ part,
+                                                     double* __restrict__ grad,
+                                                     float* __restrict__ grad32) {
+  constexpr int NPAR = (NDES + 2) * NNEU + 1;
+  __shared__ double run[16][64];
+  const int pl = threadIdx.x & 63, u = threadIdx.x >> 6;
+  const int p = blockIdx.x * 64 + pl;
+  const int len = (nblocks + 15) / 16, b1 = min(nblocks, (u + 1) * len);
   double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += part[(size_t)b * npar + p];
+  if (p < NPAR)
+#pragma unroll 8
+    for (int b = u * len; b < b1; ++b) s += part[(size_t)b * NPAR + p];
+  run[u][pl] = s;
+  __syncthreads();
+  if (u != 0 || p >= NPAR) return;
+  for (int t = 1; t < 16; ++t) s += run[t][pl];
+  const float* w2 = zpar + NNEU * (NDES + 1);
+  if (p < NNEU * NDES)
+    s *= (double)w2[p / NDES];
+  else if (p < NNEU * (NDES + 1))
+    s *= -(double)w2[p - NNEU * NDES];
+  else if (p == NPAR - 1)
+    s = -s;
   grad[p] = s;
   if (grad32) grad32[p] = (float)s;
-}
-
-__global__ void k_grad_positions(int n, const int* __restrict__ struct_of,
-                                 const double* __restrict__ gE, const float* __restrict__ F,
-                                 double* __restrict__ gpos) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 3 * n) return;
-  const int i = t % n;
-  gpos[t] = gE ? -gE[struct_of[i]] * (double)F[t] : 0.0;
 }
 
 }  // namespace
@@ -256,8 +346,10 @@ hipError_t launch_backward(nep_ctx ctx, nep_dataset ds, const float* z, const do
   using Lay = GradLayout<9, 5, 4, 30>;
   const int N = ds->N;
   constexpr int NPAR = (Lay::NDES + 2) * 30 + 1;
-  const unsigned nblk = blocks_for((size_t)N, kChunk);
-  hipError_t e = ds->grad_rec.ensure((size_t)Lay::FIELDS * N);
+  const int ld = rec_stride(N);
+  const unsigned nblk =
+      std::min((unsigned)kMaxBlocks, blocks_for((size_t)N, kChunk * (kBlock / 64)));
+  hipError_t e = ds->grad_rec.ensure((size_t)Lay::FIELDS * ld);
   if (e == hipSuccess) e = ds->grad_part.ensure((size_t)nblk * NPAR);
   if (e != hipSuccess) return e;
   launch_kernel(ctx, true, false, k_grad_atoms<9, 5, 4, 30, kLanes>,
@@ -265,14 +357,11 @@ hipError_t launch_backward(nep_ctx ctx, nep_dataset ds, const float* z, const do
                 (const double*)ds->pos.ptr, (const uint32_t*)ds->nl.ptr, (const int*)ds->cnt_r.ptr,
                 (const int*)ds->cnt_a.ptr, (const double*)ds->boxes.ptr,
                 (const int*)ds->struct_of.ptr, z, (float)ctx->hyper.rc_radial,
-                (float)ctx->hyper.rc_angular, gE, gF, ds->grad_rec.ptr);
-  launch_kernel(ctx, false, false, k_grad_blocks<9, 5, 4, 30>, dim3(nblk), dim3(kBlock), N,
-                (const float*)ds->grad_rec.ptr, z, ds->grad_part.ptr);
-  launch_kernel(ctx, false, gpos == nullptr, k_grad_final, dim3(blocks_for(NPAR, kBlock)),
-                dim3(kBlock), (int)nblk, NPAR, (const double*)ds->grad_part.ptr, grad, grad32);
-  if (gpos)
-    launch_kernel(ctx, false, true, k_grad_positions, dim3(blocks_for((size_t)3 * N, kBlock)),
-                  dim3(kBlock), N, (const int*)ds->struct_of.ptr, gE, F, gpos);
+                (float)ctx->hyper.rc_angular, gE, gF, F, gpos, ld, ds->grad_rec.ptr);
+  launch_kernel(ctx, false, false, k_grad_contract<9, 5, 4, 30>, dim3(nblk), dim3(kBlock), N, ld,
+                (const float*)ds->grad_rec.ptr, ds->grad_part.ptr);
+  launch_kernel(ctx, false, true, k_grad_final<Lay::NDES, 30>, dim3(blocks_for(NPAR, 64)),
+                dim3(1024), (int)nblk, z, (const double*)ds->grad_part.ptr, grad, grad32);
   return hipGetLastError();
 }
 

@@ -319,7 +319,7 @@ struct nep_dataset_s {
   nep::DevBuf<double> atom_terms;   // [10][N] per-atom U and W (forward)
   nep::DevBuf<double> struct_sq;    // [pop][S][3] squared errors per structure
   // backward workspace
-  nep::DevBuf<float> grad_rec;      // [fields][N]
+  nep::DevBuf<float> grad_rec;      // [fields][N padded to 16]
   nep::DevBuf<double> grad_part;    // [blocks][N_par]
   void release_cache() {
     prec.release();
