@@ -16,6 +16,8 @@
 // systems, the neighbours' positions); no atomics touch forces and the result is
 // reproducible bit for bit.  Totals are summed in float64 per block and the
 // block sums are added in block order by a one-block kernel.
+#include <type_traits>
+
 #include "nep_terms.h"
 
 namespace nep {
@@ -261,15 +263,11 @@ __device__ __forceinline__ void block_partials(double (&v)[NQ], double* __restri
   if (threadIdx.x < NQ) partials[(size_t)block * NQ + threadIdx.x] = s;
 }
 
-// Block x reduces set x: out[x][q] = sum over blocks b (in order of b) of
-// partials[x][b][q].
+// out[q] = sum over blocks b (in order of b) of partials[b][q], by one block.
 template <int NQ>
-__global__ __launch_bounds__(kBlock) void k_finalize(int nblocks, const double* __restrict__ partials,
-                                                      double* __restrict__ out,
-                                                      int* __restrict__ flags) {
+__device__ __forceinline__ void finalize_set(int nblocks, const double* __restrict__ partials,
+                                             double* __restrict__ out, int* __restrict__ flags) {
   __shared__ double sw[kBlock / 64][NQ];
-  partials += (size_t)blockIdx.x * nblocks * NQ;
-  out += (size_t)blockIdx.x * NQ;
   double acc[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
@@ -281,6 +279,47 @@ __global__ __launch_bounds__(kBlock) void k_finalize(int nblocks, const double* 
     out[threadIdx.x] = tot;
     if (!isfinite(tot)) flags[kFlagNonFinite] = 1;
   }
+}
+
+// Block x reduces set x.
+template <int NQ>
+__global__ __launch_bounds__(kBlock) void k_finalize(int nblocks, const double* __restrict__ partials,
+                                                      double* __restrict__ out,
+                                                      int* __restrict__ flags) {
+  finalize_set<NQ>(nblocks, partials + (size_t)blockIdx.x * nblocks * NQ,
+                   out + (size_t)blockIdx.x * NQ, flags);
+}
+
+// Results in the caller's order, dst[r*n + c] = src[r*n + iperm[c]] for every
+// array whose destination is given, and the totals by the last block when
+// totals is given: one launch in place of up to five (a launch of a few
+// microseconds' work costs about 4 us on the stream, half of a small system's
+// evaluation).
+__global__ __launch_bounds__(kBlock) void k_outputs(
+    int n, const int* __restrict__ iperm, const float* __restrict__ U, float* __restrict__ U_dst,
+    const float* __restrict__ F, float* __restrict__ F_dst, const float* __restrict__ W,
+    float* __restrict__ W_dst, const float* __restrict__ J, float* __restrict__ J_dst, int nblocks,
+    const double* __restrict__ partials, double* __restrict__ totals, int* __restrict__ flags) {
+  if (totals && blockIdx.x == gridDim.x - 1) {
+    finalize_set<13>(nblocks, partials, totals, flags);
+    return;
+  }
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= n) return;
+  const int k = iperm[c];
+  auto copy = [&](const float* __restrict__ src, float* __restrict__ dst, auto rows) {
+    constexpr int R = decltype(rows)::value;
+    if (!dst) return;
+    float v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = src[(size_t)r * n + k];
+#pragma unroll
+    for (int r = 0; r < R; ++r) dst[(size_t)r * n + c] = v[r];
+  };
+  copy(U, U_dst, std::integral_constant<int, 1>{});
+  copy(F, F_dst, std::integral_constant<int, 3>{});
+  copy(W, W_dst, std::integral_constant<int, 9>{});
+  copy(J, J_dst, std::integral_constant<int, 3>{});
 }
 
 // MODE 0: evaluation -> block sums of (U, W_ab (9), J (3)).
@@ -621,16 +660,22 @@ hipError_t launch_gather(nep_ctx ctx, const double* pos, double* vel, float* U_o
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(nep_ctx ctx, int nq, int nsets, const double* block_sums, double* out,
-                           bool first) {
+hipError_t launch_finalize(nep_ctx ctx, int nsets, const double* block_sums, double* out) {
   if (nsets == 0) return hipSuccess;
-  const int nb = (int)gather_blocks(ctx->sys.n);
-  if (nq == 13)
-    launch_kernel(ctx, first, true, k_finalize<13>, dim3(nsets), dim3(kBlock), nb, block_sums, out,
-                  ctx->flags.ptr);
-  else
-    launch_kernel(ctx, first, true, k_finalize<5>, dim3(nsets), dim3(kBlock), nb, block_sums, out,
-                  ctx->flags.ptr);
+  launch_kernel(ctx, true, true, k_finalize<5>, dim3(nsets), dim3(kBlock),
+                (int)gather_blocks(ctx->sys.n), block_sums, out, ctx->flags.ptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_outputs(nep_ctx ctx, float* U, float* F, float* W, float* J,
+                          const double* block_sums, double* totals) {
+  const int n = ctx->sys.n;
+  const unsigned nb = blocks_for((size_t)n, kBlock) + (totals ? 1u : 0u);
+  if (nb == 0) return hipSuccess;
+  launch_kernel(ctx, false, false, k_outputs, dim3(nb), dim3(kBlock), n,
+                (const int*)ctx->sys.iperm.ptr, (const float*)ctx->U.ptr, U,
+                (const float*)ctx->F.ptr, F, (const float*)ctx->W.ptr, W, (const float*)ctx->J.ptr,
+                J, (int)gather_blocks(n), block_sums, totals, ctx->flags.ptr);
   return hipGetLastError();
 }
 

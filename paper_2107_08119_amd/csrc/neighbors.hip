@@ -33,13 +33,28 @@ __global__ void k_zero(int* __restrict__ a, int m) {
 
 // Integer cell offsets w = floor(s) of every atom (optionally wrapping the
 // positions into the cell first) and, on the cell path, the cell index.
-__global__ void k_bin(int n, double* __restrict__ pos, Box box, int nc0, int nc1, int nc2,
-                      int use_cells, int wrap_in_place, int* __restrict__ wrap,
-                      int* __restrict__ cell_of, int* __restrict__ cell_cnt,
-                      float* __restrict__ pos_ref) {
+// With src (a new system) the positions, and the velocities when vel_src is
+// given, are first taken over from the caller's arrays, in the caller's order
+// (perm, iperm the identity); otherwise pos holds them.
+__global__ void k_bin(int n, const double* __restrict__ src, const double* __restrict__ vel_src,
+                      double* __restrict__ pos, double* __restrict__ vel, int* __restrict__ perm,
+                      int* __restrict__ iperm, Box box, int nc0, int nc1, int nc2, int use_cells,
+                      int wrap_in_place, int* __restrict__ wrap, int* __restrict__ cell_of,
+                      int* __restrict__ cell_cnt, float* __restrict__ pos_ref) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  double r[3] = {pos[i], pos[n + i], pos[2 * n + i]};
+  double r[3];
+  if (src) {
+    perm[i] = i;
+    iperm[i] = i;
+    for (int c = 0; c < 3; ++c) {
+      r[c] = src[(size_t)c * n + i];
+      pos[(size_t)c * n + i] = r[c];
+      if (vel_src) vel[(size_t)c * n + i] = vel_src[(size_t)c * n + i];
+    }
+  } else {
+    for (int c = 0; c < 3; ++c) r[c] = pos[(size_t)c * n + i];
+  }
   double s[3];
   int w[3];
   fractional(box, r, s);
@@ -234,22 +249,18 @@ __global__ void k_rank_permute(int n, const int* __restrict__ start,
   rec[k] = r;
 }
 
-template <class T>
-__global__ void k_take_rows(int n, int rows, const T* __restrict__ src, const int* __restrict__ perm,
-                            T* __restrict__ dst) {
+// Two [3][n] arrays of the caller's into the internal order: a, and b unless
+// it is NULL.
+__global__ void k_take_rows2(int n, const double* __restrict__ a, double* __restrict__ a_dst,
+                             const double* __restrict__ b, double* __restrict__ b_dst,
+                             const int* __restrict__ perm) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   const int o = perm[k];
-  for (int r = 0; r < rows; ++r) dst[(size_t)r * n + k] = src[(size_t)r * n + o];
-}
-
-template <class T>
-__global__ void k_put_rows(int n, int rows, const T* __restrict__ src, const int* __restrict__ iperm,
-                           T* __restrict__ dst) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
-  const int k = iperm[c];
-  for (int r = 0; r < rows; ++r) dst[(size_t)r * n + c] = src[(size_t)r * n + k];
+  for (int r = 0; r < 3; ++r) {
+    a_dst[(size_t)r * n + k] = a[(size_t)r * n + o];
+    if (b) b_dst[(size_t)r * n + k] = b[(size_t)r * n + o];
+  }
 }
 
 // Two [3][n] arrays back to the caller's order in one pass.
@@ -263,17 +274,6 @@ __global__ void k_put_rows2(int n, const double* __restrict__ a, double* __restr
     a_dst[(size_t)r * n + c] = a[(size_t)r * n + k];
     b_dst[(size_t)r * n + c] = b[(size_t)r * n + k];
   }
-}
-
-// iperm[perm[k]] = k.
-__global__ void k_invert_perm(int n, const int* __restrict__ perm, int* __restrict__ iperm) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) iperm[perm[k]] = k;
-}
-
-__global__ void k_iota(int n, int* __restrict__ a) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) a[k] = k;
 }
 
 // One block per cell: the records of the 27 surrounding cells are staged in
@@ -719,16 +719,11 @@ hipError_t unpack_neighbors(nep_ctx ctx, int* nbr, int* img, int* cnt_r, int* cn
   return hipGetLastError();
 }
 
-void launch_take_rows(nep_ctx ctx, int n, int rows, const double* src, double* dst) {
+void launch_take_rows(nep_ctx ctx, int n, const double* pos, double* pos_dst, const double* vel,
+                      double* vel_dst) {
   if (n == 0) return;
-  launch_kernel(ctx, false, false, k_take_rows<double>, dim3(blocks_for(n, kBlock)), dim3(kBlock),
-                n, rows, src, (const int*)ctx->sys.perm.ptr, dst);
-}
-
-void launch_put_rows(nep_ctx ctx, int n, int rows, const double* src, double* dst) {
-  if (n == 0) return;
-  launch_kernel(ctx, false, false, k_put_rows<double>, dim3(blocks_for(n, kBlock)), dim3(kBlock),
-                n, rows, src, (const int*)ctx->sys.iperm.ptr, dst);
+  launch_kernel(ctx, false, false, k_take_rows2, dim3(blocks_for(n, kBlock)), dim3(kBlock), n, pos,
+                pos_dst, vel, vel_dst, (const int*)ctx->sys.perm.ptr);
 }
 
 void launch_put_rows2(nep_ctx ctx, int n, const double* a, double* a_dst, const double* b,
@@ -736,17 +731,6 @@ void launch_put_rows2(nep_ctx ctx, int n, const double* a, double* a_dst, const 
   if (n == 0) return;
   launch_kernel(ctx, false, false, k_put_rows2, dim3(blocks_for(n, kBlock)), dim3(kBlock), n, a,
                 a_dst, b, b_dst, (const int*)ctx->sys.iperm.ptr);
-}
-
-void launch_put_rows(nep_ctx ctx, int n, int rows, const float* src, float* dst) {
-  if (n == 0) return;
-  launch_kernel(ctx, false, false, k_put_rows<float>, dim3(blocks_for(n, kBlock)), dim3(kBlock), n,
-                rows, src, (const int*)ctx->sys.iperm.ptr, dst);
-}
-
-void launch_iota(nep_ctx ctx, int n, int* dst) {
-  if (n == 0) return;
-  launch_kernel(ctx, false, false, k_iota, dim3(blocks_for(n, kBlock)), dim3(kBlock), n, dst);
 }
 
 void prepare_system_geometry(System& s, const double* H, double rc_r, double rc_a, double skin) {
@@ -787,7 +771,8 @@ void prepare_system_geometry(System& s, const double* H, double rc_r, double rc_
   if (!s.use_cells) s.nc[0] = s.nc[1] = s.nc[2] = 1;
 }
 
-nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel) {
+nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const double* src,
+                           const double* vel_src) {
   System& s = ctx->sys;
   const int n = s.n;
   hipError_t e = hipSuccess;
@@ -819,9 +804,10 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel) {
     if (zero)
       launch_kernel(ctx, true, false, k_zero, dim3(blocks_for(ncell, kBlock)), blk,
                     s.cell_cnt.ptr, ncell);
-    launch_kernel(ctx, !zero, false, k_bin, dim3(blocks_for(n, kBlock)), blk, n, s.pos_s.ptr,
-                  s.box, s.nc[0], s.nc[1], s.nc[2], 1, wrap_in_place ? 1 : 0, s.wrap.ptr,
-                  s.cell_of.ptr, s.cell_cnt.ptr, (float*)nullptr);
+    launch_kernel(ctx, !zero, false, k_bin, dim3(blocks_for(n, kBlock)), blk, n, src, vel_src,
+                  s.pos_s.ptr, s.vel_s.ptr, s.perm.ptr, s.iperm.ptr, s.box, s.nc[0], s.nc[1],
+                  s.nc[2], 1, wrap_in_place ? 1 : 0, s.wrap.ptr, s.cell_of.ptr, s.cell_cnt.ptr,
+                  (float*)nullptr);
     const int nsb = (ncell + 1023) / 1024;
     if (ncell > 1024 * kScanChunks && nsb <= 1024) {
       launch_kernel(ctx, false, false, k_scan_blocks, dim3(nsb), dim3(1024), ncell,
@@ -860,20 +846,15 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel) {
     // (a fixed workspace may have no room for the per-atom copy)
     if (!(s.nl_rm.view && !s.nl_rm.ptr) && (e = s.nl_rm.ensure(ncap)) != hipSuccess)
       return check_hip(ctx, e, "allocating neighbour lists");
-    launch_kernel(ctx, true, false, k_bin, dim3(blocks_for(n, kBlock)), blk, n, s.pos_s.ptr, s.box,
-                  1, 1, 1, 0, wrap_in_place ? 1 : 0, s.wrap.ptr, (int*)nullptr, (int*)nullptr,
-                  s.pos_ref.ptr);
+    launch_kernel(ctx, true, false, k_bin, dim3(blocks_for(n, kBlock)), blk, n, src, vel_src,
+                  s.pos_s.ptr, s.vel_s.ptr, s.perm.ptr, s.iperm.ptr, s.box, 1, 1, 1, 0,
+                  wrap_in_place ? 1 : 0, s.wrap.ptr, (int*)nullptr, (int*)nullptr, s.pos_ref.ptr);
     const int waves = image_waves(n);
     launch_kernel(ctx, false, false, k_build_all_pairs, dim3(blocks_for(n, waves)),
                   dim3(64 * waves), n, s.cap, (const double*)s.pos_s.ptr, s.box, s.kimg[0],
                   s.kimg[1], s.kimg[2], (const int*)s.wrap.ptr, rc2_r, rc2_a, s.nl.ptr,
                   s.nl_rm.ptr, s.cnt_r.ptr, s.cnt_a.ptr, ctx->flags.ptr);
   }
-  // caller index -> internal index, for the coalesced copies back (the cell
-  // path's k_rank_permute writes it)
-  if (n > 0 && !s.use_cells)
-    launch_kernel(ctx, false, false, k_invert_perm, dim3(blocks_for(n, kBlock)), blk, n,
-                  (const int*)s.perm.ptr, s.iperm.ptr);
   launch_kernel(ctx, false, true, k_reverse, dim3(blocks_for((size_t)n, kReverseAtoms)), blk, n,
                 s.cap, (const uint32_t*)s.nl.ptr,
                 (const uint32_t*)s.nl_rm.ptr,

@@ -58,22 +58,18 @@ nep_status size_system_buffers(nep_ctx ctx) {
 
 }  // namespace
 
-hipError_t evaluate_internal(nep_ctx ctx, bool vel, double* out, int mode, double kick,
-                             double mass, bool want_w, bool want_j, double* block_out, double dt,
+hipError_t evaluate_internal(nep_ctx ctx, bool vel, int mode, double kick, double mass,
+                             bool want_w, bool want_j, double* block_out, double dt,
                              double* pos_next, const double* fe) {
   static const double kNoField[3] = {0.0, 0.0, 0.0};
   if (!fe) fe = kNoField;
   System& s = ctx->sys;
   hipError_t e = timed(ctx, 0, [&] { return launch_partials(ctx, s.pos_s.ptr); });
   if (e != hipSuccess) return e;
-  double* sums = block_out ? block_out : ctx->partials.ptr;
   return timed(ctx, 1, [&] {
-    hipError_t r = launch_gather(ctx, s.pos_s.ptr, vel ? s.vel_s.ptr : nullptr, nullptr,
-                                 ctx->F.ptr, want_w ? ctx->W.ptr : nullptr,
-                                 want_j ? ctx->J.ptr : nullptr, sums, mode, kick, mass, dt,
-                                 pos_next, fe, block_out != nullptr);
-    if (r != hipSuccess || block_out) return r;
-    return launch_finalize(ctx, mode == 0 ? 13 : 5, 1, sums, out, s.n == 0);
+    return launch_gather(ctx, s.pos_s.ptr, vel ? s.vel_s.ptr : nullptr, nullptr, ctx->F.ptr,
+                         want_w ? ctx->W.ptr : nullptr, want_j ? ctx->J.ptr : nullptr, block_out,
+                         mode, kick, mass, dt, pos_next, fe, true);
   });
 }
 
@@ -259,13 +255,7 @@ nep_status nep_build_neighbors(nep_ctx ctx, int n_atoms, const double* pos_dev,
   nep_status st = size_system_buffers(ctx);
   if (st != NEP_OK) return st;
   if (n_atoms > 0) {
-    launch_iota(ctx, n_atoms, s.perm.ptr);
-    st = check_hip(ctx,
-                   hipMemcpyAsync(s.pos_s.ptr, pos_dev, sizeof(double) * 3 * n_atoms,
-                                  hipMemcpyDeviceToDevice, ctx->stream),
-                   "copying positions");
-    if (st != NEP_OK) return st;
-    st = build_neighbors(ctx, false, false);
+    st = build_neighbors(ctx, false, false, pos_dev);
     if (st != NEP_OK) return st;
   }
   ctx->have_list = true;
@@ -340,18 +330,12 @@ nep_status nep_compute(nep_ctx ctx, const double* pos_dev, const double* vel_dev
   if (J_dev && !vel_dev) return fail(ctx, NEP_EINVAL, "J_dev needs vel_dev");
   DeviceGuard guard(ctx->device);
   ctx->md_forces_valid = false;
-  launch_take_rows(ctx, n, 3, pos_dev, s.pos_s.ptr);
-  if (vel_dev) launch_take_rows(ctx, n, 3, vel_dev, s.vel_s.ptr);
-  hipError_t e = evaluate_internal(ctx, vel_dev != nullptr,
-                                   totals_dev ? totals_dev : ctx->totals.ptr, 0, 0.0, 1.0,
-                                   W_dev != nullptr, J_dev != nullptr);
-  if (e == hipSuccess) {
-    launch_put_rows(ctx, n, 3, ctx->F.ptr, F_dev);
-    if (U_dev) launch_put_rows(ctx, n, 1, ctx->U.ptr, U_dev);
-    if (W_dev) launch_put_rows(ctx, n, 9, ctx->W.ptr, W_dev);
-    if (J_dev) launch_put_rows(ctx, n, 3, ctx->J.ptr, J_dev);
-    e = hipGetLastError();
-  }
+  launch_take_rows(ctx, n, pos_dev, s.pos_s.ptr, vel_dev, s.vel_s.ptr);
+  hipError_t e = evaluate_internal(ctx, vel_dev != nullptr, 0, 0.0, 1.0, W_dev != nullptr,
+                                   J_dev != nullptr, ctx->partials.ptr);
+  if (e == hipSuccess)
+    e = launch_outputs(ctx, U_dev, F_dev, W_dev, J_dev, ctx->partials.ptr,
+                       totals_dev ? totals_dev : ctx->totals.ptr);
   return check_hip(ctx, e, "launching force kernels");
 }
 
@@ -407,10 +391,9 @@ nep_status nep_md_step_driven(nep_ctx ctx, int n_steps, double dt_fs, int rebuil
     });
     if (e != hipSuccess) return check_hip(ctx, e, "launching integrator");
   } else {
-    launch_take_rows(ctx, n, 3, pos_dev, s.pos_s.ptr);
-    launch_take_rows(ctx, n, 3, vel_dev, s.vel_s.ptr);
-    e = evaluate_internal(ctx, true, nullptr, 1, 0.0, mass_amu, false, false, ctx->partials.ptr,
-                          0.0, nullptr, fe_host);
+    launch_take_rows(ctx, n, pos_dev, s.pos_s.ptr, vel_dev, s.vel_s.ptr);
+    e = evaluate_internal(ctx, true, 1, 0.0, mass_amu, false, false, ctx->partials.ptr, 0.0,
+                          nullptr, fe_host);
     if (e != hipSuccess) return check_hip(ctx, e, "launching force kernels");
     e = timed(ctx, 3, [&] {
       return launch_kick_drift(ctx, s.pos_s.ptr, s.vel_s.ptr, kick, mass_amu, dt_fs);
@@ -431,20 +414,21 @@ nep_status nep_md_step_driven(nep_ctx ctx, int n_steps, double dt_fs, int rebuil
       ctx->steps_since_rebuild = 0;
     }
     const bool last = step == n_steps - 1;
-    e = evaluate_internal(ctx, true, nullptr, last ? 1 : 2, kick, mass_amu, W_dev != nullptr,
-                          J_dev != nullptr,
-                          ctx->partials.ptr + (size_t)pending * nb * 5, dt_fs,
+    e = evaluate_internal(ctx, true, last ? 1 : 2, kick, mass_amu, W_dev != nullptr,
+                          J_dev != nullptr, ctx->partials.ptr + (size_t)pending * nb * 5, dt_fs,
                           last ? nullptr : s.pos_t.ptr, fe_host);
     if (e != hipSuccess) return check_hip(ctx, e, "launching force kernels");
     if (!last && n > 0) s.pos_s.swap(s.pos_t);
     // per-atom W and J of this step in the caller's order (the gather writes
-    // them in cell order: coalesced, then one scatter pass each)
-    if (W_dev) launch_put_rows(ctx, n, 9, ctx->W.ptr, W_dev);
-    if (J_dev) launch_put_rows(ctx, n, 3, ctx->J.ptr, J_dev);
+    // them in cell order: coalesced, then one pass into the caller's order)
+    if (W_dev || J_dev) {
+      e = launch_outputs(ctx, nullptr, nullptr, W_dev, J_dev, nullptr, nullptr);
+      if (e != hipSuccess) return check_hip(ctx, e, "launching the per-atom copies");
+    }
     if (++pending == chunk || last) {
       e = timed(ctx, 3, [&] {
-        return launch_finalize(ctx, 5, pending, ctx->partials.ptr,
-                               thermo_dev + (size_t)5 * (step + 1 - pending), true);
+        return launch_finalize(ctx, pending, ctx->partials.ptr,
+                               thermo_dev + (size_t)5 * (step + 1 - pending));
       });
       if (e != hipSuccess) return check_hip(ctx, e, "launching thermo sums");
       pending = 0;
@@ -495,7 +479,7 @@ nep_status nep_time_partials(nep_ctx ctx, const double* pos_dev, int reps, doubl
   if (reps < 1 || reps > 100000) return fail(ctx, NEP_EINVAL, "reps must be in [1, 100000]");
   if (ctx->sys.n > 0 && !pos_dev) return fail(ctx, NEP_EINVAL, "pos_dev is NULL");
   DeviceGuard guard(ctx->device);
-  launch_take_rows(ctx, ctx->sys.n, 3, pos_dev, ctx->sys.pos_s.ptr);
+  launch_take_rows(ctx, ctx->sys.n, pos_dev, ctx->sys.pos_s.ptr, nullptr, nullptr);
   hipEvent_t a = nullptr, b = nullptr;
   hipError_t e = hipEventCreate(&a);
   if (e == hipSuccess) e = hipEventCreate(&b);
@@ -521,7 +505,7 @@ nep_status nep_autotune(nep_ctx ctx, const double* pos_dev, int reps, int* lanes
   if (reps < 1 || reps > 10000) return fail(ctx, NEP_EINVAL, "reps must be in [1, 10000]");
   if (ctx->sys.n > 0 && !pos_dev) return fail(ctx, NEP_EINVAL, "pos_dev is NULL");
   DeviceGuard guard(ctx->device);
-  launch_take_rows(ctx, ctx->sys.n, 3, pos_dev, ctx->sys.pos_s.ptr);
+  launch_take_rows(ctx, ctx->sys.n, pos_dev, ctx->sys.pos_s.ptr, nullptr, nullptr);
   const bool timing = ctx->timer.on;
   ctx->timer.on = false;
   hipEvent_t a = nullptr, b = nullptr;

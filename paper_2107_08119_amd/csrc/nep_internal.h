@@ -359,17 +359,19 @@ int population_max_structure();
 // Build the list of the internal positions sys.pos_s; on the cell path the
 // atoms (positions, velocities when have_vel, perm) are first re-sorted into
 // cell order.  wrap_in_place maps the internal positions into the box.
-nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel);
-// dst[r*n + k] = src[r*n + perm[k]] (caller order -> internal order).
-void launch_take_rows(nep_ctx ctx, int n, int rows, const double* src, double* dst);
-// dst[r*n + c] = src[r*n + iperm[c]] (internal order -> caller order; the
-// same as dst[r*n + perm[k]] = src[r*n + k], with coalesced stores).
-void launch_put_rows(nep_ctx ctx, int n, int rows, const double* src, double* dst);
-void launch_put_rows(nep_ctx ctx, int n, int rows, const float* src, float* dst);
-// both [3][n] arrays a (to a_dst) and b (to b_dst) in one launch
+// src: the caller's positions of a new system (and vel_src its velocities or
+// NULL), taken over in the caller's order first; NULL: a rebuild of pos_s.
+nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel,
+                           const double* src = nullptr, const double* vel_src = nullptr);
+// The caller's [3][n] positions, and velocities unless vel is NULL, in the
+// internal order: dst[r*n + k] = src[r*n + perm[k]].
+void launch_take_rows(nep_ctx ctx, int n, const double* pos, double* pos_dst, const double* vel,
+                      double* vel_dst);
+// Both [3][n] arrays a (to a_dst) and b (to b_dst) in the caller's order:
+// dst[r*n + c] = src[r*n + iperm[c]] (the same as dst[r*n + perm[k]] =
+// src[r*n + k], with coalesced stores).
 void launch_put_rows2(nep_ctx ctx, int n, const double* a, double* a_dst, const double* b,
                       double* b_dst);
-void launch_iota(nep_ctx ctx, int n, int* dst);
 void prepare_system_geometry(System& s, const double* box_host, double rc_r, double rc_a,
                              double skin);
 // Expand the list into the caller's numbering (see nep_get_neighbors).
@@ -395,14 +397,17 @@ hipError_t launch_partials(nep_ctx ctx, const double* pos, int variant = -1);
 // mode 0: plain evaluation (totals = E, W(9), J(3)); mode 1: velocity-Verlet
 // second half-kick fused (vel updated, thermo row written).
 // Pass 2 (k_gather, modes as documented there) writing per-block sums to
-// block_out [gather_blocks(n)][13 or 5]; launch_finalize adds nsets such
-// arrays (consecutive in block_sums) into out [nsets][nq].  fe [3]: the
+// block_out [gather_blocks(n)][13 or 5]; launch_finalize adds nsets of the
+// 5-value arrays (consecutive in block_sums) into out [nsets][5].  fe [3]: the
 // HNEMD driving field added as F_e . W_i in the MD modes.
 hipError_t launch_gather(nep_ctx ctx, const double* pos, double* vel, float* U_out, float* F_out,
                          float* W_out, float* J_out, double* block_out, int mode, double kick,
                          double mass, double dt, double* pos_next, const double* fe, bool last);
-hipError_t launch_finalize(nep_ctx ctx, int nq, int nsets, const double* block_sums, double* out,
-                           bool first);
+hipError_t launch_finalize(nep_ctx ctx, int nsets, const double* block_sums, double* out);
+// The evaluation's float32 results in the caller's order (each destination
+// may be NULL) and, unless totals is NULL, the 13 totals from block_sums.
+hipError_t launch_outputs(nep_ctx ctx, float* U, float* F, float* W, float* J,
+                          const double* block_sums, double* totals);
 size_t gather_blocks(int n);
 // The caller's positions and velocities (caller order) gathered into the
 // internal arrays with the first half-kick and drift applied (the forces kept
@@ -483,11 +488,10 @@ inline unsigned long long* pair_totals(nep_ctx ctx) {
 int n_des_of(const nep_hyper& h);
 // One force evaluation of the internal state (positions sys.pos_s, velocities
 // sys.vel_s when vel is true): pass 1 and pass 2 into the internal U, F, W, J,
-// with the totals (13 values, or 5 thermo values in the MD modes) in out.
-// MD modes: block sums go to block_out and are reduced later (out unused).
-hipError_t evaluate_internal(nep_ctx ctx, bool vel, double* out, int mode, double kick,
-                             double mass, bool want_w = false, bool want_j = false,
-                             double* block_out = nullptr, double dt = 0.0,
+// block sums (of 13 values, or 5 thermo values in the MD modes) to block_out,
+// to be added later.
+hipError_t evaluate_internal(nep_ctx ctx, bool vel, int mode, double kick, double mass,
+                             bool want_w, bool want_j, double* block_out, double dt = 0.0,
                              double* pos_next = nullptr, const double* fe = nullptr);
 // noalloc.hip: locate the static workspace of nep_evaluate_static on the
 // current device (once per device, at context creation).

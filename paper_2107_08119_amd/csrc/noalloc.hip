@@ -195,29 +195,16 @@ nep_status nep_evaluate_static(nep_ctx ctx, int n_atoms, const double* pos_dev,
   ctx->sys = view;
   ctx->species_n = 0;  // one species
   ctx->have_masses = false;
-  System& s = ctx->sys;
   if (n_atoms > 0) {
-    launch_iota(ctx, n_atoms, s.perm.ptr);
-    st = check_hip(ctx,
-                   hipMemcpyAsync(s.pos_s.ptr, pos_dev, sizeof(double) * 3 * n_atoms,
-                                  hipMemcpyDeviceToDevice, ctx->stream),
-                   "copying positions");
+    // leaves the caller's positions and velocities in the internal order
+    st = build_neighbors(ctx, false, vel_dev != nullptr, pos_dev, vel_dev);
     if (st != NEP_OK) return st;
-    st = build_neighbors(ctx, false, false);
-    if (st != NEP_OK) return st;
-    launch_take_rows(ctx, n_atoms, 3, pos_dev, s.pos_s.ptr);
-    if (vel_dev) launch_take_rows(ctx, n_atoms, 3, vel_dev, s.vel_s.ptr);
   }
-  hipError_t e = evaluate_internal(ctx, vel_dev != nullptr,
-                                   totals_dev ? totals_dev : ctx->totals.ptr, 0, 0.0, 1.0,
-                                   W_dev != nullptr, J_dev != nullptr);
-  if (e == hipSuccess) {
-    launch_put_rows(ctx, n_atoms, 3, ctx->F.ptr, F_dev);
-    if (U_dev) launch_put_rows(ctx, n_atoms, 1, ctx->U.ptr, U_dev);
-    if (W_dev) launch_put_rows(ctx, n_atoms, 9, ctx->W.ptr, W_dev);
-    if (J_dev) launch_put_rows(ctx, n_atoms, 3, ctx->J.ptr, J_dev);
-    e = hipGetLastError();
-  }
+  hipError_t e = evaluate_internal(ctx, vel_dev != nullptr, 0, 0.0, 1.0, W_dev != nullptr,
+                                   J_dev != nullptr, ctx->partials.ptr);
+  if (e == hipSuccess)
+    e = launch_outputs(ctx, U_dev, F_dev, W_dev, J_dev, ctx->partials.ptr,
+                       totals_dev ? totals_dev : ctx->totals.ptr);
   return check_hip(ctx, e, "launching force kernels");
 }
 
