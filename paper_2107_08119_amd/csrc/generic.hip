@@ -1,21 +1,33 @@
 // Pass 1 for any model size within n_max^R, n_max^A <= 15, l_max <= 4 and
 // at most 64 hidden neurons (the paper's models of Sec. III, e.g. 80-50-1):
-// one 64-lane wave per atom, lanes over the atom's neighbour pairs.
+// 16 atoms per block of four waves, 16 lanes per atom.
 //
 // The terms are those of nep_terms.h (factorised angular descriptor, network,
-// partial force of Sec. II D), with the per-atom sums done by the wave:
-//   * radial q_n: each lane adds f_c T_n of its pairs, then a fixed-order
-//     wave sum gives R_n and q_n = (R_n + R_0)/2 (g_n = f_c (T_n + 1)/2);
-//   * angular moments c_nlm = sum_j g_n(r_ij) Yhat_lm(u_ij): the lanes write
-//     their pairs' g_n and Yhat_lm to LDS and lane k accumulates outputs
-//     (n, lm) = k, k + 64, ... over the pairs in index order;
-//   * network: lane mu evaluates neuron mu; dU/dq_v is formed by lane v from
-//     the neurons' w2 sech^2 in LDS;
-//   * partial forces: lane p evaluates pair p from dU/dq and a_nlm in LDS,
-//     as sums over T_n and T_n' (the n = 0 terms folded per atom), and
-//     stores the pair vector r_ij in the atom's own slot for pass 2 (systems
-//     of up to kPairVectorMaxAtoms atoms).
+// partial force of Sec. II D):
+//   * staging: the block reads the list and reverse slots of its atoms, 48
+//     slots at a time with atoms fastest (coalesced), classifies the pairs and
+//     packs those inside a cutoff per atom in LDS, angular ones first; the
+//     pair vectors r_ij go to the atom's own slots for pass 2 (systems of up
+//     to kPairVectorMaxAtoms atoms);
+//   * radial q_n: each lane adds f_c T_n of its pairs, the atom's 16 lanes are
+//     summed in a fixed order, q_n = (R_n + R_0)/2 (g_n = f_c (T_n + 1)/2);
+//   * angular moments c_nlm = sum_j g_n(r_ij) Yhat_lm(u_ij): per atom the
+//     product (n x pairs)(pairs x lm) as 16x16x4 MFMA steps, the operands
+//     passed through LDS; the sums stay in registers;
+//   * network: W1 Q^T and W1^T G for the block's 16 atoms on the matrix cores,
+//     a wave per 16 neurons and per 16 descriptor components;
+//   * partial forces: lane p evaluates pair p of its atom; the sums over n of
+//     a_nlm (T_n + 1) and a_nlm T_n' for all lm are two more products per 16
+//     pairs, with a_nlm = 2 dU/dq_nl c_nlm formed where c_nlm lies.
 // Every sum has a fixed order, so results are reproducible bit for bit.
+//
+// Bound: the VALU work per pair (geometry, Chebyshev recursions, harmonics
+// and their gradients, about 700 instructions for both loops) and, where an
+// atom has few angular pairs, the loads and stores of the list slots.  One
+// wave per atom, with the contractions on the VALU from LDS, left most lanes
+// idle where an atom has fewer than 64 pairs (6 angular ones in PbTe): 63.0
+// against 27.4 us for 80-50-1 on 8,000 atoms, 527 against 213 us for PbTe on
+// 64,000 atoms.
 //
 // Multicomponent systems take the descriptor and the hidden layer's input in
 // float64 (pair geometry, basis, harmonics, the sums q and c_nlm, and the
@@ -33,7 +45,12 @@ namespace {
 
 // Largest sizes of the runtime-sized instantiation.
 constexpr int kMaxR = 16, kMaxA = 16, kMaxNeu = 64;
-constexpr int kWaves = 4;  // atoms per block
+constexpr int kAtoms = 16;  // atoms per block, 16 lanes each
+constexpr int kWaves = 4;
+// List slots per atom staged at a time: most lists with a 0.5 A skin fit at
+// once, longer ones (80 slots in PbTe) take further rounds of staging.
+constexpr int kSlots = 48;
+constexpr int kRow = kSlots + 1;  // LDS row of an atom's pairs (odd: no bank aliasing)
 
 // Sizes of one instantiation: TR > 0 fixes (n_max^R + 1, n_max^A + 1, l_max,
 // N_neu) = (TR, TA, TL, TNEU) at compile time (loops unrolled, LDS sized to
@@ -44,40 +61,58 @@ struct Shape {
   static constexpr int MR = kFixed ? TR : kMaxR;
   static constexpr int MA = kFixed ? TA : kMaxA;
   static constexpr int ML = kFixed ? TL : 4;
-  static constexpr int MLM = (ML + 1) * (ML + 1) - 1;
   static constexpr int MNEU = kFixed ? TNEU : kMaxNeu;
   static constexpr int MDES = MR + MA * ML;
+  // A lane of lane group h = lane / 16 holds the moments n = RPL h + r, r < RPL.
+  static constexpr int RPL = MA > 8 ? 4 : 2;
+  static constexpr int KT = (MDES + 15) / 16;  // 16-wide tiles of the descriptor
+  static constexpr int QS = 16 * KT + 4;       // LDS row of an atom's descriptor
+  static constexpr int NT = (MNEU + 15) / 16;  // 16-wide tiles of the hidden layer
+  static constexpr int GS = 16 * NT + 4;       // LDS row of an atom's w2 sech^2
 };
 
-// Sum over the 64 lanes of a wave in a fixed order; every lane gets the
-// same bits (each step adds two partial sums, which commutes exactly).
-__device__ __forceinline__ float wave_sum(float v) {
-  v = group_sum<16>(v);
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// One 16x16x4 step: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16].
+// Element r of lane l is C[mma_row(l / 16, r)][l % 16].
+__device__ __forceinline__ f32x4 mma(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f64x4 mma(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+// Row i of A goes to element r of lane group h in C: i = 4 h + r in float32,
+// 4 r + h in float64.  A supplies in row i whatever lane (h, r) is to hold.
+template <class DT>
+__device__ __forceinline__ void mma_owner(int i, int& h, int& r) {
+  h = sizeof(DT) == 8 ? i & 3 : i >> 2;
+  r = sizeof(DT) == 8 ? i >> 2 : i & 3;
+}
+
+// Sum over the 16 lanes of an atom in a fixed order; every lane gets the same
+// bits (each step adds two partial sums, which commutes exactly).
+__device__ __forceinline__ float atom_sum(float v) { return group_sum<16>(v); }
+__device__ __forceinline__ double atom_sum(double v) {
+#pragma unroll
+  for (int d = 1; d < 16; d <<= 1) v += __shfl_xor(v, d, 64);
   return v;
 }
 
-// Fixed-order sum over the 64 lanes in float64 (butterfly: each step adds the
-// same two values on both partners, so every lane gets the same bits).
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d, 64);
-  return v;
-}
+// l of harmonic index lm = l^2 - 1 + (m + l)
+__device__ __forceinline__ int l_of(int lm) { return lm < 3 ? 1 : (lm < 8 ? 2 : (lm < 15 ? 3 : 4)); }
 
 // r_ij of list entry e in float64, rounded exactly as the float32
 // displacement is before its final rounding (so the two agree to float32).
-__device__ __forceinline__ void displacement_d(uint32_t e, const double* __restrict__ pos, int n,
-                                               double xi, double yi, double zi, const double* h,
-                                               int& j, double& dx, double& dy, double& dz) {
-  j = (int)(e & kAtomMask);
+__device__ __forceinline__ void image_displacement_d(uint32_t e, const double (&pj)[3], double xi,
+                                                     double yi, double zi, const double* h,
+                                                     double& dx, double& dy, double& dz) {
   int n0, n1, n2;
   unpack_image(e, n0, n1, n2);
   const double a0 = (double)n0, a1 = (double)n1, a2 = (double)n2;
-  dx = (pos[j] - xi) + (a0 * h[0] + a1 * h[3] + a2 * h[6]);
-  dy = (pos[n + j] - yi) + (a0 * h[1] + a1 * h[4] + a2 * h[7]);
-  dz = (pos[2 * n + j] - zi) + (a0 * h[2] + a1 * h[5] + a2 * h[8]);
+  dx = (pj[0] - xi) + (a0 * h[0] + a1 * h[3] + a2 * h[6]);
+  dy = (pj[1] - yi) + (a0 * h[1] + a1 * h[4] + a2 * h[7]);
+  dz = (pj[2] - zi) + (a0 * h[2] + a1 * h[5] + a2 * h[8]);
 }
 
 constexpr double kPiD = 3.14159265358979323846;
@@ -179,406 +214,577 @@ __device__ __forceinline__ void radial_basis_n(float r, float rc_inv, int nb, fl
 // F64: the float64 descriptor and hidden-layer input of multicomponent
 // systems (wspd = sqrt(Z) in float64 beside wsp).
 template <int TR, int TA, int TL, int TNEU, bool F64>
-__global__ __launch_bounds__(64 * kWaves) void k_partials_generic(
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_partials_generic(
     int n, const double* __restrict__ pos, const uint32_t* __restrict__ nl,
     const int* __restrict__ cnt_r, const int* __restrict__ cnt_a, const int* __restrict__ rev,
     Box box, const float* __restrict__ z, int nr_rt, int na_rt, int lmax_rt, int nneu_rt,
-    double rc_rd, double rc_ad, const float* __restrict__ wsp,
-    const double* __restrict__ wspd, const int* __restrict__ perm,
+    double rc_rd, double rc_ad, const double* __restrict__ wspd, const int* __restrict__ perm,
     Partial3* __restrict__ pin, float* __restrict__ fown, float* __restrict__ U,
     Partial3* __restrict__ geo) {
   using S = Shape<TR, TA, TL, TNEU>;
   using DT = typename std::conditional<F64, double, float>::type;
+  using D4 = typename std::conditional<F64, f64x4, f32x4>::type;
+  constexpr int MR = S::MR, MA = S::MA, RPL = S::RPL, KT = S::KT, QS = S::QS, NT = S::NT,
+                GS = S::GS;
   const float rc_r = (float)rc_rd, rc_a = (float)rc_ad;
-  constexpr int kMaxR = S::MR, kMaxA = S::MA, kMaxLM = S::MLM, kMaxNeu = S::MNEU;
-  constexpr int kMaxDes = S::MDES;
   const int NR = S::kFixed ? TR : nr_rt;
   const int NA = S::kFixed ? TA : na_rt;
   const int LMAX = S::kFixed ? TL : lmax_rt;
   const int NNEU = S::kFixed ? TNEU : nneu_rt;
   const int NLM = (LMAX + 1) * (LMAX + 1) - 1;
   const int NDES = NR + NA * LMAX;
-  // Compiled shapes with l_max = 4 read LDS four floats at a time: the
-  // network rows, the descriptor and the neurons' w2 sech^2 are padded with
-  // zeros to multiples of 4, and the harmonics rows hold 24 floats.
-  constexpr bool kVec = S::kFixed && TL == 4 && !F64;
-  constexpr int kDes4 = ((kMaxDes + 3) / 4) * 4;
-  constexpr int kRS = kVec ? kDes4 + (kDes4 % 32 == 0 ? 4 : 0) : kMaxDes + 1;
-  constexpr int kNeuRows = kVec ? ((kMaxNeu + 3) / 4) * 4 : kMaxNeu;
-  constexpr int kYS = kVec ? kMaxLM : kMaxLM + 1;
-  const int RS = kVec ? kRS : NDES + 1;  // LDS row of neuron mu: w1[mu][:] (padded)
-  __shared__ __align__(16) float s_w1[kNeuRows * kRS];
-  __shared__ float s_b1[kMaxNeu], s_w2[kMaxNeu];
-  // pairs staged per round: all 64 lanes' pairs, or in float64 two halves of
-  // 32 (half the LDS, so that more waves fit a CU; the sums keep pair order)
-  constexpr int kStage = F64 ? 32 : 64;
-  __shared__ DT s_g[kWaves][kStage][kMaxA + 1];           // angular g_n of the staged pairs
-  __shared__ __align__(16) DT s_y[kWaves][kStage][kYS];   // Yhat_lm of the staged pairs
-  __shared__ __align__(16) DT s_q[kWaves][kDes4];
-  __shared__ float s_dq[kWaves][kMaxDes];
-  __shared__ float s_c[kWaves][kMaxA * kMaxLM];  // c_nlm (float32 path), then a_nlm
-  __shared__ double s_cd[F64 ? kWaves : 1][F64 ? kMaxA * kMaxLM : 1];  // c_nlm in float64
-  __shared__ __align__(16) float s_gmu[kWaves][kNeuRows];
-  if constexpr (kVec) {
-    for (int t = threadIdx.x; t < kNeuRows * kRS; t += blockDim.x) {
-      const int mu = t / kRS, v = t % kRS;
-      s_w1[t] = mu < NNEU && v < NDES ? z[mu * NDES + v] : 0.f;
-    }
-  } else {
-    for (int t = threadIdx.x; t < NNEU * NDES; t += blockDim.x)
-      s_w1[(t / NDES) * RS + t % NDES] = z[t];
-  }
-  for (int t = threadIdx.x; t < NNEU; t += blockDim.x) {
-    s_b1[t] = z[NNEU * NDES + t];
-    s_w2[t] = z[NNEU * (NDES + 1) + t];
-  }
-  const float b2 = z[NNEU * (NDES + 2)];
-  __syncthreads();
 
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int i = (int)xcd_block(blockIdx.x, gridDim.x) * kWaves + wave;
-  if (i >= n) return;  // whole waves leave together; no block barrier below
-  const int cr = cnt_r[i], ca = cnt_a[i];
-  const double xi = pos[i], yi = pos[n + i], zi = pos[2 * n + i];
-  // multicomponent weight of pair (i, j): sqrt(Z_i) sqrt(Z_j), 1 for one species
-  const float wi = wsp ? wsp[perm[i]] : 1.f;
+  // staged pairs of the block's atoms: r_ij and the index of the reverse slot
+  __shared__ float4 s_pair[F64 ? 1 : kAtoms][F64 ? 1 : kRow];
+  __shared__ double s_d[F64 ? 4 : 1][F64 ? kAtoms : 1][F64 ? kRow : 1];  // x, y, z, sqrt(Z_j)
+  __shared__ int s_dst[F64 ? kAtoms : 1][F64 ? kRow : 1];
+  __shared__ unsigned long long s_mask[2][kAtoms];  // slots of the two pair classes
+  __shared__ int s_count[2][kAtoms];                // staged angular pairs, staged pairs
+  // Operands of the per-atom products, one block per wave.  HB pairs of each
+  // of the wave's four atoms at a time (float64: 8, so that two blocks fit a
+  // compute unit).  Descriptor: rows (24 Yhat_lm, g_n); forces: rows (T_n + 1,
+  // T_n'), replaced by the products (24 + 24).
+  constexpr int HB = F64 ? 8 : 16;
+  constexpr int YS = F64 ? 24 + MA + (MA % 2 == 0 ? 1 : 0) : 44;  // DT per descriptor row
+  constexpr int FS = 52;                                          // float per force row
+  constexpr int kBuf = 4 * HB * YS * (int)sizeof(DT) > 4 * HB * FS * 4
+                           ? 4 * HB * YS * (int)sizeof(DT)
+                           : 4 * HB * FS * 4;
+  static_assert(24 + MA <= YS && 8 * RPL <= FS, "operand rows");
+  static_assert(MA * 25 * (int)sizeof(DT) <= kBuf, "moments of one atom");
+  __shared__ __align__(16) char s_buf[kWaves][kBuf];
+  __shared__ __align__(16) DT s_q[kAtoms][QS];  // descriptor, then dU/dq in float32
+  __shared__ __align__(16) float s_g[kAtoms][GS];
+  __shared__ DT s_u[kWaves][kAtoms];
+
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int h = lane >> 4, col = lane & 15;
+  const int al = 4 * wave + h;  // the lane's atom within the block
+  const int i0 = (int)xcd_block(blockIdx.x, gridDim.x) * kAtoms;
   const float rcr_inv = 1.f / rc_r, rca_inv = 1.f / rc_a;
   const double rcr_inv_d = 1.0 / rc_rd, rca_inv_d = 1.0 / rc_ad;
   const float rcr2 = rc_r * rc_r, rca2 = rc_a * rc_a;
-  const int nout = NA * NLM;  // angular moments, lane k owns k, k + 64, ...
-  DT qr[kMaxR];
-  constexpr int kR4 = (kMaxA * 6 + 63) / 64;  // rounds of the four-output groups
-  DT cacc[kVec ? 1 : (kMaxA * kMaxLM + 63) / 64];
-  float4 cacc4[kVec ? kR4 : 1];
-#pragma unroll
-  for (int a = 0; a < kMaxR; ++a) qr[a] = 0;
-#pragma unroll
-  for (int r = 0; r < (kVec ? 1 : (kMaxA * kMaxLM + 63) / 64); ++r) cacc[r] = 0;
-#pragma unroll
-  for (int r = 0; r < (kVec ? kR4 : 1); ++r) cacc4[r] = make_float4(0.f, 0.f, 0.f, 0.f);
   auto wave_lds_sync = [] {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
 
-  // ---- descriptor
-  for (int base = 0; base < cr; base += 64) {
-    const int s = base + lane;
-    DT g[kMaxA], yh[kMaxLM];
+  // ---- staging: thread (a, w) handles slots w, w + 16, w + 32 of atom a
+  const int sa = tid & 15, sw = tid >> 4;
+  const int ia = i0 + sa;
+  const int cra = ia < n ? cnt_r[ia] : 0, caa = ia < n ? cnt_a[ia] : 0;
+  const double xa = ia < n ? pos[ia] : 0.0, ya = ia < n ? pos[n + ia] : 0.0,
+               za = ia < n ? pos[2 * n + ia] : 0.0;
+  int most = cra;
 #pragma unroll
-    for (int a = 0; a < kMaxA; ++a) g[a] = 0;
+  for (int d = 1; d < 16; d <<= 1) most = max(most, __shfl_xor(most, d, 64));
+  const int chunks = (most + kSlots - 1) / kSlots;  // the same for the whole block
+  // slots kSlots c ..; the first time they are seen (write) their pair vectors
+  // and the zero partial forces of pairs beyond r_c^R are written
+  auto stage = [&](int c, bool write) {
+    constexpr int T = kSlots / 16;
+    uint32_t e[T];
+    int rv[T];
+    double pj[T][3], wj[T];
 #pragma unroll
-    for (int m = 0; m < kMaxLM; ++m) yh[m] = 0;
-    if (s < cr) {
-      int j;
-      float dx, dy, dz;
+    for (int t = 0; t < T; ++t) {
+      const int sl = c * kSlots + sw + 16 * t;
+      const size_t idx = sl < cra ? (size_t)sl * n + ia : 0;
+      e[t] = nl[idx];
+      rv[t] = rev[idx];
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int j = c * kSlots + sw + 16 * t < cra ? (int)(e[t] & kAtomMask) : 0;
+      pj[t][0] = pos[j];
+      pj[t][1] = pos[n + j];
+      pj[t][2] = pos[2 * n + j];
+      if constexpr (F64) wj[t] = wspd[perm[j]];
+    }
+    if (tid < 32) s_mask[tid >> 4][tid & 15] = 0ull;
+    __syncthreads();  // the masks are clear, the previous chunk has been read
+    float v[T][3];
+    double d[T][3];
+    int dst[T];
+    unsigned long long ma = 0ull, mr = 0ull;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int sl = c * kSlots + sw + 16 * t;
       if constexpr (F64) {
-        double ex, ey, ez;
-        displacement_d(nl[(size_t)s * n + i], pos, n, xi, yi, zi, box.h, j, ex, ey, ez);
-        dx = (float)ex;
-        dy = (float)ey;
-        dz = (float)ez;
-        // in or out of a cutoff exactly as the float32 partial-force loop decides
-        const float r2 = pair_r2(dx, dy, dz);
-        const double wij = wspd[perm[i]] * wspd[perm[j]];
-        const double r = sqrt(ex * ex + ey * ey + ez * ez);
-        if (r2 < rcr2) {
-          double fc, T[kMaxR];
-          chebyshev_values_d<kMaxR>(r, rcr_inv_d, fc, T);
-          const double wf = wij * fc;
-          qr[0] += wf;
+        image_displacement_d(e[t], pj[t], xa, ya, za, box.h, d[t][0], d[t][1], d[t][2]);
 #pragma unroll
-          for (int a = 1; a < kMaxR; ++a) qr[a] += wf * T[a];
-        }
-        if (s < ca && r2 < rca2) {
-          radial_basis_d<kMaxA>(r, rca_inv_d, NA, g);
-#pragma unroll
-          for (int a = 0; a < kMaxA; ++a) g[a] *= wij;
-          const double rinv = 1.0 / r;
-          harmonics_d(ex * rinv, ey * rinv, ez * rinv, yh);
-        }
+        for (int x = 0; x < 3; ++x) v[t][x] = (float)d[t][x];
       } else {
-        displacement(nl[(size_t)s * n + i], pos, n, xi, yi, zi, box.h, j, dx, dy, dz);
-        const float wij = wsp ? wi * wsp[perm[j]] : 1.f;
-        const float r2 = pair_r2(dx, dy, dz);
-        const float rinv = __builtin_amdgcn_rsqf(r2);
-        const float r = r2 * rinv;
-        if (r2 < rcr2) {  // entries a >= NR are never read
-          float fc, T[kMaxR];
-          chebyshev_values<kMaxR>(r, rcr_inv, fc, T);
-          const float wf = wij * fc;
-          qr[0] += wf;
+        image_displacement(e[t], pj[t][0], pj[t][1], pj[t][2], xa, ya, za, box.h, v[t][0], v[t][1],
+                           v[t][2]);
+      }
+      dst[t] = rv[t] * n + (int)(e[t] & kAtomMask);
+      if (sl >= cra) continue;
+      if (write && geo) geo[(size_t)sl * n + ia] = Partial3{v[t][0], v[t][1], v[t][2]};
+      const float r2 = pair_r2(v[t][0], v[t][1], v[t][2]);
+      if (sl < caa && r2 < rca2)
+        ma |= 1ull << (sw + 16 * t);
+      else if (r2 < rcr2)
+        mr |= 1ull << (sw + 16 * t);
+      else if (write)
+        pin[(size_t)(unsigned)dst[t]] = Partial3{0.f, 0.f, 0.f};
+    }
+    if (ma) atomicOr(&s_mask[0][sa], ma);
+    if (mr) atomicOr(&s_mask[1][sa], mr);
+    __syncthreads();
+    const unsigned long long fa = s_mask[0][sa], fr = s_mask[1][sa];
+    const int na = __popcll(fa);
+    if (sw == 0) {
+      s_count[0][sa] = na;
+      s_count[1][sa] = na + __popcll(fr);
+    }
 #pragma unroll
-          for (int a = 1; a < kMaxR; ++a) qr[a] += wf * T[a];
-        }
-        if (s < ca && r2 < rca2) {
-          radial_basis_n<kMaxA>(r, rca_inv, NA, g, nullptr);
+    for (int t = 0; t < T; ++t) {
+      const unsigned long long bit = 1ull << (sw + 16 * t);
+      if (!((fa | fr) & bit)) continue;
+      const int k = (fa & bit) ? __popcll(fa & (bit - 1)) : na + __popcll(fr & (bit - 1));
+      if constexpr (F64) {
 #pragma unroll
-          for (int a = 0; a < kMaxA; ++a) g[a] *= wij;
-          harmonics(dx * rinv, dy * rinv, dz * rinv, yh);
-        }
+        for (int x = 0; x < 3; ++x) s_d[x][sa][k] = d[t][x];
+        s_d[3][sa][k] = wj[t];
+        s_dst[sa][k] = dst[t];
+      } else {
+        s_pair[sa][k] = make_float4(v[t][0], v[t][1], v[t][2], __int_as_float(dst[t]));
       }
     }
-    for (int half = 0; half < 64 / kStage; ++half) {
-    if (lane / kStage == half) {
+    __syncthreads();
+  };
+  // the wave's four atoms: staged angular pairs (uniform) and the largest counts
+  int n_ang[4], max_ang, max_in;
+  auto counts = [&] {
+    max_ang = 0;
+    max_in = 0;
 #pragma unroll
-      for (int a = 0; a < kMaxA; ++a) s_g[wave][lane % kStage][a] = g[a];
-#pragma unroll
-      for (int m = 0; m < kMaxLM; ++m) s_y[wave][lane % kStage][m] = yh[m];
+    for (int g = 0; g < 4; ++g) {
+      n_ang[g] = __builtin_amdgcn_readfirstlane(s_count[0][4 * wave + g]);
+      max_ang = max(max_ang, n_ang[g]);
+      max_in = max(max_in, __builtin_amdgcn_readfirstlane(s_count[1][4 * wave + g]));
     }
-    wave_lds_sync();
-    // pairs past the list's angular part have g = 0: skip them
-    const int np = max(0, min(kStage, min(cr, ca) - base - half * kStage));
-    if constexpr (kVec) {  // lane k owns outputs (n, 4 m4 .. 4 m4 + 3), k = 6 n + m4
+  };
+
+  const double wi = F64 ? (i0 + al < n ? wspd[perm[i0 + al]] : 0.0) : 1.0;
+
+  // ---- descriptor
+  DT qr[MR];
+  D4 c[4][2];  // moments of atom g, tile t: n = RPL h + r, lm = 16 t + col
 #pragma unroll
-      for (int r = 0; r < kR4; ++r) {
-        const int k = lane + 64 * r;
-        if (k < NA * 6) {
-          const int a = k / 6, m4 = k % 6;
-          float4 acc = cacc4[r];
-          for (int p = 0; p < np; ++p) {
-            const float gv = s_g[wave][p][a];
-            const float4 y4 = *reinterpret_cast<const float4*>(&s_y[wave][p][4 * m4]);
-            acc.x += gv * y4.x;
-            acc.y += gv * y4.y;
-            acc.z += gv * y4.z;
-            acc.w += gv * y4.w;
-          }
-          cacc4[r] = acc;
+  for (int a = 0; a < MR; ++a) qr[a] = 0;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) c[g][t] = D4{0, 0, 0, 0};
+  // row `col` of the moments' first operand holds n = RPL oh + orr
+  int oh, orr;
+  mma_owner<DT>(col, oh, orr);
+  const int arow = orr < RPL && RPL * oh + orr < MA ? RPL * oh + orr : -1;
+  DT* const yg = reinterpret_cast<DT*>(s_buf[wave]);
+  for (int ch = 0; ch < chunks; ++ch) {
+    stage(ch, true);
+    counts();
+    const int my_ang = s_count[0][al], my_in = s_count[1][al];
+    for (int base = 0; base < max_in; base += 16) {
+      const int k = base + col;
+      const bool rad = k < my_in, ang = k < my_ang;
+      DT x = 1, y = 0, zz = 0, w = 1;
+      if (rad) {
+        if constexpr (F64) {
+          x = s_d[0][al][k];
+          y = s_d[1][al][k];
+          zz = s_d[2][al][k];
+          w = wi * s_d[3][al][k];
+        } else {
+          const float4 v = s_pair[al][k];
+          x = v.x;
+          y = v.y;
+          zz = v.z;
         }
       }
-    } else {
-#pragma unroll
-      for (int r = 0; r < (kMaxA * kMaxLM + 63) / 64; ++r) {
-        const int k = lane + 64 * r;
-        if (k < nout) {
-          const int a = k / NLM, m = k % NLM;
-          DT acc = cacc[r];
-          for (int p = 0; p < np; ++p) acc += s_g[wave][p][a] * s_y[wave][p][m];
-          cacc[r] = acc;
-        }
+      DT r, rinv;
+      if constexpr (F64) {
+        r = sqrt(x * x + y * y + zz * zz);
+        rinv = 1.0 / r;
+      } else {
+        const float r2 = pair_r2(x, y, zz);
+        rinv = __builtin_amdgcn_rsqf(r2);
+        r = r2 * rinv;
       }
-    }
-    wave_lds_sync();
-    }
-  }
-  // radial components q_0 = R_0, q_n = (R_n + R_0)/2, and angular moments to LDS
-  const DT r0 = wave_sum(qr[0]);
-  if (lane == 0) s_q[wave][0] = r0;
-#pragma unroll
-  for (int a = 1; a < kMaxR; ++a) {
-    const DT v = wave_sum(qr[a]);
-    if (lane == 0 && a < NR) s_q[wave][a] = (DT)0.5 * (v + r0);
-  }
-  if constexpr (kVec) {
-#pragma unroll
-    for (int r = 0; r < kR4; ++r) {
-      const int k = lane + 64 * r;
-      if (k < NA * 6) {
-        s_c[wave][4 * k] = cacc4[r].x;  // (n, 4 m4 + c) is n 24 + 4 m4 + c = 4 k + c
-        s_c[wave][4 * k + 1] = cacc4[r].y;
-        s_c[wave][4 * k + 2] = cacc4[r].z;
-        s_c[wave][4 * k + 3] = cacc4[r].w;
-      }
-    }
-    for (int v = NDES + lane; v < kDes4; v += 64) s_q[wave][v] = 0.f;  // padding
-  } else {
-#pragma unroll
-    for (int r = 0; r < (kMaxA * kMaxLM + 63) / 64; ++r) {
-      const int k = lane + 64 * r;
-      if (k < nout) {
+      if (rad) {  // entries a >= NR are never read
+        DT fc, T[MR];
         if constexpr (F64)
-          s_cd[wave][k] = cacc[r];
+          chebyshev_values_d<MR>(r, rcr_inv_d, fc, T);
         else
-          s_c[wave][k] = cacc[r];
-      }
-    }
-  }
-  wave_lds_sync();
-  // angular components q_nl = sum_m c_nlm^2
-  if (lane < NA * LMAX) {
-    const int a = lane / LMAX, l = lane % LMAX + 1;
-    DT s2 = 0;
-    for (int m = 0; m < 2 * l + 1; ++m) {
-      const int k = a * NLM + l * l - 1 + m;
-      const DT v = F64 ? (DT)s_cd[F64 ? wave : 0][F64 ? k : 0] : (DT)s_c[wave][k];
-      s2 += v * v;
-    }
-    s_q[wave][NR + a * LMAX + (l - 1)] = s2;
-  }
-  wave_lds_sync();
-
-  // ---- network (Eqs. nn1, nn2): lane mu is neuron mu
-  DT u = 0;
-  if (lane < NNEU) {
-    DT act = -(DT)s_b1[lane];
-    if constexpr (kVec) {
-#pragma unroll 4
-      for (int v4 = 0; v4 < kDes4 / 4; ++v4) {
-        const float4 w4 = *reinterpret_cast<const float4*>(&s_w1[lane * kRS + 4 * v4]);
-        const float4 q4 = *reinterpret_cast<const float4*>(&s_q[wave][4 * v4]);
-        act += w4.x * q4.x;
-        act += w4.y * q4.y;
-        act += w4.z * q4.z;
-        act += w4.w * q4.w;
-      }
-    } else {
-      for (int v = 0; v < NDES; ++v) act += (DT)s_w1[lane * RS + v] * s_q[wave][v];
-    }
-    if constexpr (F64) {
-      const double ea = exp(-2.0 * fabs(act));
-      const double inv = 1.0 / (1.0 + ea);
-      const double th = copysign((1.0 - ea) * inv, act);
-      u = (double)s_w2[lane] * th;
-      s_gmu[wave][lane] = (float)((double)s_w2[lane] * (4.0 * ea * inv * inv));
-    } else {
-      const float ea = __expf(-2.f * fabsf(act));
-      const float inv = __builtin_amdgcn_rcpf(1.f + ea);
-      const float th = copysignf((1.f - ea) * inv, act);
-      u = s_w2[lane] * th;
-      s_gmu[wave][lane] = s_w2[lane] * (4.f * ea * inv * inv);
-    }
-  } else if (kVec && lane < kNeuRows) {
-    s_gmu[wave][lane] = 0.f;  // padding (its w1 row is zero too)
-  }
-  u = wave_sum(u) - (DT)b2;
-  if (lane == 0) U[i] = (float)u;
-  wave_lds_sync();
-  // dU/dq_v: lane v (two rounds for up to 128 descriptor components)
-  for (int v = lane; v < NDES; v += 64) {
-    float d = 0.f;
-    if constexpr (kVec) {
-#pragma unroll 2
-      for (int m4 = 0; m4 < kNeuRows / 4; ++m4) {
-        const float4 g4 = *reinterpret_cast<const float4*>(&s_gmu[wave][4 * m4]);
-        d += g4.x * s_w1[(4 * m4) * kRS + v];
-        d += g4.y * s_w1[(4 * m4 + 1) * kRS + v];
-        d += g4.z * s_w1[(4 * m4 + 2) * kRS + v];
-        d += g4.w * s_w1[(4 * m4 + 3) * kRS + v];
-      }
-    } else {
-      for (int mu = 0; mu < NNEU; ++mu) d += s_gmu[wave][mu] * s_w1[mu * RS + v];
-    }
-    s_dq[wave][v] = d;
-  }
-  wave_lds_sync();
-  // a_nlm = 2 dU/dq_nl c_nlm
+          chebyshev_values<MR>(r, rcr_inv, fc, T);
+        const DT wf = F64 ? w * fc : fc;
+        qr[0] += wf;
 #pragma unroll
-  for (int r = 0; r < (kMaxA * kMaxLM + 63) / 64; ++r) {
-    const int k = lane + 64 * r;
-    if (k < nout) {
-      const int a = k / NLM, m = k % NLM;
-      int l = 1;
-      while ((l + 1) * (l + 1) - 1 <= m) ++l;
-      if constexpr (F64)
-        s_c[wave][k] = (float)(2.0 * (double)s_dq[wave][NR + a * LMAX + (l - 1)] *
-                               s_cd[F64 ? wave : 0][F64 ? k : 0]);
-      else
-        s_c[wave][k] = 2.f * s_dq[wave][NR + a * LMAX + (l - 1)] * s_c[wave][k];
+        for (int a = 1; a < MR; ++a) qr[a] += wf * T[a];
+      }
+      if (base >= max_ang) continue;  // the wave's angular pairs are done
+      DT gn[MA], yh[24];
+#pragma unroll
+      for (int a = 0; a < MA; ++a) gn[a] = 0;
+#pragma unroll
+      for (int m = 0; m < 24; ++m) yh[m] = 0;
+      if (ang) {
+        if constexpr (F64) {
+          radial_basis_d<MA>(r, rca_inv_d, NA, gn);
+#pragma unroll
+          for (int a = 0; a < MA; ++a) gn[a] *= w;
+          harmonics_d(x * rinv, y * rinv, zz * rinv, yh);
+        } else {
+          radial_basis_n<MA>(r, rca_inv, NA, gn, nullptr);
+          harmonics(x * rinv, y * rinv, zz * rinv, yh);
+        }
+      }
+#pragma unroll
+      for (int half = 0; half < 16 / HB; ++half) {
+        if (base + HB * half >= max_ang) break;
+        if (col / HB == half) {
+          DT* row = yg + (h * HB + col % HB) * YS;
+          if constexpr (F64) {
+#pragma unroll
+            for (int m = 0; m < 24; ++m) row[m] = yh[m];
+#pragma unroll
+            for (int a = 0; a < MA; ++a) row[24 + a] = gn[a];
+          } else {
+#pragma unroll
+            for (int m = 0; m < 24; m += 4)
+              *reinterpret_cast<float4*>(row + m) =
+                  make_float4(yh[m], yh[m + 1], yh[m + 2], yh[m + 3]);
+#pragma unroll
+            for (int a = 0; a < MA; a += 4)
+              *reinterpret_cast<float4*>(row + 24 + a) =
+                  make_float4(gn[a], a + 1 < MA ? gn[a + 1] : 0.f, a + 2 < MA ? gn[a + 2] : 0.f,
+                              a + 3 < MA ? gn[a + 3] : 0.f);
+          }
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int np = n_ang[g] - base - HB * half;  // uniform; pairs past it are zero
+#pragma unroll
+          for (int st = 0; st < HB / 4; ++st) {
+            if (4 * st >= np) break;
+            const DT* row = yg + (g * HB + 4 * st + h) * YS;
+            const DT av = arow >= 0 ? row[24 + (arow >= 0 ? arow : 0)] : (DT)0;
+            c[g][0] = mma(av, row[col], c[g][0]);
+            c[g][1] = mma(av, col < 8 ? row[16 + (col & 7)] : (DT)0, c[g][1]);
+          }
+        }
+        wave_lds_sync();
+      }
     }
   }
-  wave_lds_sync();
-  // row 0 becomes a'_0lm = 2 a_0lm + sum_{n>=1} a_nlm, the constant part of
-  // sum_n a_nlm (T_n + 1)
-  if (lane < NLM) {
-    float s0 = 2.f * s_c[wave][lane];
-    for (int a = 1; a < NA; ++a) s0 += s_c[wave][a * NLM + lane];
-    s_c[wave][lane] = s0;
+  // radial components q_0 = R_0, q_n = (R_n + R_0)/2
+  {
+    const DT r0 = atom_sum(qr[0]);
+    if (col == 0) s_q[al][0] = r0;
+#pragma unroll
+    for (int a = 1; a < MR; ++a) {
+      const DT v = atom_sum(qr[a]);
+      if (col == 0 && a < NR) s_q[al][a] = (DT)0.5 * (v + r0);
+    }
+    for (int v = NDES + col; v < QS; v += 16) s_q[al][v] = 0;  // padding
   }
-  // sum_n dU/dq_n over the radial components
-  float dqs = 0.f;
-  for (int a = 0; a < NR; ++a) dqs += s_dq[wave][a];
-  wave_lds_sync();
+  // angular components q_nl = sum_m c_nlm^2, one atom of the wave at a time
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+#pragma unroll
+    for (int r = 0; r < RPL; ++r) {
+      const int nn = RPL * h + r;
+      if (nn < NA) {
+        yg[nn * 25 + col] = c[g][0][r];
+        if (col < 8) yg[nn * 25 + 16 + col] = c[g][1][r];
+      }
+    }
+    wave_lds_sync();
+    for (int v = lane; v < NA * LMAX; v += 64) {
+      const int a = v / LMAX, l = v % LMAX + 1;
+      DT s2 = 0;
+      for (int m = 0; m < 2 * l + 1; ++m) {
+        const DT cm = yg[a * 25 + l * l - 1 + m];
+        s2 += cm * cm;
+      }
+      s_q[4 * wave + g][NR + v] = s2;
+    }
+    wave_lds_sync();
+  }
+  __syncthreads();
 
-  // ---- partial forces: lane p is pair p
+  // ---- network (Eqs. nn1, nn2): wave w evaluates neurons 16 w .. 16 w + 15
+  if (wave < NT) {
+    int nh, nrr;
+    mma_owner<DT>(col, nh, nrr);
+    const int mu_a = 16 * wave + 4 * nh + nrr;  // row `col` of W1
+    float wv[KT][4];
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int v = 16 * t + 4 * h + e;
+        wv[t][e] = mu_a < NNEU && v < NDES ? z[mu_a * NDES + v] : 0.f;
+      }
+    float b1[4], w2[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int mu = 16 * wave + 4 * h + r;
+      b1[r] = mu < NNEU ? z[NNEU * NDES + mu] : 0.f;
+      w2[r] = mu < NNEU ? z[NNEU * (NDES + 1) + mu] : 0.f;
+    }
+    D4 act = {0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) act = mma((DT)wv[t][e], s_q[col][16 * t + 4 * h + e], act);
+    DT up = 0;
+    float gm[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      // tanh and its derivative 1 - tanh^2 from e = exp(-2|a|) (no cancellation)
+      const DT x = act[r] - (DT)b1[r];
+      if constexpr (F64) {
+        const double ea = exp(-2.0 * fabs(x));
+        const double inv = 1.0 / (1.0 + ea);
+        up += (double)w2[r] * copysign((1.0 - ea) * inv, x);
+        gm[r] = (float)((double)w2[r] * (4.0 * ea * inv * inv));
+      } else {
+        const float ea = __expf(-2.f * fabsf(x));
+        const float inv = __builtin_amdgcn_rcpf(1.f + ea);
+        up += w2[r] * copysignf((1.f - ea) * inv, x);
+        gm[r] = w2[r] * (4.f * ea * inv * inv);
+      }
+    }
+    up += __shfl_xor(up, 16, 64);
+    up += __shfl_xor(up, 32, 64);
+    if (h == 0) s_u[wave][col] = up;
+    *reinterpret_cast<float4*>(&s_g[col][16 * wave + 4 * h]) =
+        make_float4(gm[0], gm[1], gm[2], gm[3]);
+  }
+  __syncthreads();
+  if (tid < kAtoms && i0 + tid < n) {
+    DT u = s_u[0][tid];
+#pragma unroll
+    for (int w = 1; w < NT; ++w) u += s_u[w][tid];
+    U[i0 + tid] = (float)(u - (DT)z[NNEU * (NDES + 2)]);
+  }
+  // dU/dq = W1^T G: wave w forms components 16 d .. 16 d + 15, d = w, w + 4, ...
+  float* const dq0 = reinterpret_cast<float*>(&s_q[0][0]);  // [kAtoms][QS]
+  for (int d = wave; d < KT; d += kWaves) {
+    const int v = 16 * d + col;
+    float wv[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int mu = 16 * t + 4 * h + e;
+        wv[t][e] = mu < NNEU && v < NDES ? z[mu * NDES + v] : 0.f;
+      }
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = mma(wv[t][e], s_g[col][16 * t + 4 * h + e], acc);
+    *reinterpret_cast<float4*>(dq0 + col * QS + 16 * d + 4 * h) =
+        make_float4(acc[0], acc[1], acc[2], acc[3]);
+  }
+  __syncthreads();
+
+  // ---- partial forces
+  // a_nlm = 2 dU/dq_nl c_nlm, the second operand of the products over n
+  float an[4][2][RPL];
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int lm = 16 * t + col, l = l_of(lm);
+#pragma unroll
+      for (int r = 0; r < RPL; ++r) {
+        const int nn = RPL * h + r;
+        const bool in = nn < NA && lm < NLM;
+        const float dq = dq0[(4 * wave + g) * QS + (in ? NR + nn * LMAX + (l - 1) : 0)];
+        an[g][t][r] = in ? (float)((DT)2 * (DT)dq * c[g][t][r]) : 0.f;
+      }
+    }
+  const float* const dq = dq0 + al * QS;
+  float dqs = 0.f;  // sum_n dU/dq_n over the radial components
+  for (int a = 0; a < NR; ++a) dqs += dq[a];
+  float* const tb = reinterpret_cast<float*>(s_buf[wave]);
   float fx = 0.f, fy = 0.f, fz = 0.f;
-  for (int base = 0; base < cr; base += 64) {
-    const int s = base + lane;
-    if (s < cr) {
-      const size_t idx = (size_t)s * n + i;
-      int j;
-      float dx, dy, dz;
-      displacement(nl[idx], pos, n, xi, yi, zi, box.h, j, dx, dy, dz);
-      if (geo) geo[idx] = Partial3{dx, dy, dz};  // r_ij for pass 2's virial
-      const int dst = rev[idx] * n + j;
+  for (int cc = 0; cc < chunks; ++cc) {
+    // last chunk first: it is the one that is staged
+    if (cc > 0) {
+      stage(chunks - 1 - cc, false);
+      counts();
+    }
+    const int my_ang = s_count[0][al], my_in = s_count[1][al];
+    for (int base = 0; base < max_in; base += 16) {
+      const int k = base + col;
+      const bool rad = k < my_in, ang = k < my_ang;
+      float dx = 1.f, dy = 0.f, dz = 0.f, wij = 1.f;
+      int dst = 0;
+      if (rad) {
+        if constexpr (F64) {
+          dx = (float)s_d[0][al][k];
+          dy = (float)s_d[1][al][k];
+          dz = (float)s_d[2][al][k];
+          wij = (float)wi * (float)s_d[3][al][k];
+          dst = s_dst[al][k];
+        } else {
+          const float4 v = s_pair[al][k];
+          dx = v.x;
+          dy = v.y;
+          dz = v.z;
+          dst = __float_as_int(v.w);
+        }
+      }
       const float r2 = pair_r2(dx, dy, dz);
       const float rinv = __builtin_amdgcn_rsqf(r2);
       const float r = r2 * rinv;
       const float x = dx * rinv, y = dy * rinv, z = dz * rinv;
       float px = 0.f, py = 0.f, pz = 0.f;
-      if (r2 < rcr2) {
+      if (rad) {
         // sum_n dU/dq_n g_n' = f_c' (S_1 + sum_n dU/dq_n)/2 + f_c (dx/dr) S_2/2
-        float fc, dfc, dxdr, T[kMaxR], dT[kMaxR];
-        chebyshev_terms<kMaxR>(r, rcr_inv, fc, dfc, dxdr, T, dT);
-        float s1 = s_dq[wave][0], s2 = 0.f;
+        float fc, dfc, dxdr, T[MR], dT[MR];
+        chebyshev_terms<MR>(r, rcr_inv, fc, dfc, dxdr, T, dT);
+        float s1 = dq[0], s2 = 0.f;
 #pragma unroll
-        for (int a = 1; a < kMaxR; ++a)
+        for (int a = 1; a < MR; ++a)
           if (a < NR) {
-            s1 += s_dq[wave][a] * T[a];
-            s2 += s_dq[wave][a] * dT[a];
+            s1 += dq[a] * T[a];
+            s2 += dq[a] * dT[a];
           }
         const float f = 0.5f * (dfc * (s1 + dqs) + fc * dxdr * s2);
         px += f * x;
         py += f * y;
         pz += f * z;
       }
-      if (s < ca && r2 < rca2) {
-        float fc, dfc, dxdr, T[kMaxA], dT[kMaxA];
-        chebyshev_terms<kMaxA>(r, rca_inv, fc, dfc, dxdr, T, dT);
-        const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
-        const float xyz = xy * z;
-        (void)xyz;
-        // per lm: At = a'_0 + sum_{n>=1} a_n T_n, D = sum_{n>=1} a_n T_n';
-        // A = f_c At/2 multiplies the harmonic's gradient and
-        // B = f_c' At/2 + f_c (dx/dr) D/2 the harmonic
-        float st = 0.f, sd = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-        const float* aw = s_c[wave];
-#define NEP_PF(idx, YV, GX, GY, GZ)                     \
-  if ((idx) < NLM) {                                    \
-    float At = aw[(idx)], D = 0.f;                      \
-    for (int a = 1; a < NA; ++a) {                      \
-      const float c = aw[a * NLM + (idx)];              \
-      At += c * T[a];                                   \
-      D += c * dT[a];                                   \
-    }                                                   \
-    st += At * (YV);                                    \
-    sd += D * (YV);                                     \
-    gx += At * (GX);                                    \
-    gy += At * (GY);                                    \
-    gz += At * (GZ);                                    \
-  }
-        NEP_YLM_TABLE(NEP_PF)
+      if (base < max_ang) {
+        float fc, dfc, dxdr;
+        float At[24], D[24];
+        {
+          float T[MA], dT[MA];
+          chebyshev_terms<MA>(r, rca_inv, fc, dfc, dxdr, T, dT);
+#pragma unroll
+          for (int half = 0; half < 16 / HB; ++half) {
+            if (base + HB * half >= max_ang) break;
+            float* const row = tb + (h * HB + col % HB) * FS;
+            if (col / HB == half) {
+              // T_n + 1 and T_n' for n < 4 RPL (n >= N_A meet a_nlm = 0)
+              float t1[4 * RPL], t2[4 * RPL];
+#pragma unroll
+              for (int a = 0; a < 4 * RPL; ++a) {
+                t1[a] = a < MA ? T[a < MA ? a : 0] + 1.f : 0.f;
+                t2[a] = a < MA ? dT[a < MA ? a : 0] : 0.f;
+              }
+#pragma unroll
+              for (int a = 0; a < 4 * RPL; a += 4) {
+                *reinterpret_cast<float4*>(row + a) =
+                    make_float4(t1[a], t1[a + 1], t1[a + 2], t1[a + 3]);
+                *reinterpret_cast<float4*>(row + 4 * RPL + a) =
+                    make_float4(t2[a], t2[a + 1], t2[a + 2], t2[a + 3]);
+              }
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              if (base + HB * half >= n_ang[g]) continue;  // uniform
+              float* const rows = tb + g * HB * FS;
+              const float* const src = rows + (col % HB) * FS;
+              float t1[RPL], t2[RPL];
+#pragma unroll
+              for (int q = 0; q < RPL; ++q) {
+                t1[q] = src[RPL * h + q];
+                t2[q] = src[4 * RPL + RPL * h + q];
+              }
+              f32x4 p1[2], p2[2];
+#pragma unroll
+              for (int t = 0; t < 2; ++t) {
+                p1[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                p2[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q < RPL; ++q) {
+                  p1[t] = mma(t1[q], an[g][t][q], p1[t]);
+                  p2[t] = mma(t2[q], an[g][t][q], p2[t]);
+                }
+              }
+              wave_lds_sync();  // every lane has read the atom's rows
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                if (4 * h + q >= HB) break;
+                float* const o = rows + (4 * h + q) * FS;
+                o[col] = p1[0][q];
+                o[24 + col] = p2[0][q];
+                if (col < 8) {
+                  o[16 + col] = p1[1][q];
+                  o[40 + col] = p2[1][q];
+                }
+              }
+            }
+            wave_lds_sync();
+            if (col / HB == half) {
+#pragma unroll
+              for (int m = 0; m < 24; m += 4) {
+                const float4 v1 = *reinterpret_cast<const float4*>(row + m);
+                const float4 v2 = *reinterpret_cast<const float4*>(row + 24 + m);
+                At[m] = v1.x, At[m + 1] = v1.y, At[m + 2] = v1.z, At[m + 3] = v1.w;
+                D[m] = v2.x, D[m + 1] = v2.y, D[m + 2] = v2.z, D[m + 3] = v2.w;
+              }
+            }
+            wave_lds_sync();  // the rows are written again in the next round
+          }
+        }
+        if (ang) {
+          const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
+          const float xyz = xy * z;
+          (void)xyz;
+          // per lm: A = f_c At/2 multiplies the harmonic's gradient and
+          // B = f_c' At/2 + f_c (dx/dr) D/2 the harmonic
+          float st = 0.f, sd = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
+#define NEP_PF(idx, YV, GX, GY, GZ) \
+  st += At[idx] * (YV);             \
+  sd += D[idx] * (YV);              \
+  gx += At[idx] * (GX);             \
+  gy += At[idx] * (GY);             \
+  gz += At[idx] * (GZ);
+          NEP_YLM_TABLE(NEP_PF)
 #undef NEP_PF
-        const float hf = 0.5f * fc;
-        const float sb = 0.5f * (dfc * st + fc * dxdr * sd);
-        gx *= hf;
-        gy *= hf;
-        gz *= hf;
-        const float ug = x * gx + y * gy + z * gz;
-        px += sb * x + (gx - x * ug) * rinv;
-        py += sb * y + (gy - y * ug) * rinv;
-        pz += sb * z + (gz - z * ug) * rinv;
+          const float hf = 0.5f * fc;
+          const float sb = 0.5f * (dfc * st + fc * dxdr * sd);
+          gx *= hf;
+          gy *= hf;
+          gz *= hf;
+          const float ug = x * gx + y * gy + z * gz;
+          px += sb * x + (gx - x * ug) * rinv;
+          py += sb * y + (gy - y * ug) * rinv;
+          pz += sb * z + (gz - z * ug) * rinv;
+        }
       }
-      if (wsp) {  // every term of the pair carries its weight once
-        const float wij = wi * wsp[perm[j]];
-        px *= wij;
-        py *= wij;
-        pz *= wij;
+      if (rad) {
+        if constexpr (F64) {  // every term of the pair carries its weight once
+          px *= wij;
+          py *= wij;
+          pz *= wij;
+        }
+        fx += px;
+        fy += py;
+        fz += pz;
+        pin[(size_t)(unsigned)dst] = Partial3{px, py, pz};
       }
-      fx += px;
-      fy += py;
-      fz += pz;
-      pin[(size_t)(unsigned)dst] = Partial3{px, py, pz};
     }
   }
-  fx = wave_sum(fx);
-  fy = wave_sum(fy);
-  fz = wave_sum(fz);
-  if (lane == 0) {
-    fown[i] = fx;
-    fown[n + i] = fy;
-    fown[2 * n + i] = fz;
+  fx = atom_sum(fx);
+  fy = atom_sum(fy);
+  fz = atom_sum(fz);
+  if (col == 0 && i0 + al < n) {
+    fown[i0 + al] = fx;
+    fown[n + i0 + al] = fy;
+    fown[2 * n + i0 + al] = fz;
   }
 }
 
@@ -597,14 +803,12 @@ template <int TR, int TA, int TL, int TNEU, bool F64>
 void launch_shape(nep_ctx ctx, const double* pos) {
   const System& s = ctx->sys;
   const nep_hyper& h = ctx->hyper;
-  const bool species = ctx->species_on();
   launch_kernel(ctx, true, true, k_partials_generic<TR, TA, TL, TNEU, F64>,
-                dim3(blocks_for(s.n, kWaves)), dim3(64 * kWaves), s.n, pos,
+                dim3(blocks_for(s.n, kAtoms)), dim3(64 * kWaves), s.n, pos,
                 (const uint32_t*)s.nl.ptr, (const int*)s.cnt_r.ptr, (const int*)s.cnt_a.ptr,
                 (const int*)s.rev.ptr, s.box, (const float*)ctx->z.ptr, h.n_max_radial + 1,
                 h.n_max_angular + 1, h.l_max, h.n_neuron, h.rc_radial, h.rc_angular,
-                species ? (const float*)ctx->species_w.ptr : (const float*)nullptr,
-                species ? (const double*)ctx->species_wd.ptr : (const double*)nullptr,
+                F64 ? (const double*)ctx->species_wd.ptr : (const double*)nullptr,
                 (const int*)s.perm.ptr, ctx->p.ptr, ctx->fown.ptr, ctx->U.ptr,
                 s.n <= kPairVectorMaxAtoms ? ctx->geo.ptr : (Partial3*)nullptr);
 }

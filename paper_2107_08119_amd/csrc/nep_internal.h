@@ -239,8 +239,7 @@ struct nep_ctx_s {
   // multicomponent system (caller order): sqrt(Z) per atom and optional masses
   int species_n = 0;              // atoms the arrays describe; 0 = one species
   bool have_masses = false;
-  nep::DevBuf<float> species_w;   // [n] sqrt(atomic number)
-  nep::DevBuf<double> species_wd;  // [n] the same in float64 (descriptor sums)
+  nep::DevBuf<double> species_wd;  // [n] sqrt(atomic number)
   nep::DevBuf<double> masses;     // [n] amu
   nep::DevBuf<double> totals;     // [16]
   nep::DevBuf<int> flags;         // [kFlagWords]: kNumFlags flags, two 64-bit pair totals
