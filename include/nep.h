@@ -64,7 +64,7 @@ typedef enum {
  * 0 < rc_angular <= rc_radial.  Force evaluation and MD: (n_max^R, n_max^A,
  * l_max, N_neu) = (8, 4, 4, 30) has tuned kernels (2, 4 or 8 lanes per atom);
  * any n_max^R, n_max^A <= 15, 1 <= l_max <= 4, N_neu <= 64 (e.g. the paper's
- * 80-50-1 silicon model) runs on a one-wave-per-atom kernel; other sizes
+ * 80-50-1 silicon model) runs on a kernel of its own; other sizes
  * return NEP_ENOTIMPL.  Datasets, SNES and the backward need (8, 4, 4, 30). */
 typedef struct {
   double rc_radial, rc_angular;
@@ -147,8 +147,8 @@ nep_status nep_get_neighbors(nep_ctx ctx, int* cnt_radial_dev, int* cnt_angular_
  * the arrays are copied (host memory, synchronous) and persist across list
  * rebuilds until a build with another atom count or a call with
  * atomic_numbers_host == NULL, which returns to one species with the mass of
- * each call.  With species set, forces come from the one-wave-per-atom
- * kernel (nep_autotune reports 64 lanes).  The training entry points
+ * each call.  With species set, forces come from the kernel of every model
+ * size (nep_autotune reports 64 lanes).  The training entry points
  * (datasets, SNES, backward) remain one-species.  NEP_EINVAL for n or a value
  * out of range. */
 nep_status nep_set_species(nep_ctx ctx, int n, const int* atomic_numbers_host,
@@ -454,8 +454,9 @@ nep_status nep_autotune(nep_ctx ctx, const double* pos_dev, int reps, int* lanes
                         double* ms_out);
 
 /* Use `lanes` (2, 4 or 8) lanes per atom in the descriptor/network/partial-
- * force kernel of this context, or 64 for the one-wave-per-atom kernel that
- * every model size uses.  NEP_EINVAL for other values. */
+ * force kernel of this context, or 64 for the kernel of every model size.
+ * Until this call or nep_autotune the shape follows the system's size.
+ * NEP_EINVAL for other values. */
 nep_status nep_set_tile(nep_ctx ctx, int lanes);
 
 #ifdef __cplusplus

@@ -579,10 +579,19 @@ void launch_partials_shape(nep_ctx ctx, const double* pos, bool first, bool last
                 s.n <= kPairVectorMaxAtoms ? ctx->geo.ptr : (Partial3*)nullptr);
 }
 
+// Tile shape of the default model by the system's size: the most lanes per atom
+// whose blocks still find a compute unit each (256 of them), since below that a
+// wave's own chain sets the time.  Measured on diamond cells (us): 1,000 atoms
+// 8.9 with the kernel of every model size (one atom per wave), 14.6 with 8
+// lanes, 18.5 with 4; 4,096 atoms 13.5, 15.0 and 19.0; 8,000 atoms 16.6, 15.7
+// and 19.7; 17,576 atoms 39.4, 31.2 and 27.6.
+inline int default_variant(int n) { return n <= 16 * 256 ? 3 : (n <= 32 * 256 ? 2 : 1); }
+
 hipError_t launch_partials(nep_ctx ctx, const double* pos, int variant) {
   const System& s = ctx->sys;
   if (s.n == 0) return hipSuccess;
   if (variant < 0) variant = ctx->md_variant;
+  if (variant < 0) variant = default_variant(s.n);
   if (!is_default_variant(ctx->hyper) || variant == 3 || ctx->species_on())
     return launch_partials_generic(ctx, pos);
   switch (variant) {

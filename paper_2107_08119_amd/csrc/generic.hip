@@ -1,20 +1,20 @@
 // Pass 1 for any model size within n_max^R, n_max^A <= 15, l_max <= 4 and
 // at most 64 hidden neurons (the paper's models of Sec. III, e.g. 80-50-1):
-// 16 atoms per block of four waves, 16 lanes per atom.
+// blocks of four waves with four atoms per wave, 16 lanes each, or in small
+// systems one atom per wave.
 //
 // The terms are those of nep_terms.h (factorised angular descriptor, network,
 // partial force of Sec. II D):
 //   * staging: the block reads the list and reverse slots of its atoms, 48
-//     slots at a time with atoms fastest (coalesced), classifies the pairs and
-//     packs those inside a cutoff per atom in LDS, angular ones first; the
+//     (64) slots at a time with atoms fastest, classifies the pairs and packs those inside a cutoff per atom in LDS, angular ones first; the
 //     pair vectors r_ij go to the atom's own slots for pass 2 (systems of up
 //     to kPairVectorMaxAtoms atoms);
-//   * radial q_n: each lane adds f_c T_n of its pairs, the atom's 16 lanes are
+//   * radial q_n: each lane adds f_c T_n of its pairs, the atom's lanes are
 //     summed in a fixed order, q_n = (R_n + R_0)/2 (g_n = f_c (T_n + 1)/2);
 //   * angular moments c_nlm = sum_j g_n(r_ij) Yhat_lm(u_ij): per atom the
 //     product (n x pairs)(pairs x lm) as 16x16x4 MFMA steps, the operands
 //     passed through LDS; the sums stay in registers;
-//   * network: W1 Q^T and W1^T G for the block's 16 atoms on the matrix cores,
+//   * network: W1 Q^T and W1^T G for the block's atoms on the matrix cores,
 //     a wave per 16 neurons and per 16 descriptor components;
 //   * partial forces: lane p evaluates pair p of its atom; the sums over n of
 //     a_nlm (T_n + 1) and a_nlm T_n' for all lm are two more products per 16
@@ -45,13 +45,7 @@ namespace {
 
 // Largest sizes of the runtime-sized instantiation.
 constexpr int kMaxR = 16, kMaxA = 16, kMaxNeu = 64;
-constexpr int kAtoms = 16;  // atoms per block, 16 lanes each
-constexpr int kWaves = 4;
-// List slots per atom staged at a time: most lists with a 0.5 A skin fit at
-// once, longer ones (80 slots in PbTe) take further rounds of staging.
-constexpr int kSlots = 48;
-constexpr int kRow = kSlots + 1;  // LDS row of an atom's pairs (odd: no bank aliasing)
-
+constexpr int kWaves = 4;  // per block
 // Sizes of one instantiation: TR > 0 fixes (n_max^R + 1, n_max^A + 1, l_max,
 // N_neu) = (TR, TA, TL, TNEU) at compile time (loops unrolled, LDS sized to
 // the model); TR == 0 takes them at run time up to the maxima above.
@@ -90,12 +84,19 @@ __device__ __forceinline__ void mma_owner(int i, int& h, int& r) {
   r = sizeof(DT) == 8 ? i >> 2 : i & 3;
 }
 
-// Sum over the 16 lanes of an atom in a fixed order; every lane gets the same
+// Sum over the L lanes of an atom in a fixed order; every lane gets the same
 // bits (each step adds two partial sums, which commutes exactly).
-__device__ __forceinline__ float atom_sum(float v) { return group_sum<16>(v); }
+template <int L>
+__device__ __forceinline__ float atom_sum(float v) {
+  v = group_sum<16>(v);
+#pragma unroll
+  for (int d = 16; d < L; d <<= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+template <int L>
 __device__ __forceinline__ double atom_sum(double v) {
 #pragma unroll
-  for (int d = 1; d < 16; d <<= 1) v += __shfl_xor(v, d, 64);
+  for (int d = 1; d < L; d <<= 1) v += __shfl_xor(v, d, 64);
   return v;
 }
 
@@ -213,8 +214,9 @@ __device__ __forceinline__ void radial_basis_n(float r, float rc_inv, int nb, fl
 
 // F64: the float64 descriptor and hidden-layer input of multicomponent
 // systems (wspd = sqrt(Z) in float64 beside wsp).
-template <int TR, int TA, int TL, int TNEU, bool F64>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_partials_generic(
+// AW: atoms per wave, 64 / AW lanes each.
+template <int TR, int TA, int TL, int TNEU, bool F64, int AW>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(F64 && TR == 0 && AW > 1 ? 1 : 2))) void k_partials_generic(
     int n, const double* __restrict__ pos, const uint32_t* __restrict__ nl,
     const int* __restrict__ cnt_r, const int* __restrict__ cnt_a, const int* __restrict__ rev,
     Box box, const float* __restrict__ z, int nr_rt, int na_rt, int lmax_rt, int nneu_rt,
@@ -226,6 +228,15 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
   using D4 = typename std::conditional<F64, f64x4, f32x4>::type;
   constexpr int MR = S::MR, MA = S::MA, RPL = S::RPL, KT = S::KT, QS = S::QS, NT = S::NT,
                 GS = S::GS;
+  constexpr int L = 64 / AW;            // lanes per atom
+  constexpr int kAtoms = kWaves * AW;   // per block
+  // List slots per atom staged at a time: with 16 lanes per atom most lists with
+  // a 0.5 A skin fit at once, longer ones (80 slots in PbTe) take further rounds.
+  constexpr int W = 64 * kWaves / kAtoms;  // slots staged side by side
+  constexpr int T = W >= 48 ? 1 : 48 / W;  // slots per thread
+  constexpr int kSlots = W * T;
+  constexpr int kRow = kSlots + 1;  // LDS row of an atom's pairs (odd: no bank aliasing)
+  static_assert(kSlots <= 64, "slot masks");
   const float rc_r = (float)rc_rd, rc_a = (float)rc_ad;
   const int NR = S::kFixed ? TR : nr_rt;
   const int NA = S::kFixed ? TA : na_rt;
@@ -240,16 +251,17 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
   __shared__ int s_dst[F64 ? kAtoms : 1][F64 ? kRow : 1];
   __shared__ unsigned long long s_mask[2][kAtoms];  // slots of the two pair classes
   __shared__ int s_count[2][kAtoms];                // staged angular pairs, staged pairs
-  // Operands of the per-atom products, one block per wave.  HB pairs of each
-  // of the wave's four atoms at a time (float64: 8, so that two blocks fit a
-  // compute unit).  Descriptor: rows (24 Yhat_lm, g_n); forces: rows (T_n + 1,
-  // T_n'), replaced by the products (24 + 24).
-  constexpr int HB = F64 ? 8 : 16;
+  // Operands of the per-atom products, one buffer per wave.  HB pairs of each
+  // of the wave's atoms at a time (float64: half of them, so that two blocks
+  // fit a compute unit).  Descriptor: rows (24 Yhat_lm, g_n); forces: rows
+  // (T_n + 1, T_n'), replaced by the products (24 + 24).
+  constexpr int HB = F64 ? L / 2 : L;
+  constexpr int TB = HB < 16 ? HB : 16;  // rows of one product over n
   constexpr int YS = F64 ? 24 + MA + (MA % 2 == 0 ? 1 : 0) : 44;  // DT per descriptor row
   constexpr int FS = 52;                                          // float per force row
-  constexpr int kBuf = 4 * HB * YS * (int)sizeof(DT) > 4 * HB * FS * 4
-                           ? 4 * HB * YS * (int)sizeof(DT)
-                           : 4 * HB * FS * 4;
+  constexpr int kBuf = AW * HB * YS * (int)sizeof(DT) > AW * HB * FS * 4
+                           ? AW * HB * YS * (int)sizeof(DT)
+                           : AW * HB * FS * 4;
   static_assert(24 + MA <= YS && 8 * RPL <= FS, "operand rows");
   static_assert(MA * 25 * (int)sizeof(DT) <= kBuf, "moments of one atom");
   __shared__ __align__(16) char s_buf[kWaves][kBuf];
@@ -259,7 +271,9 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int h = lane >> 4, col = lane & 15;
-  const int al = 4 * wave + h;  // the lane's atom within the block
+  const int g_own = lane / L, sub = lane % L;
+  const int al = AW * wave + g_own;  // the lane's atom within the block
+  const int ac = col % kAtoms;       // the atom of column `col` of the network's products
   const int i0 = (int)xcd_block(blockIdx.x, gridDim.x) * kAtoms;
   const float rcr_inv = 1.f / rc_r, rca_inv = 1.f / rc_a;
   const double rcr_inv_d = 1.0 / rc_rd, rca_inv_d = 1.0 / rc_ad;
@@ -270,39 +284,38 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
 
-  // ---- staging: thread (a, w) handles slots w, w + 16, w + 32 of atom a
-  const int sa = tid & 15, sw = tid >> 4;
+  // ---- staging: thread (a, w) handles slots w, w + W, ... of atom a
+  const int sa = tid % kAtoms, sw = tid / kAtoms;
   const int ia = i0 + sa;
   const int cra = ia < n ? cnt_r[ia] : 0, caa = ia < n ? cnt_a[ia] : 0;
   const double xa = ia < n ? pos[ia] : 0.0, ya = ia < n ? pos[n + ia] : 0.0,
                za = ia < n ? pos[2 * n + ia] : 0.0;
   int most = cra;
 #pragma unroll
-  for (int d = 1; d < 16; d <<= 1) most = max(most, __shfl_xor(most, d, 64));
+  for (int d = 1; d < kAtoms; d <<= 1) most = max(most, __shfl_xor(most, d, 64));
   const int chunks = (most + kSlots - 1) / kSlots;  // the same for the whole block
   // slots kSlots c ..; the first time they are seen (write) their pair vectors
   // and the zero partial forces of pairs beyond r_c^R are written
   auto stage = [&](int c, bool write) {
-    constexpr int T = kSlots / 16;
     uint32_t e[T];
     int rv[T];
     double pj[T][3], wj[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      const int sl = c * kSlots + sw + 16 * t;
+      const int sl = c * kSlots + sw + W * t;
       const size_t idx = sl < cra ? (size_t)sl * n + ia : 0;
       e[t] = nl[idx];
       rv[t] = rev[idx];
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      const int j = c * kSlots + sw + 16 * t < cra ? (int)(e[t] & kAtomMask) : 0;
+      const int j = c * kSlots + sw + W * t < cra ? (int)(e[t] & kAtomMask) : 0;
       pj[t][0] = pos[j];
       pj[t][1] = pos[n + j];
       pj[t][2] = pos[2 * n + j];
       if constexpr (F64) wj[t] = wspd[perm[j]];
     }
-    if (tid < 32) s_mask[tid >> 4][tid & 15] = 0ull;
+    if (tid < 2 * kAtoms) s_mask[tid / kAtoms][tid % kAtoms] = 0ull;
     __syncthreads();  // the masks are clear, the previous chunk has been read
     float v[T][3];
     double d[T][3];
@@ -310,7 +323,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
     unsigned long long ma = 0ull, mr = 0ull;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      const int sl = c * kSlots + sw + 16 * t;
+      const int sl = c * kSlots + sw + W * t;
       if constexpr (F64) {
         image_displacement_d(e[t], pj[t], xa, ya, za, box.h, d[t][0], d[t][1], d[t][2]);
 #pragma unroll
@@ -324,9 +337,9 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
       if (write && geo) geo[(size_t)sl * n + ia] = Partial3{v[t][0], v[t][1], v[t][2]};
       const float r2 = pair_r2(v[t][0], v[t][1], v[t][2]);
       if (sl < caa && r2 < rca2)
-        ma |= 1ull << (sw + 16 * t);
+        ma |= 1ull << (sw + W * t);
       else if (r2 < rcr2)
-        mr |= 1ull << (sw + 16 * t);
+        mr |= 1ull << (sw + W * t);
       else if (write)
         pin[(size_t)(unsigned)dst[t]] = Partial3{0.f, 0.f, 0.f};
     }
@@ -341,7 +354,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      const unsigned long long bit = 1ull << (sw + 16 * t);
+      const unsigned long long bit = 1ull << (sw + W * t);
       if (!((fa | fr) & bit)) continue;
       const int k = (fa & bit) ? __popcll(fa & (bit - 1)) : na + __popcll(fr & (bit - 1));
       if constexpr (F64) {
@@ -355,16 +368,16 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
     }
     __syncthreads();
   };
-  // the wave's four atoms: staged angular pairs (uniform) and the largest counts
-  int n_ang[4], max_ang, max_in;
+  // the wave's atoms: staged angular pairs (uniform) and the largest counts
+  int n_ang[AW], max_ang, max_in;
   auto counts = [&] {
     max_ang = 0;
     max_in = 0;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      n_ang[g] = __builtin_amdgcn_readfirstlane(s_count[0][4 * wave + g]);
+    for (int g = 0; g < AW; ++g) {
+      n_ang[g] = __builtin_amdgcn_readfirstlane(s_count[0][AW * wave + g]);
       max_ang = max(max_ang, n_ang[g]);
-      max_in = max(max_in, __builtin_amdgcn_readfirstlane(s_count[1][4 * wave + g]));
+      max_in = max(max_in, __builtin_amdgcn_readfirstlane(s_count[1][AW * wave + g]));
     }
   };
 
@@ -372,11 +385,11 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
 
   // ---- descriptor
   DT qr[MR];
-  D4 c[4][2];  // moments of atom g, tile t: n = RPL h + r, lm = 16 t + col
+  D4 c[AW][2];  // moments of atom g, tile t: n = RPL h + r, lm = 16 t + col
 #pragma unroll
   for (int a = 0; a < MR; ++a) qr[a] = 0;
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < AW; ++g)
 #pragma unroll
     for (int t = 0; t < 2; ++t) c[g][t] = D4{0, 0, 0, 0};
   // row `col` of the moments' first operand holds n = RPL oh + orr
@@ -388,8 +401,8 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
     stage(ch, true);
     counts();
     const int my_ang = s_count[0][al], my_in = s_count[1][al];
-    for (int base = 0; base < max_in; base += 16) {
-      const int k = base + col;
+    for (int base = 0; base < max_in; base += L) {
+      const int k = base + sub;
       const bool rad = k < my_in, ang = k < my_ang;
       DT x = 1, y = 0, zz = 0, w = 1;
       if (rad) {
@@ -443,10 +456,10 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
         }
       }
 #pragma unroll
-      for (int half = 0; half < 16 / HB; ++half) {
+      for (int half = 0; half < L / HB; ++half) {
         if (base + HB * half >= max_ang) break;
-        if (col / HB == half) {
-          DT* row = yg + (h * HB + col % HB) * YS;
+        if (sub / HB == half) {
+          DT* row = yg + (g_own * HB + sub % HB) * YS;
           if constexpr (F64) {
 #pragma unroll
             for (int m = 0; m < 24; ++m) row[m] = yh[m];
@@ -466,7 +479,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
         }
         wave_lds_sync();
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < AW; ++g) {
           const int np = n_ang[g] - base - HB * half;  // uniform; pairs past it are zero
 #pragma unroll
           for (int st = 0; st < HB / 4; ++st) {
@@ -483,18 +496,18 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
   }
   // radial components q_0 = R_0, q_n = (R_n + R_0)/2
   {
-    const DT r0 = atom_sum(qr[0]);
-    if (col == 0) s_q[al][0] = r0;
+    const DT r0 = atom_sum<L>(qr[0]);
+    if (sub == 0) s_q[al][0] = r0;
 #pragma unroll
     for (int a = 1; a < MR; ++a) {
-      const DT v = atom_sum(qr[a]);
-      if (col == 0 && a < NR) s_q[al][a] = (DT)0.5 * (v + r0);
+      const DT v = atom_sum<L>(qr[a]);
+      if (sub == 0 && a < NR) s_q[al][a] = (DT)0.5 * (v + r0);
     }
-    for (int v = NDES + col; v < QS; v += 16) s_q[al][v] = 0;  // padding
+    for (int v = NDES + sub; v < QS; v += L) s_q[al][v] = 0;  // padding
   }
   // angular components q_nl = sum_m c_nlm^2, one atom of the wave at a time
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
+  for (int g = 0; g < AW; ++g) {
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
       const int nn = RPL * h + r;
@@ -511,7 +524,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
         const DT cm = yg[a * 25 + l * l - 1 + m];
         s2 += cm * cm;
       }
-      s_q[4 * wave + g][NR + v] = s2;
+      s_q[AW * wave + g][NR + v] = s2;
     }
     wave_lds_sync();
   }
@@ -541,7 +554,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
 #pragma unroll
     for (int t = 0; t < KT; ++t)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) act = mma((DT)wv[t][e], s_q[col][16 * t + 4 * h + e], act);
+      for (int e = 0; e < 4; ++e) act = mma((DT)wv[t][e], s_q[ac][16 * t + 4 * h + e], act);
     DT up = 0;
     float gm[4];
 #pragma unroll
@@ -562,9 +575,11 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
     }
     up += __shfl_xor(up, 16, 64);
     up += __shfl_xor(up, 32, 64);
-    if (h == 0) s_u[wave][col] = up;
-    *reinterpret_cast<float4*>(&s_g[col][16 * wave + 4 * h]) =
-        make_float4(gm[0], gm[1], gm[2], gm[3]);
+    if (col < kAtoms) {
+      if (h == 0) s_u[wave][col] = up;
+      *reinterpret_cast<float4*>(&s_g[col][16 * wave + 4 * h]) =
+          make_float4(gm[0], gm[1], gm[2], gm[3]);
+    }
   }
   __syncthreads();
   if (tid < kAtoms && i0 + tid < n) {
@@ -589,17 +604,18 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = mma(wv[t][e], s_g[col][16 * t + 4 * h + e], acc);
-    *reinterpret_cast<float4*>(dq0 + col * QS + 16 * d + 4 * h) =
-        make_float4(acc[0], acc[1], acc[2], acc[3]);
+      for (int e = 0; e < 4; ++e) acc = mma(wv[t][e], s_g[ac][16 * t + 4 * h + e], acc);
+    if (col < kAtoms)
+      *reinterpret_cast<float4*>(dq0 + col * QS + 16 * d + 4 * h) =
+          make_float4(acc[0], acc[1], acc[2], acc[3]);
   }
   __syncthreads();
 
   // ---- partial forces
   // a_nlm = 2 dU/dq_nl c_nlm, the second operand of the products over n
-  float an[4][2][RPL];
+  float an[AW][2][RPL];
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < AW; ++g)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int lm = 16 * t + col, l = l_of(lm);
@@ -607,7 +623,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
       for (int r = 0; r < RPL; ++r) {
         const int nn = RPL * h + r;
         const bool in = nn < NA && lm < NLM;
-        const float dq = dq0[(4 * wave + g) * QS + (in ? NR + nn * LMAX + (l - 1) : 0)];
+        const float dq = dq0[(AW * wave + g) * QS + (in ? NR + nn * LMAX + (l - 1) : 0)];
         an[g][t][r] = in ? (float)((DT)2 * (DT)dq * c[g][t][r]) : 0.f;
       }
     }
@@ -623,8 +639,8 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
       counts();
     }
     const int my_ang = s_count[0][al], my_in = s_count[1][al];
-    for (int base = 0; base < max_in; base += 16) {
-      const int k = base + col;
+    for (int base = 0; base < max_in; base += L) {
+      const int k = base + sub;
       const bool rad = k < my_in, ang = k < my_ang;
       float dx = 1.f, dy = 0.f, dz = 0.f, wij = 1.f;
       int dst = 0;
@@ -671,10 +687,10 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
           float T[MA], dT[MA];
           chebyshev_terms<MA>(r, rca_inv, fc, dfc, dxdr, T, dT);
 #pragma unroll
-          for (int half = 0; half < 16 / HB; ++half) {
+          for (int half = 0; half < L / HB; ++half) {
             if (base + HB * half >= max_ang) break;
-            float* const row = tb + (h * HB + col % HB) * FS;
-            if (col / HB == half) {
+            float* const row = tb + (g_own * HB + sub % HB) * FS;
+            if (sub / HB == half) {
               // T_n + 1 and T_n' for n < 4 RPL (n >= N_A meet a_nlm = 0)
               float t1[4 * RPL], t2[4 * RPL];
 #pragma unroll
@@ -692,10 +708,11 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
             }
             wave_lds_sync();
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              if (base + HB * half >= n_ang[g]) continue;  // uniform
-              float* const rows = tb + g * HB * FS;
-              const float* const src = rows + (col % HB) * FS;
+            for (int gt = 0; gt < AW * (HB / TB); ++gt) {
+              const int g = gt / (HB / TB), first = TB * (gt % (HB / TB));
+              if (base + HB * half + first >= n_ang[g]) continue;  // uniform
+              float* const rows = tb + (g * HB + first) * FS;
+              const float* const src = rows + (col % TB) * FS;
               float t1[RPL], t2[RPL];
 #pragma unroll
               for (int q = 0; q < RPL; ++q) {
@@ -716,7 +733,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
               wave_lds_sync();  // every lane has read the atom's rows
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
-                if (4 * h + q >= HB) break;
+                if (4 * h + q >= TB) break;
                 float* const o = rows + (4 * h + q) * FS;
                 o[col] = p1[0][q];
                 o[24 + col] = p2[0][q];
@@ -727,7 +744,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
               }
             }
             wave_lds_sync();
-            if (col / HB == half) {
+            if (sub / HB == half) {
 #pragma unroll
               for (int m = 0; m < 24; m += 4) {
                 const float4 v1 = *reinterpret_cast<const float4*>(row + m);
@@ -778,10 +795,10 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2))
       }
     }
   }
-  fx = atom_sum(fx);
-  fy = atom_sum(fy);
-  fz = atom_sum(fz);
-  if (col == 0 && i0 + al < n) {
+  fx = atom_sum<L>(fx);
+  fy = atom_sum<L>(fy);
+  fz = atom_sum<L>(fz);
+  if (sub == 0 && i0 + al < n) {
     fown[i0 + al] = fx;
     fown[n + i0 + al] = fy;
     fown[2 * n + i0 + al] = fz;
@@ -799,18 +816,33 @@ bool generic_supports(const nep_hyper& h) {
 
 namespace {
 
-template <int TR, int TA, int TL, int TNEU, bool F64>
-void launch_shape(nep_ctx ctx, const double* pos) {
+template <int TR, int TA, int TL, int TNEU, bool F64, int AW>
+void launch_atoms(nep_ctx ctx, const double* pos) {
   const System& s = ctx->sys;
   const nep_hyper& h = ctx->hyper;
-  launch_kernel(ctx, true, true, k_partials_generic<TR, TA, TL, TNEU, F64>,
-                dim3(blocks_for(s.n, kAtoms)), dim3(64 * kWaves), s.n, pos,
+  launch_kernel(ctx, true, true, k_partials_generic<TR, TA, TL, TNEU, F64, AW>,
+                dim3(blocks_for(s.n, kWaves * AW)), dim3(64 * kWaves), s.n, pos,
                 (const uint32_t*)s.nl.ptr, (const int*)s.cnt_r.ptr, (const int*)s.cnt_a.ptr,
                 (const int*)s.rev.ptr, s.box, (const float*)ctx->z.ptr, h.n_max_radial + 1,
                 h.n_max_angular + 1, h.l_max, h.n_neuron, h.rc_radial, h.rc_angular,
                 F64 ? (const double*)ctx->species_wd.ptr : (const double*)nullptr,
                 (const int*)s.perm.ptr, ctx->p.ptr, ctx->fown.ptr, ctx->U.ptr,
                 s.n <= kPairVectorMaxAtoms ? ctx->geo.ptr : (Partial3*)nullptr);
+}
+
+// Atoms per wave: one while two blocks per compute unit hold every atom (256
+// units x 2 blocks x 4 waves): the chip is then not full and the shorter chain
+// of a wave counts (12.9 against 20.5 us for 80-50-1 on 1,000 atoms, 8.9
+// against 13.0 us for 29-30-1, 16.9 against 23.5 us for PbTe), else four (20.9
+// against 26.4 us for 80-50-1 on 2,744 atoms; two per wave lie between).
+constexpr int kOneAtomWaves = 2048;
+
+template <int TR, int TA, int TL, int TNEU, bool F64>
+void launch_shape(nep_ctx ctx, const double* pos) {
+  if (ctx->sys.n <= kOneAtomWaves)
+    launch_atoms<TR, TA, TL, TNEU, F64, 1>(ctx, pos);
+  else
+    launch_atoms<TR, TA, TL, TNEU, F64, 4>(ctx, pos);
 }
 
 bool is_shape(const nep_hyper& h, int nr, int na, int lmax, int nneu) {

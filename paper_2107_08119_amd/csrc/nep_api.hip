@@ -506,7 +506,7 @@ nep_status nep_autotune(nep_ctx ctx, const double* pos_dev, int reps, int* lanes
   hipError_t e = hipEventCreate(&a);
   if (e == hipSuccess) e = hipEventCreate(&b);
   int best = ctx->md_variant;
-  // other model sizes have the one-wave-per-atom kernel only
+  // other model sizes have one kernel only
   const int nv = have_training_variant(ctx->hyper) && !ctx->species_on() ? 3 : 1;
   // shapes timed in interleaved rounds; each keeps its fastest round
   constexpr int kRounds = 3;

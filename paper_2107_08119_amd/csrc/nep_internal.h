@@ -235,7 +235,8 @@ struct nep_ctx_s {
   nep::DevBuf<float> W;           // [9][n] internal per-atom virials
   nep::DevBuf<float> J;           // [3][n] internal heat currents
   nep::DevBuf<double> partials;   // [blocks][16] block sums
-  int md_variant = 1;             // pass-1 tile shape: 0, 1, 2, 3 = 2, 4, 8, 64 lanes per atom
+  int md_variant = -1;            // pass-1 tile shape: 0, 1, 2, 3 = 2, 4, 8, 64 lanes per atom,
+                                  // -1 = by the system's size
   // multicomponent system (caller order): sqrt(Z) per atom and optional masses
   int species_n = 0;              // atoms the arrays describe; 0 = one species
   bool have_masses = false;
@@ -385,13 +386,13 @@ bool have_force_variant(const nep_hyper& h);
 // The dataset (training, differentiation) kernels exist for the default sizes only.
 bool have_training_variant(const nep_hyper& h);
 // generic.hip: pass 1 for any size with n_max <= 15, l_max <= 4, <= 64 neurons
-// (one wave per atom).
+// (16 lanes per atom, in small systems 64).
 bool generic_supports(const nep_hyper& h);
 hipError_t launch_partials_generic(nep_ctx ctx, const double* pos);
 // pass 1: descriptor, network, partial forces; pass 2: scatter-free gather.
 // Pass 1 on the internal system with tile shape `variant` (0, 1, 2 = 2, 4, 8
-// lanes per atom, 3 = one wave per atom; -1 = the context's choice).  Models
-// other than the default sizes always use the one-wave-per-atom kernel.
+// lanes per atom, 3 = the kernel of every model size; -1 = the context's
+// choice).  Models other than the default sizes always use the latter.
 hipError_t launch_partials(nep_ctx ctx, const double* pos, int variant = -1);
 // mode 0: plain evaluation (totals = E, W(9), J(3)); mode 1: velocity-Verlet
 // second half-kick fused (vel updated, thermo row written).

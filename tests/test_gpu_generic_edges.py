@@ -1,6 +1,6 @@
-"""The 16-atoms-per-block force kernel where its tiles have remainders: atom
-counts around a block, list lengths around its 48 (float64 descriptor: 32)
-staged slots, angular pair counts around its 4, 8 and 16 pairs per product,
+"""The force kernel of every model size where its tiles have remainders: atom
+counts around a block (4 and 16 atoms), list lengths around its staged slots
+(48 and 64), angular pair counts around its 4, 8 and 16 pairs per product,
 runtime-sized models down to one radial function and one neuron; one and two
 species.  Against the float64 oracle at 1e-5 relative (norm over all
 components), the bound of the other force tests."""
@@ -59,3 +59,43 @@ def test_tiles_match_oracle(model, n, species):
         assert rel(nep.aos(out["F"]), ref["F"]) < TOL
     assert rel(nep.aos(out["W"]).reshape(-1, 3, 3), ref["W"]) < TOL
     assert rel(nep.aos(out["J"]), ref["J"]) < TOL
+
+
+@pytest.mark.parametrize("model,n", [("si_80_50_1", 2048), ("si_80_50_1", 2049), ("si_80_50_1", 2063),
+                                     ("pbte_41_40_1", 2064), ("wide", 2065), ("odd", 2063),
+                                     ("si_29_30_1", 2049), ("si_29_30_1", 4096), ("si_29_30_1", 4097),
+                                     ("si_29_30_1", 8192), ("si_29_30_1", 8193)])
+def test_shapes_chosen_by_size_match_oracle(model, n):
+    """Around the sizes where the kernel's shape changes: the first, last and
+    some other atoms of a jittered lattice with vacancies."""
+    from paper_2107_08119_amd import nep
+    rng = np.random.default_rng(n)
+    cells = int(np.ceil((n / 8) ** (1.0 / 3.0)))
+    if model == "pbte_41_40_1":
+        pos, box, Z, _ = I.rocksalt_supercell(cells, cells, cells)
+    else:
+        pos, box = I.diamond_supercell(cells, cells, cells)
+        Z = None
+    keep = np.sort(rng.permutation(len(pos))[:n])
+    pos = pos[keep] + 0.08 * rng.standard_normal((n, 3))
+    Z = None if Z is None else Z[keep]
+    vel = 0.01 * rng.standard_normal((n, 3))
+    sizes = MODELS.get(model, (5.0, 4.0, 8, 4, 4, 30))
+    h, oh = nep.hyper(*sizes), O.hyper(*sizes)
+    z = I.random_parameters(nep.num_params(h), 7, std=0.03)
+    if Z is not None:
+        z[:h.n_neuron * nep.num_descriptors(h)] *= np.float32(1.0 / 300.0)
+    ctx = nep.Context(0)
+    ctx.load_params(h, z)
+    p = nep.soa(pos)
+    ctx.build_neighbors(p, box, skin=0.5, max_neighbors=256)
+    if Z is not None:
+        ctx.set_species(Z)
+    out = ctx.compute(p, nep.soa(vel))
+    ctx.synchronize()
+    sel = np.unique(np.concatenate([[0, 1, n - 2, n - 1], rng.integers(0, n, 60)])).astype(np.int32)
+    ref = O.nep_eval(oh, z, pos, box, vel=vel, sel=sel, Z=Z)
+    assert rel(out["U"].cpu().numpy()[sel], ref["U"]) < TOL
+    assert rel(nep.aos(out["F"])[sel], ref["F"]) < TOL
+    assert rel(nep.aos(out["W"]).reshape(-1, 3, 3)[sel], ref["W"]) < TOL
+    assert rel(nep.aos(out["J"])[sel], ref["J"]) < TOL
