@@ -757,20 +757,12 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(F64
           }
         }
         if (ang) {
-          const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
-          const float xyz = xy * z;
-          (void)xyz;
-          // per lm: A = f_c At/2 multiplies the harmonic's gradient and
-          // B = f_c' At/2 + f_c (dx/dr) D/2 the harmonic
-          float st = 0.f, sd = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-#define NEP_PF(idx, YV, GX, GY, GZ) \
-  st += At[idx] * (YV);             \
-  sd += D[idx] * (YV);              \
-  gx += At[idx] * (GX);             \
-  gy += At[idx] * (GY);             \
-  gz += At[idx] * (GZ);
-          NEP_YLM_TABLE(NEP_PF)
-#undef NEP_PF
+          // A = f_c At/2 multiplies the harmonics' gradients and
+          // B = f_c' At/2 + f_c (dx/dr) D/2 the harmonics
+          float st, sd, gx, gy, gz;
+          harmonic_sums(
+              x, y, z, [&](int m) { return At[m]; }, [&](int m) { return D[m]; }, st, sd, gx, gy,
+              gz);
           const float hf = 0.5f * fc;
           const float sb = 0.5f * (dfc * st + fc * dxdr * sd);
           gx *= hf;

@@ -142,6 +142,38 @@ __device__ __forceinline__ void chebyshev_terms(float r, float rc_inv, float& fc
   }
 }
 
+// f_c(r) and f_c'(r).
+__device__ __forceinline__ void cutoff_terms(float r, float rc_inv, float& fc, float& dfc) {
+  float sy, cy;
+  sincos_quarter_turn(kPi * (r * rc_inv - 0.5f), sy, cy);
+  fc = 0.5f * (1.f - sy);
+  dfc = -0.5f * kPi * rc_inv * cy;
+}
+
+// s1 = sum_{n<NB} a_n T_n(x) and s2 = sum_{n<NB} a_n T_n'(x) by Clenshaw's
+// recurrence b_n = a_n + 2x b_{n+1} - b_{n+2} and its derivative (halved),
+// d_n = b_{n+1} + 2x d_{n+1} - d_{n+2}: s1 = a_0 + x b_1 - b_2 and
+// s2 = b_1 + 2 (x d_1 - d_2); four operations per term in place of five.
+template <int NB>
+__device__ __forceinline__ void chebyshev_sums(float r, float rc_inv, const float* a, float& dxdr,
+                                               float& s1, float& s2) {
+  const float tm1 = r * rc_inv - 1.f;
+  const float x2 = 4.f * tm1 * tm1 - 2.f;  // 2x
+  dxdr = 4.f * tm1 * rc_inv;
+  float b1 = 0.f, b2 = 0.f, d1 = 0.f, d2 = 0.f;
+#pragma unroll
+  for (int n = NB - 1; n >= 1; --n) {
+    const float dn = (b1 - d2) + x2 * d1;
+    const float bn = (a[n] - b2) + x2 * b1;
+    d2 = d1;
+    d1 = dn;
+    b2 = b1;
+    b1 = bn;
+  }
+  s1 = a[0] + 0.5f * x2 * b1 - b2;
+  s2 = b1 + x2 * d1 - 2.f * d2;
+}
+
 // ------------------------------------------------------- angular harmonics
 // Real harmonics for l = 1..4 scaled by sqrt(4 pi/(2l+1)) so that
 // sum_m Y_lm(u) Y_lm(v) = P_l(u.v) for unit u, v, written as polynomials in

@@ -12,10 +12,15 @@
 //   dU_i/dr_ij = sum_n dU/dq_n g_n'(r) u
 //              + sum_lm [ B_lm Yhat_lm(u) u + A_lm (grad Yhat_lm - u (u.grad Yhat_lm)) / r ],
 // with a_nlm = 2 dU/dq_nl c_nlm, A_lm = sum_n a_nlm g_n(r), B_lm = sum_n a_nlm g_n'(r).
-// Since g_n = f_c (T_n + 1)/2, both come from At_lm = a'_0lm + sum_{n>=1} a_nlm T_n
-// (a'_0lm = 2 a_0lm + sum_{n>=1} a_nlm, folded once per atom) and
+// Since g_n = f_c (T_n + 1)/2, both come from At_lm = sum_n a_nlm (T_n + 1) and
 // D_lm = sum_{n>=1} a_nlm T_n':  A_lm = f_c At_lm / 2,
 // B_lm = f_c' At_lm / 2 + f_c (dx/dr) D_lm / 2.
+//
+// The sums over lm use the form Yhat_lm = Q_lm(z) Re or Im (x + i y)^m, with
+// Q_lm a polynomial in z: per m the coefficients are combined over l first,
+// then with the powers of x + i y, whose x and y derivatives are m times the
+// power below (harmonic_sums).  For one pair this takes about 130 operations
+// instead of about 190 with every harmonic and gradient component written out.
 #pragma once
 
 #include "nep_device.h"
@@ -27,6 +32,128 @@ struct Model {
   static constexpr int kNLM = (LMAX + 1) * (LMAX + 1) - 1;  // harmonics l = 1..LMAX
   static constexpr int kNDES = NR + NA * LMAX;
 };
+
+// Re and Im (x + i y)^m, m = 1..4.
+struct PlanePowers {
+  float a1, b1, a2, b2, a3, b3, a4, b4;
+};
+__device__ __forceinline__ PlanePowers plane_powers(float x, float y) {
+  PlanePowers p;
+  p.a1 = x;
+  p.b1 = y;
+  p.a2 = x * x - y * y;
+  p.b2 = 2.f * x * y;
+  p.a3 = x * p.a2 - y * p.b2;
+  p.b3 = x * p.b2 + y * p.a2;
+  p.a4 = p.a2 * p.a2 - p.b2 * p.b2;
+  p.b4 = 2.f * p.a2 * p.b2;
+  return p;
+}
+
+// Q_lm(z) of l = 1..4, indexed qLM.
+struct ZFactors {
+  float q10, q20, q30, q40, q21, q31, q41, q32, q42, q43;
+  static constexpr float q22 = 0.5f * NEP_S3, q33 = 0.25f * NEP_S10, q44 = 0.125f * NEP_S35;
+};
+__device__ __forceinline__ ZFactors z_factors(float z, float zz) {
+  ZFactors q;
+  q.q10 = z;
+  q.q20 = 1.5f * zz - 0.5f;
+  q.q30 = z * (2.5f * zz - 1.5f);
+  q.q40 = (4.375f * zz - 3.75f) * zz + 0.375f;
+  q.q21 = NEP_S3 * z;
+  q.q31 = 1.25f * NEP_S6 * zz - 0.25f * NEP_S6;
+  q.q41 = z * (1.75f * NEP_S10 * zz - 0.75f * NEP_S10);
+  q.q32 = 0.5f * NEP_S15 * z;
+  q.q42 = 1.75f * NEP_S5 * zz - 0.25f * NEP_S5;
+  q.q43 = 0.25f * NEP_S70 * z;
+  return q;
+}
+
+// The 24 harmonics Yhat_lm (l = 1..4) of the unit vector (x, y, z).
+__device__ __forceinline__ void harmonics(float x, float y, float z, float (&out)[24]) {
+  const PlanePowers p = plane_powers(x, y);
+  const ZFactors q = z_factors(z, z * z);
+  out[0] = x, out[1] = y, out[2] = z;
+  out[5] = q.q20, out[11] = q.q30, out[19] = q.q40;
+  out[6] = q.q21 * p.a1, out[4] = q.q21 * p.b1;
+  out[12] = q.q31 * p.a1, out[10] = q.q31 * p.b1;
+  out[20] = q.q41 * p.a1, out[18] = q.q41 * p.b1;
+  out[7] = q.q22 * p.a2, out[3] = q.q22 * p.b2;
+  out[13] = q.q32 * p.a2, out[9] = q.q32 * p.b2;
+  out[21] = q.q42 * p.a2, out[17] = q.q42 * p.b2;
+  out[14] = q.q33 * p.a3, out[8] = q.q33 * p.b3;
+  out[22] = q.q43 * p.a3, out[16] = q.q43 * p.b3;
+  out[23] = q.q44 * p.a4, out[15] = q.q44 * p.b4;
+}
+
+// For coefficients At_lm = at(lm) and D_lm = d(lm) at the unit vector
+// (x, y, z): sa = sum At Yhat, sd = sum D Yhat and g = sum At grad Yhat.
+template <class FA, class FD>
+__device__ __forceinline__ void harmonic_sums(float x, float y, float z, FA&& at, FD&& d,
+                                              float& sa, float& sd, float& gx, float& gy,
+                                              float& gz) {
+  const float zz = z * z;
+  const PlanePowers p = plane_powers(x, y);
+  const ZFactors q = z_factors(z, zz);
+  // derivatives of the Q_lm that are not constants of NEP_S3, NEP_S15, NEP_S70
+  const float e20 = 3.f * z, e30 = 7.5f * zz - 1.5f, e40 = z * (17.5f * zz - 7.5f);
+  const float e31 = 2.5f * NEP_S6 * z, e41 = 5.25f * NEP_S10 * zz - 0.75f * NEP_S10;
+  const float e42 = 3.5f * NEP_S5 * z;
+  {  // m = 0
+    const float c1 = at(2), c2 = at(5), c3 = at(11), c4 = at(19);
+    sa = c1 * q.q10 + c2 * q.q20 + c3 * q.q30 + c4 * q.q40;
+    gz = c1 + c2 * e20 + c3 * e30 + c4 * e40;
+    sd = d(2) * q.q10 + d(5) * q.q20 + d(11) * q.q30 + d(19) * q.q40;
+  }
+  // m >= 1: u multiplies Re, v Im (x + i y)^m; du, dv their z derivatives
+  {
+    const float c2 = at(6), c3 = at(12), c4 = at(20), s2 = at(4), s3 = at(10), s4 = at(18);
+    const float u = at(0) + c2 * q.q21 + c3 * q.q31 + c4 * q.q41;
+    const float v = at(1) + s2 * q.q21 + s3 * q.q31 + s4 * q.q41;
+    const float du = c2 * NEP_S3 + c3 * e31 + c4 * e41;
+    const float dv = s2 * NEP_S3 + s3 * e31 + s4 * e41;
+    sa += u * p.a1 + v * p.b1;
+    gz += du * p.a1 + dv * p.b1;
+    gx = u;
+    gy = v;
+    sd += (d(0) + d(6) * q.q21 + d(12) * q.q31 + d(20) * q.q41) * p.a1 +
+          (d(1) + d(4) * q.q21 + d(10) * q.q31 + d(18) * q.q41) * p.b1;
+  }
+  {
+    const float c3 = at(13), c4 = at(21), s3 = at(9), s4 = at(17);
+    const float u = at(7) * q.q22 + c3 * q.q32 + c4 * q.q42;
+    const float v = at(3) * q.q22 + s3 * q.q32 + s4 * q.q42;
+    const float du = c3 * (0.5f * NEP_S15) + c4 * e42;
+    const float dv = s3 * (0.5f * NEP_S15) + s4 * e42;
+    sa += u * p.a2 + v * p.b2;
+    gz += du * p.a2 + dv * p.b2;
+    const float x2 = 2.f * x, y2 = 2.f * y;
+    gx += u * x2 + v * y2;
+    gy += v * x2 - u * y2;
+    sd += (d(7) * q.q22 + d(13) * q.q32 + d(21) * q.q42) * p.a2 +
+          (d(3) * q.q22 + d(9) * q.q32 + d(17) * q.q42) * p.b2;
+  }
+  {
+    const float c4 = at(22), s4 = at(16);
+    const float u = at(14) * q.q33 + c4 * q.q43;
+    const float v = at(8) * q.q33 + s4 * q.q43;
+    sa += u * p.a3 + v * p.b3;
+    gz += c4 * (0.25f * NEP_S70) * p.a3 + s4 * (0.25f * NEP_S70) * p.b3;
+    const float a = 3.f * p.a2, b = 3.f * p.b2;
+    gx += u * a + v * b;
+    gy += v * a - u * b;
+    sd += (d(14) * q.q33 + d(22) * q.q43) * p.a3 + (d(8) * q.q33 + d(16) * q.q43) * p.b3;
+  }
+  {
+    const float u = at(23) * q.q44, v = at(15) * q.q44;
+    sa += u * p.a4 + v * p.b4;
+    const float a = 4.f * p.a3, b = 4.f * p.b3;
+    gx += u * a + v * b;
+    gy += v * a - u * b;
+    sd += d(23) * q.q44 * p.a4 + d(15) * q.q44 * p.b4;
+  }
+}
 
 // Add pair (dx, dy, dz) to the radial sums (when rad) and to the angular
 // moments c[NA][NLM] (when ang).  The radial sums are kept as
@@ -50,17 +177,12 @@ __device__ __forceinline__ void pair_descriptor(float dx, float dy, float dz, bo
   if (ang) {
     float g[NA];
     radial_basis<NA, false>(r, rca_inv, g, nullptr);
-    const float x = dx * rinv, y = dy * rinv, z = dz * rinv;
-    const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
-    const float xyz = xy * z;
-    (void)xyz;
-#define NEP_ACC(idx, YV, GX, GY, GZ)                                        \
-  if constexpr ((idx) < NLM) {                                              \
-    const float yv = (YV);                                                  \
-    _Pragma("unroll") for (int a = 0; a < NA; ++a) c[a][idx] += g[a] * yv; \
-  }
-    NEP_YLM_TABLE(NEP_ACC)
-#undef NEP_ACC
+    float yh[24];
+    harmonics(dx * rinv, dy * rinv, dz * rinv, yh);
+#pragma unroll
+    for (int m = 0; m < NLM; ++m)
+#pragma unroll
+      for (int a = 0; a < NA; ++a) c[a][m] += g[a] * yh[m];
   }
 }
 
@@ -90,17 +212,12 @@ __device__ __forceinline__ void pair_descriptor_first(float dx, float dy, float 
   radial_basis<NA, false>(r, rca_inv, g, nullptr);
 #pragma unroll
   for (int a = 0; a < NA; ++a) g[a] = ang ? g[a] : 0.f;
-  const float x = dx * rinv, y = dy * rinv, z = dz * rinv;
-  const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
-  const float xyz = xy * z;
-  (void)xyz;
-#define NEP_SET(idx, YV, GX, GY, GZ)                                       \
-  if constexpr ((idx) < NLM) {                                             \
-    const float yv = (YV);                                                 \
-    _Pragma("unroll") for (int a = 0; a < NA; ++a) c[a][idx] = g[a] * yv; \
-  }
-  NEP_YLM_TABLE(NEP_SET)
-#undef NEP_SET
+  float yh[24];
+  harmonics(dx * rinv, dy * rinv, dz * rinv, yh);
+#pragma unroll
+  for (int m = 0; m < NLM; ++m)
+#pragma unroll
+    for (int a = 0; a < NA; ++a) c[a][m] = g[a] * yh[m];
 }
 
 // q_n = (R_n + R_0) / 2 from the complete sums R_n of pair_descriptor.
@@ -118,16 +235,6 @@ __device__ __forceinline__ float radial_dq_sum(const float* dq) {
 #pragma unroll
   for (int a = 0; a < NR; ++a) s += dq[a];
   return s;
-}
-
-// The 24 harmonics Yhat_lm (l = 1..4) of the unit vector (x, y, z).
-__device__ __forceinline__ void harmonics(float x, float y, float z, float (&out)[24]) {
-  const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
-  const float xyz = xy * z;
-  (void)xyz;
-#define NEP_Y(idx, YV, GX, GY, GZ) out[idx] = (YV);
-  NEP_YLM_TABLE(NEP_Y)
-#undef NEP_Y
 }
 
 // Angular components q[NR + n LMAX + l - 1] = sum_m c_nlm^2.
@@ -293,41 +400,32 @@ __device__ __forceinline__ void network_mfma(const float* q, const float4* rows,
   u = x[aw * kNetX + 32];
 }
 
-// a_nlm = 2 dU/dq_nl c_nlm in place of c, then row 0 replaced by
-// a'_0lm = 2 a_0lm + sum_{n>=1} a_nlm (the constant part of sum_n a_nlm (T_n + 1)).
+// a_nlm = 2 dU/dq_nl c_nlm in place of c, row 0 doubled (T_0 + 1 = 2).
 template <int NR, int NA, int LMAX>
 __device__ __forceinline__ void angular_coefficients(const float* dq,
                                                      float (&c)[NA][Model<NR, NA, LMAX>::kNLM]) {
-  constexpr int NLM = Model<NR, NA, LMAX>::kNLM;
 #pragma unroll
   for (int a = 0; a < NA; ++a)
 #pragma unroll
     for (int l = 1; l <= LMAX; ++l) {
-      const float f = 2.f * dq[NR + a * LMAX + (l - 1)];
+      const float f = (a == 0 ? 4.f : 2.f) * dq[NR + a * LMAX + (l - 1)];
 #pragma unroll
       for (int m = 0; m < 2 * l + 1; ++m) c[a][l * l - 1 + m] *= f;
     }
-#pragma unroll
-  for (int m = 0; m < NLM; ++m) {
-    float s = 2.f * c[0][m];
-#pragma unroll
-    for (int a = 1; a < NA; ++a) s += c[a][m];
-    c[0][m] = s;
-  }
 }
 
 // Partial force dU_i/dr_ij of pair (dx, dy, dz) from dq (radial part, when
 // rad; dq_sum = radial_dq_sum(dq)) and the angular coefficients a as left by
 // angular_coefficients (when ang).  Radial part: sum_n dU/dq_n g_n' =
 // f_c' (S_1 + dq_sum) / 2 + f_c (dx/dr) S_2 / 2 with S_1 = sum_n dU/dq_n T_n
-// and S_2 = sum_n dU/dq_n T_n'.
+// and S_2 = sum_n dU/dq_n T_n', both by Clenshaw's recurrence.
 template <int NR, int NA, int LMAX>
 __device__ __forceinline__ void pair_force(float dx, float dy, float dz, bool rad, bool ang,
                                            float rcr_inv, float rca_inv, const float* dq,
                                            float dq_sum,
                                            const float (&c)[NA][Model<NR, NA, LMAX>::kNLM],
                                            float& px, float& py, float& pz) {
-  constexpr int NLM = Model<NR, NA, LMAX>::kNLM;
+  static_assert(LMAX == 4, "harmonic_sums");
   const float r2 = pair_r2(dx, dy, dz);
   const float rinv = __builtin_amdgcn_rsqf(r2);
   const float r = r2 * rinv;
@@ -336,14 +434,9 @@ __device__ __forceinline__ void pair_force(float dx, float dy, float dz, bool ra
   py = 0.f;
   pz = 0.f;
   if (rad) {
-    float fc, dfc, dxdr, T[NR], dT[NR];
-    chebyshev_terms<NR>(r, rcr_inv, fc, dfc, dxdr, T, dT);
-    float s1 = dq[0], s2 = 0.f;
-#pragma unroll
-    for (int a = 1; a < NR; ++a) {
-      s1 += dq[a] * T[a];
-      s2 += dq[a] * dT[a];
-    }
+    float fc, dfc, dxdr, s1, s2;
+    cutoff_terms(r, rcr_inv, fc, dfc);
+    chebyshev_sums<NR>(r, rcr_inv, dq, dxdr, s1, s2);
     const float f = 0.5f * (dfc * (s1 + dq_sum) + fc * dxdr * s2);
     px += f * x;
     py += f * y;
@@ -352,25 +445,25 @@ __device__ __forceinline__ void pair_force(float dx, float dy, float dz, bool ra
   if (ang) {
     float fc, dfc, dxdr, T[NA], dT[NA];
     chebyshev_terms<NA>(r, rca_inv, fc, dfc, dxdr, T, dT);
-    const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
-    const float xyz = xy * z;
-    (void)xyz;
-    float sa = 0.f, sd = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-#define NEP_PF(idx, YV, GX, GY, GZ)                   \
-  if constexpr ((idx) < NLM) {                        \
-    float At = c[0][idx], D = 0.f;                    \
-    _Pragma("unroll") for (int a = 1; a < NA; ++a) {  \
-      At += c[a][idx] * T[a];                         \
-      D += c[a][idx] * dT[a];                         \
-    }                                                 \
-    sa += At * (YV);                                  \
-    sd += D * (YV);                                   \
-    gx += At * (GX);                                  \
-    gy += At * (GY);                                  \
-    gz += At * (GZ);                                  \
-  }
-    NEP_YLM_TABLE(NEP_PF)
-#undef NEP_PF
+    float t1[NA];
+#pragma unroll
+    for (int a = 1; a < NA; ++a) t1[a] = T[a] + 1.f;
+    float sa, sd, gx, gy, gz;
+    harmonic_sums(
+        x, y, z,
+        [&](int m) {
+          float v = c[0][m];
+#pragma unroll
+          for (int a = 1; a < NA; ++a) v += c[a][m] * t1[a];
+          return v;
+        },
+        [&](int m) {
+          float v = NA > 1 ? c[NA > 1 ? 1 : 0][m] : 0.f;  // T_1' = 1
+#pragma unroll
+          for (int a = 2; a < NA; ++a) v += c[a][m] * dT[a];
+          return v;
+        },
+        sa, sd, gx, gy, gz);
     const float sb = 0.5f * (dfc * sa + fc * dxdr * sd);
     const float hf = 0.5f * fc;
     gx *= hf;
