@@ -31,11 +31,35 @@ __global__ void k_zero(int* __restrict__ a, int m) {
   if (t < m) a[t] = 0;
 }
 
-// Integer cell offsets w = floor(s) of every atom (optionally wrapping the
-// positions into the cell first) and, on the cell path, the cell index.
-// With src (a new system) the positions, and the velocities when vel_src is
-// given, are first taken over from the caller's arrays, in the caller's order
-// (perm, iperm the identity); otherwise pos holds them.
+// Integer cell offsets w = floor(s) of one atom at r, wrapping r into the cell
+// first when wrap_in_place, and its cell index.  Returns whether r changed.
+__device__ __forceinline__ bool bin_atom(double (&r)[3], const Box& box, int nc0, int nc1, int nc2,
+                                         int wrap_in_place, int (&w)[3], int& cell) {
+  double s[3];
+  bool moved = false;
+  fractional(box, r, s);
+  for (int a = 0; a < 3; ++a) w[a] = (int)floor(s[a]);
+  if (wrap_in_place && (w[0] | w[1] | w[2])) {
+    for (int c = 0; c < 3; ++c)
+      r[c] -= ((double)w[0] * box.h[c] + (double)w[1] * box.h[3 + c]) + (double)w[2] * box.h[6 + c];
+    moved = true;
+    fractional(box, r, s);
+    for (int a = 0; a < 3; ++a) w[a] = (int)floor(s[a]);
+  }
+  const int nc[3] = {nc0, nc1, nc2};
+  int c[3];
+  for (int a = 0; a < 3; ++a) {
+    int ca = (int)((s[a] - (double)w[a]) * (double)nc[a]);
+    c[a] = ca < 0 ? 0 : (ca >= nc[a] ? nc[a] - 1 : ca);
+  }
+  cell = (c[2] * nc1 + c[1]) * nc0 + c[0];
+  return moved;
+}
+
+// bin_atom for every atom.  With src (a new system) the positions, and the
+// velocities when vel_src is given, are first taken over from the caller's
+// arrays, in the caller's order (perm, iperm the identity); otherwise pos
+// holds them.
 __global__ void k_bin(int n, const double* __restrict__ src, const double* __restrict__ vel_src,
                       double* __restrict__ pos, double* __restrict__ vel, int* __restrict__ perm,
                       int* __restrict__ iperm, Box box, int nc0, int nc1, int nc2, int use_cells,
@@ -49,35 +73,19 @@ __global__ void k_bin(int n, const double* __restrict__ src, const double* __res
     iperm[i] = i;
     for (int c = 0; c < 3; ++c) {
       r[c] = src[(size_t)c * n + i];
-      pos[(size_t)c * n + i] = r[c];
       if (vel_src) vel[(size_t)c * n + i] = vel_src[(size_t)c * n + i];
     }
   } else {
     for (int c = 0; c < 3; ++c) r[c] = pos[(size_t)c * n + i];
   }
-  double s[3];
-  int w[3];
-  fractional(box, r, s);
-  for (int a = 0; a < 3; ++a) w[a] = (int)floor(s[a]);
-  if (wrap_in_place && (w[0] | w[1] | w[2])) {
-    for (int c = 0; c < 3; ++c) {
-      r[c] -= ((double)w[0] * box.h[c] + (double)w[1] * box.h[3 + c]) + (double)w[2] * box.h[6 + c];
-      pos[c * n + i] = r[c];
-    }
-    fractional(box, r, s);
-    for (int a = 0; a < 3; ++a) w[a] = (int)floor(s[a]);
-  }
+  int w[3], cell;
+  const bool moved = bin_atom(r, box, nc0, nc1, nc2, wrap_in_place, w, cell);
+  if (src || moved)
+    for (int c = 0; c < 3; ++c) pos[(size_t)c * n + i] = r[c];
   for (int a = 0; a < 3; ++a) wrap[a * n + i] = w[a];
   if (pos_ref)  // the positions this list is built for (no re-sort on this path)
     for (int c = 0; c < 3; ++c) pos_ref[c * n + i] = (float)r[c];
   if (use_cells) {
-    const int nc[3] = {nc0, nc1, nc2};
-    int c[3];
-    for (int a = 0; a < 3; ++a) {
-      int ca = (int)((s[a] - (double)w[a]) * (double)nc[a]);
-      c[a] = ca < 0 ? 0 : (ca >= nc[a] ? nc[a] - 1 : ca);
-    }
-    int cell = (c[2] * nc1 + c[1]) * nc0 + c[0];
     cell_of[i] = cell;
     atomicAdd(&cell_cnt[cell], 1);
   }
@@ -196,57 +204,152 @@ __global__ void k_fill(int n, const int* __restrict__ cell_of, const int* __rest
   members[start[c] + slot] = i;
 }
 
-// Order every cell's members by atom index: each atom counts the members of
-// its cell with a smaller index and takes that place (cells are small).
+// The internal arrays an atom moves to when the atoms are re-sorted into cell
+// order.
+struct Sorted {
+  double *pos, *vel;  // vel NULL: no velocities
+  int *wrap, *perm, *iperm, *cell_of;
+  CellRec* rec;
+  float* pos_ref;
+  int* flags;
+};
+
+// Atom at r (velocity v when given, offsets w, caller index, cell) to internal
+// index k, with its 32-byte record (position, index, packed offsets).
+__device__ __forceinline__ void place_atom(int n, int k, const double (&r)[3], const double (&v)[3],
+                                           int w0, int w1, int w2, int caller, int cell,
+                                           const Sorted& o) {
+  CellRec rec;
+  rec.x = r[0];
+  rec.y = r[1];
+  rec.z = r[2];
+  o.pos[k] = r[0];
+  o.pos[n + k] = r[1];
+  o.pos[2 * n + k] = r[2];
+  o.pos_ref[k] = (float)r[0];
+  o.pos_ref[n + k] = (float)r[1];
+  o.pos_ref[2 * n + k] = (float)r[2];
+  if (o.vel) {
+    o.vel[k] = v[0];
+    o.vel[n + k] = v[1];
+    o.vel[2 * n + k] = v[2];
+  }
+  o.wrap[k] = w0;
+  o.wrap[n + k] = w1;
+  o.wrap[2 * n + k] = w2;
+  o.perm[k] = caller;
+  o.iperm[caller] = k;  // caller index -> new internal index
+  o.cell_of[k] = cell;
+  if (w0 < -127 || w0 > 127 || w1 < -127 || w1 > 127 || w2 < -127 || w2 > 127)
+    o.flags[kFlagImage] = 1;
+  rec.j = k;
+  rec.w = (w0 & 0xFF) | ((w1 & 0xFF) << 8) | ((w2 & 0xFF) << 16);
+  o.rec[k] = rec;
+}
+
 // Re-sort atoms into cell order (cells in order, each cell's members by old
-// index): old atom o finds its rank among its cell's members and moves to
-// internal index k = start[cell] + rank.  Position, velocity (when given),
-// offsets, caller index and cell move with it, and a 32-byte record
-// (position, index, packed offsets) is written per atom.
+// index, so the order does not depend on the atomics): old atom o counts the
+// members of its cell with a smaller index and moves to internal index
+// k = start[cell] + that rank (cells are small).
 __global__ void k_rank_permute(int n, const int* __restrict__ start,
                                const int* __restrict__ members, const double* __restrict__ pos,
-                               double* __restrict__ pos_out, const double* __restrict__ vel,
-                               double* __restrict__ vel_out, const int* __restrict__ wrap,
-                               int* __restrict__ wrap_out, const int* __restrict__ perm,
-                               int* __restrict__ perm_out, const int* __restrict__ cell_of,
-                               int* __restrict__ cell_out, CellRec* __restrict__ rec,
-                               int* __restrict__ iperm_out, float* __restrict__ pos_ref,
-                               int* __restrict__ flags) {
+                               const double* __restrict__ vel, const int* __restrict__ wrap,
+                               const int* __restrict__ perm, const int* __restrict__ cell_of,
+                               Sorted out) {
   const int o = blockIdx.x * blockDim.x + threadIdx.x;
   if (o >= n) return;
   const int c = cell_of[o];
   const int b = start[c], e = start[c + 1];
   int rank = 0;
   for (int m = b; m < e; ++m) rank += members[m] < o ? 1 : 0;
-  const int k = b + rank;
-  CellRec r;
-  r.x = pos[o];
-  r.y = pos[n + o];
-  r.z = pos[2 * n + o];
-  pos_out[k] = r.x;
-  pos_out[n + k] = r.y;
-  pos_out[2 * n + k] = r.z;
-  pos_ref[k] = (float)r.x;
-  pos_ref[n + k] = (float)r.y;
-  pos_ref[2 * n + k] = (float)r.z;
-  if (vel) {
-    vel_out[k] = vel[o];
-    vel_out[n + k] = vel[n + o];
-    vel_out[2 * n + k] = vel[2 * n + o];
+  const double r[3] = {pos[o], pos[n + o], pos[2 * n + o]};
+  double v[3] = {0.0, 0.0, 0.0};
+  if (out.vel)
+    for (int a = 0; a < 3; ++a) v[a] = vel[(size_t)a * n + o];
+  place_atom(n, b + rank, r, v, wrap[o], wrap[n + o], wrap[2 * n + o], perm[o], c, out);
+}
+
+// k_bin, the cell scan, k_fill and k_rank_permute of a small system in one
+// block: counts, starts and members stay in LDS.  The four launches cost 20 us
+// on the stream at 1,000 and 8,000 atoms alike, this one 8.6 and 32 us (one
+// compute unit's loads and stores), so it serves up to 3,072 atoms.
+constexpr int kSortAtoms = 3072, kSortCells = 4096;
+constexpr int kSortThreads = 1024;
+__global__ __launch_bounds__(kSortThreads) void k_sort_small(
+    int n, int ncell, const double* __restrict__ src, const double* __restrict__ vel_src,
+    const double* __restrict__ pos, const double* __restrict__ vel, const int* __restrict__ perm,
+    Box box, int nc0, int nc1, int nc2, int wrap_in_place, int* __restrict__ start, Sorted out) {
+  constexpr int Q = kSortAtoms / kSortThreads, CQ = kSortCells / kSortThreads;
+  __shared__ int s_run[kSortCells];      // counts, then the next free place of a cell
+  __shared__ int s_member[kSortAtoms];
+  __shared__ int s_wave[kSortThreads / 64];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  for (int c = t; c < ncell; c += kSortThreads) s_run[c] = 0;
+  __syncthreads();
+  double r[Q][3];
+  int w[Q][3], cell[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + q * kSortThreads;
+    if (i < n)
+      for (int a = 0; a < 3; ++a) r[q][a] = (src ? src : pos)[(size_t)a * n + i];
   }
-  const int w0 = wrap[o], w1 = wrap[n + o], w2 = wrap[2 * n + o];
-  wrap_out[k] = w0;
-  wrap_out[n + k] = w1;
-  wrap_out[2 * n + k] = w2;
-  const int caller = perm[o];
-  perm_out[k] = caller;
-  iperm_out[caller] = k;  // caller index -> new internal index
-  cell_out[k] = c;
-  if (w0 < -127 || w0 > 127 || w1 < -127 || w1 > 127 || w2 < -127 || w2 > 127)
-    flags[kFlagImage] = 1;
-  r.j = k;
-  r.w = (w0 & 0xFF) | ((w1 & 0xFF) << 8) | ((w2 & 0xFF) << 16);
-  rec[k] = r;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + q * kSortThreads;
+    if (i >= n) continue;
+    (void)bin_atom(r[q], box, nc0, nc1, nc2, wrap_in_place, w[q], cell[q]);
+    atomicAdd(&s_run[cell[q]], 1);
+  }
+  __syncthreads();
+  {  // exclusive scan of the counts, CQ consecutive cells per thread
+    int own[CQ], sum = 0;
+#pragma unroll
+    for (int q = 0; q < CQ; ++q) {
+      const int c = t * CQ + q;
+      own[q] = sum;
+      sum += c < ncell ? s_run[c] : 0;
+    }
+    int inc = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int y = __shfl_up(inc, d, 64);
+      if (lane >= d) inc += y;
+    }
+    if (lane == 63) s_wave[wv] = inc;
+    __syncthreads();
+    int before = inc - sum;
+    for (int u = 0; u < wv; ++u) before += s_wave[u];
+#pragma unroll
+    for (int q = 0; q < CQ; ++q) {
+      const int c = t * CQ + q;
+      if (c < ncell) {
+        s_run[c] = before + own[q];
+        start[c] = before + own[q];
+      }
+    }
+    if (t == 0) start[ncell] = n;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + q * kSortThreads;
+    if (i < n) s_member[atomicAdd(&s_run[cell[q]], 1)] = i;
+  }
+  __syncthreads();
+  // now s_run[c] is the end of cell c and s_run[c - 1] its beginning
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + q * kSortThreads;
+    if (i >= n) continue;
+    const int c = cell[q], b = c > 0 ? s_run[c - 1] : 0, e = s_run[c];
+    int rank = 0;
+    for (int m = b; m < e; ++m) rank += s_member[m] < i ? 1 : 0;
+    double v[3] = {0.0, 0.0, 0.0};
+    if (out.vel)
+      for (int a = 0; a < 3; ++a) v[a] = (vel_src ? vel_src : vel)[(size_t)a * n + i];
+    place_atom(n, b + rank, r[q], v, w[q][0], w[q][1], w[q][2], src ? i : perm[i], c, out);
+  }
 }
 
 // Two [3][n] arrays of the caller's into the internal order: a, and b unless
@@ -291,10 +394,18 @@ __global__ void k_put_rows2(int n, const double* __restrict__ a, double* __restr
 // cutoff (up to SC of them, their numbers in scan order in LDS) and the exact
 // test runs on those alone, with their float64 records read from global
 // memory; the lists are the same as those of the plain scan.  Atoms are in
-// cell order, so a cell's atoms are start[c] .. start[c+1]-1.
+// cell order, so a cell's atoms are start[c] .. start[c+1]-1.  `splits` blocks
+// share a cell's atoms (few cells: see build_neighbors).
+//
+// Bound: the latency of a block's phases (cell ranges, records, two passes, the
+// list stores) and, on full chips, VALU issue of the first pass.  The first pass
+// works on positions inside the box, so that atoms that lie in another image
+// pass it like any other; leaving those to the exact test, 64,000 jittered PbTe
+// atoms took 252 us (now 85) and 1,000 silicon atoms 34 us (now 13, with four
+// blocks per cell).
 template <int G, int RO, int SC, int MAXC, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_build_cells(
-    int n, int cap, const double* __restrict__ pos, Box box, int nc0, int nc1, int nc2,
+    int n, int cap, int splits, const double* __restrict__ pos, Box box, int nc0, int nc1, int nc2,
     const int* __restrict__ wrap, const int* __restrict__ start,
     const CellRec* __restrict__ rec, double rc2_r, double rc2_a, uint32_t* __restrict__ nl,
     uint32_t* __restrict__ nl_rm, int* __restrict__ cnt_r, int* __restrict__ cnt_a,
@@ -305,49 +416,72 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   __shared__ int s_first[27];  // first member slot of each neighbour cell
   __shared__ int s_img[27];    // packed periodic image offset of each neighbour cell
   __shared__ double s_shift[27][3];  // its lattice shift (for atoms with equal offsets)
-  __shared__ float4 s_pf[MAXC];  // candidate position - cell centre (float32), wrap offsets
-  __shared__ uint8_t s_cell[MAXC];
+  __shared__ float4 s_pf[MAXC];  // candidate position - cell centre (float32), its cell
   __shared__ uint32_t s_ro[NG][RO];  // radial-only entries in scan order
   __shared__ uint16_t s_cand[NG][SC];  // candidates left by the first pass
   static_assert(MAXC <= 65536, "candidate numbers in 16 bits");
-  const int cell = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int logical = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int cell = logical / splits, part = logical % splits;
   const int c0 = cell % nc0, c1 = (cell / nc0) % nc1, c2 = cell / (nc0 * nc1);
   const int tid = threadIdx.x;
-  // thread q < 27 looks up neighbour cell q (offsets o2, o1, o0 in -1..1, o0 fastest)
-  if (tid < 27) {
-    const int e0 = c0 + tid % 3 - 1, e1 = c1 + (tid / 3) % 3 - 1, e2 = c2 + tid / 9 - 1;
-    const int m0 = e0 < 0 ? -1 : (e0 >= nc0 ? 1 : 0);
-    const int m1 = e1 < 0 ? -1 : (e1 >= nc1 ? 1 : 0);
-    const int m2 = e2 < 0 ? -1 : (e2 >= nc2 ? 1 : 0);
-    const int cc = ((e2 - m2 * nc2) * nc1 + (e1 - m1 * nc1)) * nc0 + (e0 - m0 * nc0);
-    const int b = start[cc];
-    s_first[tid] = b;
-    s_off[tid + 1] = start[cc + 1] - b;
-    s_img[tid] = (m0 + 1) | ((m1 + 1) << 2) | ((m2 + 1) << 4);
-    image_shift(m0, m1, m2, box.h, s_shift[tid][0], s_shift[tid][1], s_shift[tid][2]);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    s_off[0] = 0;
-    for (int q = 1; q <= 27; ++q) s_off[q] += s_off[q - 1];
+  // lane q < 27 of the first wave looks up neighbour cell q (offsets o2, o1, o0
+  // in -1..1, o0 fastest); a wave scan numbers the candidates
+  if (tid < 64) {
+    int cnt = 0;
+    if (tid < 27) {
+      const int e0 = c0 + tid % 3 - 1, e1 = c1 + (tid / 3) % 3 - 1, e2 = c2 + tid / 9 - 1;
+      const int m0 = e0 < 0 ? -1 : (e0 >= nc0 ? 1 : 0);
+      const int m1 = e1 < 0 ? -1 : (e1 >= nc1 ? 1 : 0);
+      const int m2 = e2 < 0 ? -1 : (e2 >= nc2 ? 1 : 0);
+      const int cc = ((e2 - m2 * nc2) * nc1 + (e1 - m1 * nc1)) * nc0 + (e0 - m0 * nc0);
+      const int b = start[cc];
+      cnt = start[cc + 1] - b;
+      s_first[tid] = b;
+      s_img[tid] = (m0 + 1) | ((m1 + 1) << 2) | ((m2 + 1) << 4);
+      image_shift(m0, m1, m2, box.h, s_shift[tid][0], s_shift[tid][1], s_shift[tid][2]);
+    }
+    int sum = cnt;
+#pragma unroll
+    for (int d = 1; d < 32; d <<= 1) {
+      const int y = __shfl_up(sum, d, 64);
+      if (tid >= d) sum += y;
+    }
+    if (tid < 27) s_off[tid + 1] = sum;
+    if (tid == 0) s_off[0] = 0;
   }
   __syncthreads();
   const int total = s_off[27];
-  if (tid < 27)
-    for (int c = s_off[tid]; c < s_off[tid + 1] && c < MAXC; ++c) s_cell[c] = (uint8_t)tid;
-  __syncthreads();
   // the cell centre: the first pass works on coordinates relative to it
   const double f0 = (c0 + 0.5) / nc0, f1 = (c1 + 0.5) / nc1, f2 = (c2 + 0.5) / nc2;
   const double ox = f0 * box.h[0] + f1 * box.h[3] + f2 * box.h[6];
   const double oy = f0 * box.h[1] + f1 * box.h[4] + f2 * box.h[7];
   const double oz = f0 * box.h[2] + f1 * box.h[5] + f2 * box.h[8];
-  if (total <= MAXC)
-    for (int c = tid; c < total; c += NT) {
-      const int q = s_cell[c];
-      const CellRec r = rec[s_first[q] + (c - s_off[q])];
-      s_pf[c] = make_float4((float)((r.x + s_shift[q][0]) - ox), (float)((r.y + s_shift[q][1]) - oy),
-                            (float)((r.z + s_shift[q][2]) - oz), __int_as_float(r.w & 0xFFFFFF));
+  // a position moved into the box by its wrap counts
+  auto unwrap = [&](double x, double y, double z, int w0, int w1, int w2, double& tx, double& ty,
+                    double& tz) {
+    tx = x;
+    ty = y;
+    tz = z;
+    if (w0 | w1 | w2) {
+      tx -= (double)w0 * box.h[0] + (double)w1 * box.h[3] + (double)w2 * box.h[6];
+      ty -= (double)w0 * box.h[1] + (double)w1 * box.h[4] + (double)w2 * box.h[7];
+      tz -= (double)w0 * box.h[2] + (double)w1 * box.h[5] + (double)w2 * box.h[8];
     }
+  };
+  // eight threads per neighbour cell (27 of them)
+  static_assert(NT >= 27 * 8, "threads of the staging");
+  if (total <= MAXC && tid < 27 * 8) {
+    const int q = tid / 8, first = s_first[q], off = s_off[q], cnt = s_off[q + 1] - off;
+    const double sx = s_shift[q][0] - ox, sy = s_shift[q][1] - oy, sz = s_shift[q][2] - oz;
+    for (int m = tid % 8; m < cnt; m += 8) {
+      const CellRec r = rec[first + m];
+      double tx, ty, tz;
+      unwrap(r.x, r.y, r.z, (signed char)(r.w & 0xFF), (signed char)((r.w >> 8) & 0xFF),
+             (signed char)((r.w >> 16) & 0xFF), tx, ty, tz);
+      s_pf[off + m] = make_float4((float)(tx + sx), (float)(ty + sy), (float)(tz + sz),
+                                  __int_as_float(q));
+    }
+  }
   __syncthreads();
 
   const int grp = tid / G;
@@ -356,11 +490,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   const unsigned long long below = (1ull << k) - 1ull;
   const unsigned long long gmask = G == 64 ? ~0ull : ((1ull << G) - 1ull);
   const int a1 = start[cell + 1];
-  // First-pass bound.  For an atom within kNear of the cell centre (each
-  // component) and a candidate with its wrap offsets whose true displacement
-  // d has |d| < r_c (the larger cutoff), each float32 displacement component
-  // is off by at most eps = 2^-22 (kNear + r_c) (three roundings of values
-  // below kNear + r_c), so |d_f| < r_c + 2 eps and the float32 |d_f|^2 (three
+  // First-pass bound.  The pass works on positions moved into the box and by
+  // the neighbour cell's lattice shift, relative to the cell centre; in float64
+  // their difference is the true displacement d up to rounding of the raw
+  // coordinates (far below the factor 1 + 2^-20 of thr).  For positions within kNear of the centre (each component) and
+  // |d| < r_c (the larger cutoff), each float32 displacement component is off
+  // by at most eps = 2^-22 (kNear + r_c) (three roundings of values below
+  // kNear + r_c), so |d_f| < r_c + 2 eps and the float32 |d_f|^2 (three
   // roundings) stays below thr: such a candidate always passes.
   constexpr float kNear = 4096.f;
   const double rcm = sqrt(fmax(rc2_r, rc2_a));
@@ -369,7 +505,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
   // records from LDS when all candidates were staged, else all from global
   // memory (two instantiations, so that neither path uses generic addresses)
   auto scan = [&](auto staged) {
-  for (int i = start[cell] + grp; i < a1; i += NG) {
+  for (int i = start[cell] + part * NG + grp; i < a1; i += splits * NG) {
     const double xi = pos[i], yi = pos[n + i], zi = pos[2 * n + i];
     const int wi0 = wrap[i], wi1 = wrap[n + i], wi2 = wrap[2 * n + i];
     bool overflow = false, bad_image = false;
@@ -378,7 +514,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
       int q;  // the cell that holds candidate c: off[q] <= c < off[q+1]
       CellRec rc;
       if constexpr (decltype(staged)::value) {
-        q = s_cell[c];
+        q = __float_as_int(s_pf[c].w);
         rc = rec[s_first[q] + (c - s_off[q])];
       } else {
         int lo = 0, hi = 27;
@@ -415,22 +551,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
         entry = pack_entry(j, n0, n1, n2);
       }
     };
-    // First pass over the staged positions.  A candidate with the atom's own
-    // wrap counts (d = 0 below) is left out only if its float32 distance
-    // exceeds the bound thr above; every other candidate (and every
-    // candidate of an atom beyond kNear of the cell centre) is left to the
-    // exact test.  So the exact test sees every candidate it would keep, in
-    // scan order.
+    // First pass over the staged positions: a candidate is left out only if its
+    // float32 distance exceeds the bound thr above, so the exact test sees every
+    // candidate it would keep, in scan order.  An atom beyond kNear of the
+    // centre, or beyond 127 cells, leaves every candidate to it.
     int ncand = total;
     bool listed = false;
     if constexpr (decltype(staged)::value) {
-      const bool in_range = wi0 >= -128 && wi0 <= 127 && wi1 >= -128 && wi1 <= 127 &&
-                            wi2 >= -128 && wi2 <= 127;
-      const float xf = (float)(xi - ox), yf = (float)(yi - oy), zf = (float)(zi - oz);
-      const bool near = fabsf(xf) <= kNear && fabsf(yf) <= kNear && fabsf(zf) <= kNear;
-      const int wpack = in_range && near
-                            ? (wi0 & 0xFF) | ((wi1 & 0xFF) << 8) | ((wi2 & 0xFF) << 16)
-                            : -1;
+      double tx, ty, tz;
+      unwrap(xi, yi, zi, wi0, wi1, wi2, tx, ty, tz);
+      const float xf = (float)(tx - ox), yf = (float)(ty - oy), zf = (float)(tz - oz);
+      const bool near = fabsf(xf) <= kNear && fabsf(yf) <= kNear && fabsf(zf) <= kNear &&
+                        wi0 >= -127 && wi0 <= 127 && wi1 >= -127 && wi1 <= 127 && wi2 >= -127 &&
+                        wi2 <= 127;
       int nk = 0;
       for (int base = 0; base < total; base += G) {
         const int c = base + k;
@@ -439,7 +572,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8))) void k_
           const float4 pf = s_pf[c];
           const float ex = pf.x - xf, ey = pf.y - yf, ez = pf.z - zf;
           const float r2f = __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex));
-          pass = __float_as_int(pf.w) != wpack || r2f < thr;
+          pass = !near || r2f < thr;
         }
         const unsigned long long bp = (__ballot(pass) >> shift) & gmask;
         if (pass) {
@@ -800,45 +933,59 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const
         (e = s.perm_t.ensure(n)) != hipSuccess || (e = s.wrap_t.ensure((size_t)3 * n)) != hipSuccess ||
         (e = s.cell_t.ensure(n)) != hipSuccess)
       return check_hip(ctx, e, "allocating cell lists");
-    const bool zero = s.cell_cnt.ptr != cnt_before || s.cells_zeroed_for != ncell;
-    if (zero)
-      launch_kernel(ctx, true, false, k_zero, dim3(blocks_for(ncell, kBlock)), blk,
-                    s.cell_cnt.ptr, ncell);
-    launch_kernel(ctx, !zero, false, k_bin, dim3(blocks_for(n, kBlock)), blk, n, src, vel_src,
-                  s.pos_s.ptr, s.vel_s.ptr, s.perm.ptr, s.iperm.ptr, s.box, s.nc[0], s.nc[1],
-                  s.nc[2], 1, wrap_in_place ? 1 : 0, s.wrap.ptr, s.cell_of.ptr, s.cell_cnt.ptr,
-                  (float*)nullptr);
-    const int nsb = (ncell + 1023) / 1024;
-    if (ncell > 1024 * kScanChunks && nsb <= 1024) {
-      launch_kernel(ctx, false, false, k_scan_blocks, dim3(nsb), dim3(1024), ncell,
-                    (const int*)s.cell_cnt.ptr, s.cell_start.ptr, s.scan_part.ptr);
-      launch_kernel(ctx, false, false, k_scan_totals, dim3(1), dim3(1024), nsb, ncell,
-                    s.scan_part.ptr, s.cell_start.ptr);
-      launch_kernel(ctx, false, false, k_scan_add, dim3(blocks_for(ncell, kBlock)), blk, ncell,
-                    (const int*)s.scan_part.ptr, s.cell_start.ptr, s.cell_cnt.ptr,
-                    s.cell_fill.ptr);
+    const Sorted sorted{s.pos_t.ptr,  have_vel ? s.vel_t.ptr : (double*)nullptr,
+                        s.wrap_t.ptr, s.perm_t.ptr,
+                        s.iperm.ptr,  s.cell_t.ptr,
+                        s.cell_rec.ptr, s.pos_ref.ptr,
+                        ctx->flags.ptr};
+    if (n <= kSortAtoms && ncell <= kSortCells) {
+      launch_kernel(ctx, true, false, k_sort_small, dim3(1), dim3(kSortThreads), n, ncell, src,
+                    vel_src, (const double*)s.pos_s.ptr, (const double*)s.vel_s.ptr,
+                    (const int*)s.perm.ptr, s.box, s.nc[0], s.nc[1], s.nc[2],
+                    wrap_in_place ? 1 : 0, s.cell_start.ptr, sorted);
     } else {
-      launch_kernel(ctx, false, false, k_scan, dim3(1), dim3(1024), ncell, s.cell_cnt.ptr,
-                    s.cell_start.ptr, s.cell_fill.ptr);
+      const bool zero = s.cell_cnt.ptr != cnt_before || s.cells_zeroed_for != ncell;
+      if (zero)
+        launch_kernel(ctx, true, false, k_zero, dim3(blocks_for(ncell, kBlock)), blk,
+                      s.cell_cnt.ptr, ncell);
+      launch_kernel(ctx, !zero, false, k_bin, dim3(blocks_for(n, kBlock)), blk, n, src, vel_src,
+                    s.pos_s.ptr, s.vel_s.ptr, s.perm.ptr, s.iperm.ptr, s.box, s.nc[0], s.nc[1],
+                    s.nc[2], 1, wrap_in_place ? 1 : 0, s.wrap.ptr, s.cell_of.ptr, s.cell_cnt.ptr,
+                    (float*)nullptr);
+      const int nsb = (ncell + 1023) / 1024;
+      if (ncell > 1024 * kScanChunks && nsb <= 1024) {
+        launch_kernel(ctx, false, false, k_scan_blocks, dim3(nsb), dim3(1024), ncell,
+                      (const int*)s.cell_cnt.ptr, s.cell_start.ptr, s.scan_part.ptr);
+        launch_kernel(ctx, false, false, k_scan_totals, dim3(1), dim3(1024), nsb, ncell,
+                      s.scan_part.ptr, s.cell_start.ptr);
+        launch_kernel(ctx, false, false, k_scan_add, dim3(blocks_for(ncell, kBlock)), blk, ncell,
+                      (const int*)s.scan_part.ptr, s.cell_start.ptr, s.cell_cnt.ptr,
+                      s.cell_fill.ptr);
+      } else {
+        launch_kernel(ctx, false, false, k_scan, dim3(1), dim3(1024), ncell, s.cell_cnt.ptr,
+                      s.cell_start.ptr, s.cell_fill.ptr);
+      }
+      s.cells_zeroed_for = ncell;
+      launch_kernel(ctx, false, false, k_fill, dim3(blocks_for(n, kBlock)), blk, n,
+                    (const int*)s.cell_of.ptr, (const int*)s.cell_start.ptr, s.cell_fill.ptr,
+                    s.cell_atoms.ptr);
+      launch_kernel(ctx, false, false, k_rank_permute, dim3(blocks_for(n, kBlock)), blk, n,
+                    (const int*)s.cell_start.ptr, (const int*)s.cell_atoms.ptr,
+                    (const double*)s.pos_s.ptr, (const double*)s.vel_s.ptr, (const int*)s.wrap.ptr,
+                    (const int*)s.perm.ptr, (const int*)s.cell_of.ptr, sorted);
     }
-    s.cells_zeroed_for = ncell;
-    launch_kernel(ctx, false, false, k_fill, dim3(blocks_for(n, kBlock)), blk, n,
-                  (const int*)s.cell_of.ptr, (const int*)s.cell_start.ptr, s.cell_fill.ptr,
-                  s.cell_atoms.ptr);
-    launch_kernel(ctx, false, false, k_rank_permute, dim3(blocks_for(n, kBlock)), blk, n,
-                  (const int*)s.cell_start.ptr, (const int*)s.cell_atoms.ptr,
-                  (const double*)s.pos_s.ptr, s.pos_t.ptr,
-                  have_vel ? (const double*)s.vel_s.ptr : (const double*)nullptr,
-                  have_vel ? s.vel_t.ptr : (double*)nullptr, (const int*)s.wrap.ptr, s.wrap_t.ptr,
-                  (const int*)s.perm.ptr, s.perm_t.ptr, (const int*)s.cell_of.ptr, s.cell_t.ptr,
-                  s.cell_rec.ptr, s.iperm.ptr, s.pos_ref.ptr, ctx->flags.ptr);
     s.pos_s.swap(s.pos_t);
     if (have_vel) s.vel_s.swap(s.vel_t);
     s.wrap.swap(s.wrap_t);
     s.perm.swap(s.perm_t);
     s.cell_of.swap(s.cell_t);
-    launch_kernel(ctx, false, false, k_build_cells<32, 64, 96, 640, 256>, dim3(ncell), dim3(256), n,
-                  s.cap, (const double*)s.pos_s.ptr, s.box, s.nc[0], s.nc[1], s.nc[2],
+    // A block scans eight atoms side by side; where all cells' blocks fit the
+    // chip at once (256 compute units x 8) several blocks share a cell, up to
+    // one per eight atoms of an average cell.
+    const int per_cell = (n + 8 * ncell - 1) / (8 * ncell);
+    const int splits = std::max(1, std::min(per_cell, 2048 / ncell));
+    launch_kernel(ctx, false, false, k_build_cells<32, 64, 96, 640, 256>, dim3(ncell * splits),
+                  dim3(256), n, s.cap, splits, (const double*)s.pos_s.ptr, s.box, s.nc[0], s.nc[1], s.nc[2],
                   (const int*)s.wrap.ptr, (const int*)s.cell_start.ptr,
                   (const CellRec*)s.cell_rec.ptr, rc2_r, rc2_a, s.nl.ptr, s.nl_rm.ptr, s.cnt_r.ptr,
                   s.cnt_a.ptr, ctx->flags.ptr);

@@ -1,0 +1,48 @@
+"""Cell lists at the sizes and positions where their build takes another route:
+one block or several kernels to sort the atoms, several blocks per cell, more
+candidates than fit the staged ones, atoms lying in other images of the box.
+Entries, images and reverse slots against the oracle's float64 predicate; the
+lists are whole numbers and must be equal."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2107_08119_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def keys(i, j, n):
+    n = np.asarray(n, np.int64)
+    return np.sort((np.asarray(i, np.int64) * (1 << 23) + j) * 343 + (n[:, 0] + 3) + 7 * (n[:, 1] + 3) + 49 * (n[:, 2] + 3))
+
+
+@pytest.mark.parametrize("n,density,images", [(300, 0.05, 0), (1023, 0.05, 1), (1024, 0.05, 0), (1025, 0.05, 1),
+                                              (3072, 0.05, 1), (3073, 0.05, 1), (2500, 0.25, 1), (9000, 0.05, 0)])
+def test_lists_match_oracle(n, density, images):
+    from paper_2107_08119_amd import nep
+    rng = np.random.default_rng(n)
+    edge = max((n / density) ** (1.0 / 3.0), 16.6)  # three cells of the 5.5 A list cutoff at least
+    box = np.diag([edge, edge * 1.05, edge * 0.98 + 0.6]) + 0.4 * np.eye(3)[[1, 2, 0]]
+    inside = rng.random((n, 3)) @ box
+    shift = rng.integers(-images, images + 1, (n, 3)) * (rng.random((n, 1)) < 0.3)
+    pos = inside + shift @ box
+    cap = 1024 if density > 0.1 else 160
+    ctx = nep.Context(0)
+    ctx.load_params(nep.hyper(), I.random_parameters(931, 3))
+    ctx.build_neighbors(nep.soa(pos), box, skin=0.5, max_neighbors=cap)
+    nb = {k: v.cpu().numpy() for k, v in ctx.get_neighbors().items()}
+    ctx.synchronize()
+    slots = np.arange(cap)[:, None]
+    for rc, which in ((5.5, "cnt_radial"), (4.5, "cnt_angular")):
+        cnt, jl, img = O.neighbor_arrays(pos, box, rc, cap=cap)
+        inside = np.arange(jl.shape[1])[None] < cnt[:, None]
+        ref = keys(np.repeat(np.arange(n), cnt), jl[inside], img[inside])
+        mine = slots < nb[which][None]
+        i = np.broadcast_to(np.arange(n), (cap, n))[mine]
+        np.testing.assert_array_equal(keys(i, nb["nbr"][mine], nb["img"][mine]), ref)
+    mine = slots < nb["cnt_radial"][None]
+    i = np.broadcast_to(np.arange(n), (cap, n))[mine]
+    back, j = nb["rev"][mine], nb["nbr"][mine]
+    np.testing.assert_array_equal(nb["nbr"][back, j], i)
+    np.testing.assert_array_equal(nb["img"][back, j], -nb["img"][mine])
