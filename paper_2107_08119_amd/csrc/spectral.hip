@@ -11,7 +11,7 @@
 //   K_sum[k] += sum_i W_i(t - k) . v_i(t).
 // Block sums are added in block order (no atomics), so the sums are
 // reproducible bit for bit.  Averages divide by the number of origins of
-// each lag.  K is taken even in t; the transform is windowed (Hann) and uses
+// each lag and are kept with every sample.  K is taken even in t; the transform is windowed (Hann) and uses
 // the trapezoid rule over the lags, all in float64.
 #include <algorithm>
 #include <cmath>
@@ -44,14 +44,19 @@ inline unsigned vblocks(int n) {
 
 // Block (b, k): atoms b*kVBlock*kVAtoms + tid + kVBlock*a; lag k reads the
 // ring slot of sample t - k.  part[k][b][mu] = sum over its atoms of
-// sum_nu W_mu,nu v_nu (float64 products of the float32 virial).
+// sum_nu W_mu,nu v_nu (float64 products of the float32 virial).  The blocks of
+// lag 0 read the new sample from the caller's array and put it into the ring.
+// Bound: the read of the ring, 36 bytes per atom and lag (576 MB in 104 us at
+// 64,000 atoms and 250 lags).
 __global__ __launch_bounds__(kVBlock) void k_vvcf_blocks(int n, int lags, int head,
-                                                         const float* __restrict__ ring,
+                                                         float* __restrict__ ring,
+                                                         const float* __restrict__ W_new,
                                                          const double* __restrict__ vel,
                                                          double* __restrict__ part) {
   const int b = (int)blockIdx.x, k = (int)blockIdx.y;
   const int slot = (head - k + lags) % lags;
-  const float* __restrict__ W = ring + (size_t)slot * 9 * n;
+  float* const own = ring + (size_t)slot * 9 * n;
+  const float* __restrict__ W = k == 0 ? W_new : own;
   double acc[3] = {0.0, 0.0, 0.0};
   const int base = b * kVBlock * kVAtoms + (int)threadIdx.x;
 #pragma unroll
@@ -59,11 +64,15 @@ __global__ __launch_bounds__(kVBlock) void k_vvcf_blocks(int n, int lags, int he
     const int i = base + a * kVBlock;
     if (i < n) {
       const double vx = vel[i], vy = vel[n + i], vz = vel[2 * n + i];
+      float w[9];
+#pragma unroll
+      for (int q = 0; q < 9; ++q) w[q] = W[(size_t)q * n + i];
+      if (k == 0)
+#pragma unroll
+        for (int q = 0; q < 9; ++q) own[(size_t)q * n + i] = w[q];
 #pragma unroll
       for (int mu = 0; mu < 3; ++mu)
-        acc[mu] += (double)W[(size_t)(3 * mu) * n + i] * vx +
-                   (double)W[(size_t)(3 * mu + 1) * n + i] * vy +
-                   (double)W[(size_t)(3 * mu + 2) * n + i] * vz;
+        acc[mu] += (double)w[3 * mu] * vx + (double)w[3 * mu + 1] * vy + (double)w[3 * mu + 2] * vz;
     }
   }
   __shared__ double sw[kVBlock / 64][3];
@@ -71,24 +80,21 @@ __global__ __launch_bounds__(kVBlock) void k_vvcf_blocks(int n, int lags, int he
   if (threadIdx.x < 3) part[((size_t)k * gridDim.x + b) * 3 + threadIdx.x] = s;
 }
 
-// Thread (k, mu): ksum[k][mu] += sum over blocks in order.
-__global__ void k_vvcf_add(int lags_done, int nblocks, const double* __restrict__ part,
-                           double* __restrict__ ksum) {
+// Thread (k, mu): ksum[k][mu] += sum over blocks in order, and kavg[k][mu] its
+// average over the samples - k origins of lag k.
+__global__ void k_vvcf_add(int lags_done, long long samples, int nblocks,
+                           const double* __restrict__ part, double* __restrict__ ksum,
+                           double* __restrict__ kavg) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= 3 * lags_done) return;
   const int k = t / 3, mu = t % 3;
+  const double* p = part + (size_t)k * nblocks * 3 + mu;
   double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += part[((size_t)k * nblocks + b) * 3 + mu];
-  ksum[t] += s;
-}
-
-// Averages over the origins of each lag: lag k has samples - k of them.
-__global__ void k_vvcf_average(int lags, long long samples, const double* __restrict__ ksum,
-                               double* __restrict__ kavg) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 3 * lags) return;
-  const long long cnt = samples - t / 3;
-  kavg[t] = cnt > 0 ? ksum[t] / (double)cnt : 0.0;
+#pragma unroll 16
+  for (int b = 0; b < nblocks; ++b) s += p[3 * b];
+  const double sum = ksum[t] + s;
+  ksum[t] = sum;
+  kavg[t] = sum / (double)(samples - k);
 }
 
 // Thread (mu, f): kappa[0][mu][f] = unit * 2 / (T V F_e) * 2 * dt *
@@ -145,6 +151,7 @@ nep_status nep_vvcf_create(nep_ctx ctx, int n_atoms, int n_lags, nep_vvcf* out) 
   if (e == hipSuccess) e = v->kavg.ensure((size_t)3 * n_lags);
   if (e == hipSuccess) e = v->part.ensure((size_t)3 * n_lags * vblocks(n_atoms));
   if (e == hipSuccess) e = hipMemsetAsync(v->ksum.ptr, 0, sizeof(double) * 3 * n_lags, ctx->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(v->kavg.ptr, 0, sizeof(double) * 3 * n_lags, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
   if (e != hipSuccess) {
     nep_vvcf_destroy(v);
@@ -173,16 +180,13 @@ nep_status nep_vvcf_sample(nep_ctx ctx, nep_vvcf v, const float* W_dev, const do
   DeviceGuard guard(ctx->device);
   const int n = v->n, lags = v->lags;
   const int head = (int)(v->samples % lags);
-  hipError_t e = hipMemcpyAsync(v->ring.ptr + (size_t)head * 9 * n, W_dev, sizeof(float) * 9 * n,
-                                hipMemcpyDeviceToDevice, ctx->stream);
-  if (e != hipSuccess) return check_hip(ctx, e, "copying the virials");
   const int done = (int)std::min<long long>(v->samples + 1, lags);
   const unsigned nb = vblocks(n);
   launch_kernel(ctx, true, false, k_vvcf_blocks, dim3(nb, done), dim3(kVBlock), n, lags, head,
-                (const float*)v->ring.ptr, vel_dev, v->part.ptr);
-  launch_kernel(ctx, false, true, k_vvcf_add, dim3(blocks_of((size_t)3 * done, 256)), dim3(256),
-                done, (int)nb, (const double*)v->part.ptr, v->ksum.ptr);
-  e = hipGetLastError();
+                v->ring.ptr, W_dev, vel_dev, v->part.ptr);
+  launch_kernel(ctx, false, true, k_vvcf_add, dim3(blocks_of((size_t)3 * done, 64)), dim3(64), done,
+                v->samples + 1, (int)nb, (const double*)v->part.ptr, v->ksum.ptr, v->kavg.ptr);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return check_hip(ctx, e, "launching the correlation kernels");
   ++v->samples;
   return NEP_OK;
@@ -192,10 +196,8 @@ nep_status nep_vvcf_get(nep_ctx ctx, nep_vvcf v, double* K_host, long long* samp
   if (!ctx || !v || v->ctx != ctx) return NEP_EINVAL;
   DeviceGuard guard(ctx->device);
   const int lags = v->lags;
-  launch_kernel(ctx, true, true, k_vvcf_average, dim3(blocks_of((size_t)3 * lags, 256)), dim3(256),
-                lags, v->samples, (const double*)v->ksum.ptr, v->kavg.ptr);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess && K_host)
+  hipError_t e = hipSuccess;
+  if (K_host)
     e = hipMemcpyAsync(K_host, v->kavg.ptr, sizeof(double) * 3 * lags, hipMemcpyDeviceToHost,
                        ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -223,14 +225,12 @@ nep_status nep_vvcf_spectrum(nep_ctx ctx, nep_vvcf v, double dt_fs, double tempe
                        ctx->stream);
   if (e != hipSuccess) return check_hip(ctx, e, "spectrum buffers");
   const int lags = v->lags;
-  launch_kernel(ctx, true, false, k_vvcf_average, dim3(blocks_of((size_t)3 * lags, 256)), dim3(256),
-                lags, v->samples, (const double*)v->ksum.ptr, v->kavg.ptr);
   // W/(m K THz) per eV/(A K): (1 eV/fs in W) (1/A in 1/m) (1 fs in ps)
   const double unit = 1.602176634e-19 / 1.0e-15 * 1.0e10 * 1.0e-3;
   const double pref = unit * 2.0 / (temperature * volume * fe) * 2.0 * dt_fs;
   // x = hbar 2 pi nu / k_B T with nu in THz
   const double x_per_thz = 1.054571817e-34 * 2.0 * M_PI * 1.0e12 / (1.380649e-23 * temperature);
-  launch_kernel(ctx, false, true, k_vvcf_spectrum, dim3(blocks_of((size_t)3 * n_nu, 256)),
+  launch_kernel(ctx, true, true, k_vvcf_spectrum, dim3(blocks_of((size_t)3 * n_nu, 256)),
                 dim3(256), lags, n_nu, (const double*)v->kavg.ptr, (const double*)v->nu.ptr,
                 dt_fs, pref, x_per_thz, v->kappa.ptr);
   e = hipGetLastError();
