@@ -194,7 +194,7 @@ __host__ __device__ inline int atom_chunks(int pairs, int ang) {
   return kGSteps + kSSteps * radial_tiles(pairs) + kASteps * angular_tiles(ang);
 }
 
-// Fixed-point accumulators of a tile in LDS (162,816 bytes): forces
+// Fixed-point accumulators of a tile in LDS (at most 162,816 bytes): forces
 // [atom][3][KC] and structure virials [structure][9][KC], 32-bit integers.
 constexpr int kLdsInts = 40704;
 constexpr int kTileTarget = 64;
@@ -225,10 +225,10 @@ __global__ void k_pop_qpad(int N, const float* __restrict__ desc, float* __restr
 // One thread per (atom i, descriptor component nu < 29): D_ij[.][nu] for
 // every pair of i, written into i's radial or angular fragment chunks, and
 // row nu of G_i and V_i.  The thread of nu = 0 also writes the pair records
-// (r_ij/r_ij, offset 3 kcs j of the receiver's force accumulators in the
-// tile).  pfrag must be zero before.
+// (r_ij/r_ij, 3 times the receiver's index in the tile).  pfrag must be zero
+// before.
 __global__ __launch_bounds__(kBlock) void k_pop_geo(
-    int N, int kcs, const float4* __restrict__ rec, const int4* __restrict__ pmeta,
+    int N, const float4* __restrict__ rec, const int4* __restrict__ pmeta,
     const float* __restrict__ desc, const int* __restrict__ struct_of,
     const int* __restrict__ stile0, float rc_r, float rc_a, float* __restrict__ pfrag,
     float4* __restrict__ ppair) {
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kBlock) void k_pop_geo(
       if (v == 0) {
         const int j = (int)((unsigned)__float_as_int(e.w) % (unsigned)N);
         ppair[(size_t)m.y + p] =
-            make_float4(e.x * rinv, e.y * rinv, e.z * rinv, __int_as_float((j - t0) * 3 * kcs));
+            make_float4(e.x * rinv, e.y * rinv, e.z * rinv, __int_as_float((j - t0) * 3));
       }
     }
   } else {
@@ -385,14 +385,21 @@ __global__ __launch_bounds__(64) void k_pop_wfrag(int n_par, const float* __rest
 // so G = w2 sech^2 never moves between lanes.  Each individual's weight
 // fragments are loaded while the previous individual is multiplied.
 // dq [N][n_pop][32] (padded order, zeros at 9..11), U [n_pop][N].
-// Individuals per wave of the network kernel: the population is split into
-// chunks over blockIdx.y, so that the grid has many more waves than the
-// machine holds at once (whole waves of all individuals left the last round
-// of waves mostly empty).
+// Individuals per wave of the network kernel (`chunk`, at most kNetChunk): the
+// population is split into chunks over blockIdx.y, so that the grid has many
+// more waves than the machine holds at once (whole waves of all individuals
+// left the last round of waves mostly empty).
+// Bound: the matrix cores (85 us of 16x16x4 steps per 50 individuals of 65,600
+// atoms) and the store of dU/dq (128 bytes per individual and atom), overlapped
+// by the waves of a SIMD: with three of them 32 atoms per wave take 445 us per
+// evaluation with the contraction, with two 455 us.
 constexpr int kNetChunk = 10;
+constexpr int kNetWaves = 4096;  // four per SIMD
 
 template <int CT>
-__global__ __launch_bounds__(kBlock) void k_pop_net(int N, int n_pop,
+__global__ __launch_bounds__(kBlock)
+    __attribute__((amdgpu_waves_per_eu(CT == 1 ? 4 : (CT == 2 ? 3 : 2)))) void k_pop_net(
+    int N, int n_pop, int chunk,
                                                     const float* __restrict__ qpad,
                                                     const float4* __restrict__ wf,
                                                     const float* __restrict__ wb2,
@@ -410,8 +417,8 @@ __global__ __launch_bounds__(kBlock) void k_pop_net(int N, int n_pop,
     for (int s = 0; s < 8; ++s) qb[ct][s] = a < N ? qpad[(size_t)a * kQ + 4 * s + h] : 0.f;
   }
   // the individuals k_begin .. k_end - 1 of this wave (blockIdx.y chunk)
-  const int k_begin = blockIdx.y * kNetChunk;
-  const int k_end = min(n_pop, k_begin + kNetChunk);
+  const int k_begin = blockIdx.y * chunk;
+  const int k_end = min(n_pop, k_begin + chunk);
   float4 nxt[12];
 #pragma unroll
   for (int q = 0; q < 12; ++q) nxt[q] = wf[((size_t)k_begin * 12 + q) * 64 + l];
@@ -553,7 +560,7 @@ __device__ __forceinline__ int fixed_exponent(float bound) {
 // are used.
 constexpr int kFastPairs = 32, kFastAng = 16;
 constexpr int kFastS = 2;
-constexpr int kCols = 4;  // column tiles of 16 individuals per wave
+template <int kCols>  // column tiles of 16 individuals per wave
 struct AtomOps {
   float b[kCols][8];   // dU/dq of the lane's individuals, K index 4 q + h
   float g[kGSteps];    // own-force / virial tile
@@ -568,7 +575,8 @@ __device__ __forceinline__ bool fast_atom(int4 m) { return m.z <= kFastPairs && 
 // atom's own reads a neighbour's data or padding) and masked at use: with no
 // branch between the loads, each operand waits only for itself.
 constexpr int kPadChunks = 64, kPadPairs = 64;
-__device__ __forceinline__ void fetch_atom(AtomOps& o, int4 m, int i, int n_pop,
+template <int kCols>
+__device__ __forceinline__ void fetch_atom(AtomOps<kCols>& o, int4 m, int i, int n_pop,
                                            const float* const (&dqk)[kCols],
                                            const float* pfrag, const float4* ppair, int l,
                                            int h) {
@@ -602,7 +610,8 @@ __device__ __forceinline__ void fetch_atom(AtomOps& o, int4 m, int i, int n_pop,
 }
 
 // Forces, energies, virials and squared errors of individuals k0 .. k0+KC-1
-// (KC <= 64) on the tile of structures tile_order[blockIdx.x].
+// (k0 = kper blockIdx.y, KC <= kper <= 16 kCols, the stride kcs = kper) on the
+// tile of structures tile_order[blockIdx.x].
 // Phase 1: the waves take the tile's atoms in turn; for each atom and each
 // column tile of 16 individuals they multiply the atom's operands by dU/dq
 // and add every product element, as round(x 2^e) with the tile's exponent e
@@ -611,9 +620,16 @@ __device__ __forceinline__ void fetch_atom(AtomOps& o, int4 m, int i, int n_pop,
 // their order, so results are the same for any schedule.
 // Phase 2: one unit per (structure, individual): lanes over the atoms form
 // the energy, force and virial errors in float64 in a fixed order.
-constexpr int kContractWaves = 12;
-__global__ __launch_bounds__(64 * kContractWaves) void k_pop_contract(
-    int N, int S, int k0, int KC, int kcs, int n_pop, const int* __restrict__ tile_order,
+// Bound: on large sets the matrix cores, the LDS additions and the read of the
+// fragments, with three or four waves per SIMD to cover the fetch of an atom's
+// operands; on small sets the chain of one wave's atoms, which launch_population
+// shortens by splitting the individuals over more blocks.  The column tiles are
+// a constant of the kernel: a branch around those past KC takes the overlap of
+// their products away (213 against 179 us for 50 individuals on 120 structures).
+constexpr int contract_waves(int cols) { return cols > 2 ? 12 : 16; }
+template <int kCols>
+__global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
+    int N, int S, int kper, int n_pop, const int* __restrict__ tile_order,
     const int* __restrict__ tile_off, const int* __restrict__ tile_s0,
     const int* __restrict__ off, const int* __restrict__ struct_of,
     const int4* __restrict__ pmeta, const float* __restrict__ pfrag,
@@ -623,7 +639,8 @@ __global__ __launch_bounds__(64 * kContractWaves) void k_pop_contract(
     const double* __restrict__ e_tar, const double* __restrict__ w_tar,
     const int* __restrict__ has_v, double* __restrict__ sq) {
   __shared__ int acc[kLdsInts];
-  __shared__ int esc[2][64];
+  __shared__ int esc[2][16 * kCols];
+  const int k0 = (int)blockIdx.y * kper, KC = min(kper, n_pop - k0), kcs = kper;
   const int t = tile_order[blockIdx.x];
   const int ta = tile_off[t], tb = tile_off[t + 1];
   const int s0 = tile_s0[t], s1 = tile_s0[t + 1];
@@ -667,7 +684,7 @@ __global__ __launch_bounds__(64 * kContractWaves) void k_pop_contract(
                            int pb, int P, int kl) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int dst = 16 * pb + 4 * h + r < P ? __float_as_int(e[r].w) : 0;
+      const int dst = 16 * pb + 4 * h + r < P ? __mul24(__float_as_int(e[r].w), kcs) : 0;
       int* fj = &Fq[dst + kl];
       float x = -e[r].x * v[r], y = -e[r].y * v[r], z = -e[r].z * v[r];
       if (ang) {
@@ -681,7 +698,7 @@ __global__ __launch_bounds__(64 * kContractWaves) void k_pop_contract(
     }
   };
 
-  auto process = [&](AtomOps& o, int4 m, int i, int sl) {
+  auto process = [&](AtomOps<kCols>& o, int4 m, int i, int sl) {
     const int il = i - ta;
     const int P = m.z, A = m.w;
     const int ns = radial_tiles(P), nab = (A + 15) / 16;
@@ -774,27 +791,27 @@ __global__ __launch_bounds__(64 * kContractWaves) void k_pop_contract(
     }
   };
 
-  // Phase 1: atoms ta + w, ta + w + kContractWaves, ...; all fragment
+  // Phase 1: atoms ta + w, ta + w + (waves), ...; all fragment
   // operands of an atom are requested before its first product (the other
   // waves on the SIMD cover the wait), its pair records just before the
   // products that use them
   // (the atom records are read with vector loads, threadIdx.y being 0: a
   // scalar load would have to wait for every LDS addition in flight)
-  for (int i = ta + w; i < tb; i += kContractWaves) {
+  for (int i = ta + w; i < tb; i += contract_waves(kCols)) {
     int4 m = pmeta[i + threadIdx.y];
     m.x = __builtin_amdgcn_readfirstlane(m.x);
     m.y = __builtin_amdgcn_readfirstlane(m.y);
     m.z = __builtin_amdgcn_readfirstlane(m.z);
     m.w = __builtin_amdgcn_readfirstlane(m.w);
     const int sl = __builtin_amdgcn_readfirstlane(struct_of[i + threadIdx.y] - s0);
-    AtomOps o;
+    AtomOps<kCols> o;
     fetch_atom(o, m, i, n_pop, dqk, pfrag, ppair, l, h);
     process(o, m, i, sl);
   }
   __syncthreads();
   // Phase 2: unit (structure s, individual kl), lanes over atoms
   const int n_units = (s1 - s0) * KC;
-  for (int u = w; u < n_units; u += kContractWaves) {
+  for (int u = w; u < n_units; u += contract_waves(kCols)) {
     const int s = s0 + u / KC, kl = u % KC, k = k0 + kl;
     const int i0 = off[s], i1 = off[s + 1];
     const int eF = esc[0][kl], eW = esc[1][kl];
@@ -844,11 +861,28 @@ template <int CT>
 void launch_net(nep_ctx ctx, nep_dataset ds, int n_pop, const float* Z, bool first) {
   launch_kernel(ctx, first, false, k_pop_wfrag, dim3(n_pop), dim3(64), ctx->n_par, Z,
                 ds->wfrag.ptr, ds->wb2.ptr, ds->dqbound.ptr);
-  const int per_block = 16 * CT * (kBlock / 64);
+  // small sets take shorter chunks, so that the chip gets kNetWaves waves (26 us
+  // for 20 individuals on 3,240 atoms in chunks of 10, 11 us in chunks of 1)
+  const int tiles = (int)blocks_for(ds->N, 16 * CT);
+  const int chunk = std::max(1, std::min(kNetChunk, (int)((long long)tiles * n_pop / kNetWaves)));
   launch_kernel(ctx, false, false, k_pop_net<CT>,
-                dim3(blocks_for(ds->N, per_block), (n_pop + kNetChunk - 1) / kNetChunk),
-                dim3(kBlock), ds->N, n_pop, (const float*)ds->qpad.ptr,
+                dim3(blocks_for(ds->N, 16 * CT * (kBlock / 64)), (n_pop + chunk - 1) / chunk),
+                dim3(kBlock), ds->N, n_pop, chunk, (const float*)ds->qpad.ptr,
                 (const float4*)ds->wfrag.ptr, (const float*)ds->wb2.ptr, ds->dq.ptr, ds->U.ptr);
+}
+
+template <int kCols>
+void launch_contract(nep_ctx ctx, nep_dataset ds, int n_pop, int kper) {
+  launch_kernel(ctx, false, false, k_pop_contract<kCols>,
+                dim3(ds->n_tiles, (n_pop + kper - 1) / kper), dim3(64 * contract_waves(kCols)), ds->N,
+                ds->S, kper, n_pop, (const int*)ds->tile_order.ptr, (const int*)ds->tile_off.ptr,
+                (const int*)ds->tile_s0.ptr, (const int*)ds->off.ptr,
+                (const int*)ds->struct_of.ptr, (const int4*)ds->pmeta.ptr,
+                (const float*)ds->pfrag.ptr, (const float4*)ds->ppair.ptr,
+                (const float*)ds->dq.ptr, (const float*)ds->U.ptr, (const float2*)ds->tbound.ptr,
+                (const float*)ds->dqbound.ptr, (const double*)ds->f_tar.ptr,
+                (const double*)ds->e_tar.ptr, (const double*)ds->w_tar.ptr,
+                (const int*)ds->has_v.ptr, ds->struct_sq.ptr);
 }
 
 }  // namespace
@@ -964,7 +998,7 @@ hipError_t prepare_dataset_geometry(nep_ctx ctx, nep_dataset ds) {
     e = hipMemsetAsync(ds->ppair.ptr + pairs, 0, sizeof(float4) * kPadPairs, st);
   if (e != hipSuccess) return e;
   k_pop_geo<<<blocks_for((size_t)N * 32, kBlock), kBlock, 0, st>>>(
-      N, tile_kc, ds->prec.ptr, ds->pmeta.ptr, ds->desc.ptr, ds->struct_of.ptr, ds->stile0.ptr, rcr, rca,
+      N, ds->prec.ptr, ds->pmeta.ptr, ds->desc.ptr, ds->struct_of.ptr, ds->stile0.ptr, rcr, rca,
       ds->pfrag.ptr, ds->ppair.ptr);
   k_pop_norms<<<blocks_for(N, 64), 64, 0, st>>>(N, ds->pmeta.ptr, ds->pfrag.ptr, ds->pnorm.ptr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1009,18 +1043,33 @@ hipError_t launch_population(nep_ctx ctx, nep_dataset ds, int n_pop, const float
     default:
       launch_net<2>(ctx, ds, n_pop, Z, first);
   }
-  for (int k0 = 0; k0 < n_pop; k0 += KC)
-    launch_kernel(ctx, false, false, k_pop_contract, dim3(ds->n_tiles),
-                  dim3(64 * kContractWaves), ds->N, ds->S, k0, std::min(KC, n_pop - k0), KC, n_pop,
-                  (const int*)ds->tile_order.ptr, (const int*)ds->tile_off.ptr,
-                  (const int*)ds->tile_s0.ptr, (const int*)ds->off.ptr,
-                  (const int*)ds->struct_of.ptr, (const int4*)ds->pmeta.ptr,
-                  (const float*)ds->pfrag.ptr, (const float4*)ds->ppair.ptr,
-                  (const float*)ds->dq.ptr, (const float*)ds->U.ptr,
-                  (const float2*)ds->tbound.ptr, (const float*)ds->dqbound.ptr,
-                  (const double*)ds->f_tar.ptr,
-                  (const double*)ds->e_tar.ptr, (const double*)ds->w_tar.ptr,
-                  (const int*)ds->has_v.ptr, ds->struct_sq.ptr);
+  // Individuals per block, all groups alike: as many as fit the LDS (at most 64)
+  // when the tiles alone fill the chip, since a block reads its tile's fragments
+  // once for all of them; at most 32 or 16 while there are so few tiles that the
+  // smaller blocks still run in two rounds or one over the 256 compute units.
+  // 50 individuals, tiles x (blocks of 50 / 25 / 16), us per evaluation: 60 x 233 /
+  // 153 / 119, 120 x 256 / 173 / 181, 250 x 311 / 249 / 303, 500 x 446 / 511 / 660.
+  auto blocks = [&](int per) { return (long long)ds->n_tiles * ((n_pop + per - 1) / per); };
+  int per = std::min(KC, 64);
+  if (blocks(16) <= 256)
+    per = std::min(KC, 16);
+  else if (blocks(32) <= 512)
+    per = std::min(KC, 32);
+  const int groups = (n_pop + per - 1) / per;
+  per = (n_pop + groups - 1) / groups;
+  switch ((per + 15) / 16) {
+    case 1:
+      launch_contract<1>(ctx, ds, n_pop, per);
+      break;
+    case 2:
+      launch_contract<2>(ctx, ds, n_pop, per);
+      break;
+    case 3:
+      launch_contract<3>(ctx, ds, n_pop, per);
+      break;
+    default:
+      launch_contract<4>(ctx, ds, n_pop, per);
+  }
   return hipGetLastError();
 }
 
