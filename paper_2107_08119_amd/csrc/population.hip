@@ -194,9 +194,10 @@ __host__ __device__ inline int atom_chunks(int pairs, int ang) {
   return kGSteps + kSSteps * radial_tiles(pairs) + kASteps * angular_tiles(ang);
 }
 
-// Fixed-point accumulators of a tile in LDS (at most 162,816 bytes): forces
-// [atom][3][KC] and structure virials [structure][9][KC], 32-bit integers.
-constexpr int kLdsInts = 40704;
+// Fixed-point accumulators of a tile in LDS (162,816 bytes), 32-bit integers:
+// three planes x, y, z of [unit][KC], a unit being an atom (its force) or one of
+// the three rows that plane a holds of a structure's virial (components ab).
+constexpr int kPlane = 13568, kLdsInts = 3 * kPlane;
 constexpr int kTileTarget = 64;
 
 // Memory order of dU/dq within an (atom, individual) row of 32: padded
@@ -225,7 +226,7 @@ __global__ void k_pop_qpad(int N, const float* __restrict__ desc, float* __restr
 // One thread per (atom i, descriptor component nu < 29): D_ij[.][nu] for
 // every pair of i, written into i's radial or angular fragment chunks, and
 // row nu of G_i and V_i.  The thread of nu = 0 also writes the pair records
-// (r_ij/r_ij, 3 times the receiver's index in the tile).  pfrag must be zero
+// (r_ij/r_ij, the receiver's index in the tile).  pfrag must be zero
 // before.
 __global__ __launch_bounds__(kBlock) void k_pop_geo(
     int N, const float4* __restrict__ rec, const int4* __restrict__ pmeta,
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(kBlock) void k_pop_geo(
       if (v == 0) {
         const int j = (int)((unsigned)__float_as_int(e.w) % (unsigned)N);
         ppair[(size_t)m.y + p] =
-            make_float4(e.x * rinv, e.y * rinv, e.z * rinv, __int_as_float((j - t0) * 3));
+            make_float4(e.x * rinv, e.y * rinv, e.z * rinv, __int_as_float(j - t0));
       }
     }
   } else {
@@ -391,7 +392,7 @@ __global__ __launch_bounds__(64) void k_pop_wfrag(int n_par, const float* __rest
 // left the last round of waves mostly empty).
 // Bound: the matrix cores (85 us of 16x16x4 steps per 50 individuals of 65,600
 // atoms) and the store of dU/dq (128 bytes per individual and atom), overlapped
-// by the waves of a SIMD: with three of them 32 atoms per wave take 445 us per
+// by the waves of a SIMD: with three of them 32 atoms per wave take 440 us per
 // evaluation with the contraction, with two 455 us.
 constexpr int kNetChunk = 10;
 constexpr int kNetWaves = 4096;  // four per SIMD
@@ -399,12 +400,8 @@ constexpr int kNetWaves = 4096;  // four per SIMD
 template <int CT>
 __global__ __launch_bounds__(kBlock)
     __attribute__((amdgpu_waves_per_eu(CT == 1 ? 4 : (CT == 2 ? 3 : 2)))) void k_pop_net(
-    int N, int n_pop, int chunk,
-                                                    const float* __restrict__ qpad,
-                                                    const float4* __restrict__ wf,
-                                                    const float* __restrict__ wb2,
-                                                    float* __restrict__ dq,
-                                                    float* __restrict__ U) {
+    int N, int n_pop, int chunk, const float* __restrict__ qpad, const float4* __restrict__ wf,
+    const float* __restrict__ wb2, float* __restrict__ dq, float* __restrict__ U) {
   const int l = threadIdx.x & 63, col = l & 15, h = l >> 4;
   const int a0 = (blockIdx.x * (kBlock / 64) + threadIdx.x / 64) * 16 * CT;
   if (a0 >= N) return;  // whole waves leave together
@@ -615,18 +612,19 @@ __device__ __forceinline__ void fetch_atom(AtomOps<kCols>& o, int4 m, int i, int
 // Phase 1: the waves take the tile's atoms in turn; for each atom and each
 // column tile of 16 individuals they multiply the atom's operands by dU/dq
 // and add every product element, as round(x 2^e) with the tile's exponent e
-// of the individual, into 32-bit LDS accumulators of forces [atom][3][KC]
-// and structure virials [structure][9][KC].  Integer sums do not depend on
+// of the individual, into 32-bit LDS accumulators: of the forces, a unit per atom,
+// and of the structure virials.  Integer sums do not depend on
 // their order, so results are the same for any schedule.
-// Phase 2: one unit per (structure, individual): lanes over the atoms form
-// the energy, force and virial errors in float64 in a fixed order.
+// Phase 2: one unit per structure and a few individuals: lanes over the atoms
+// form the energy, force and virial errors in float64 in a fixed order (one
+// individual at a time took 25 us of 440 for 50 on 500 structures).
 // Bound: on large sets the matrix cores, the LDS additions and the read of the
 // fragments, with three or four waves per SIMD to cover the fetch of an atom's
 // operands; on small sets the chain of one wave's atoms, which launch_population
 // shortens by splitting the individuals over more blocks.  The column tiles are
 // a constant of the kernel: a branch around those past KC takes the overlap of
 // their products away (213 against 179 us for 50 individuals on 120 structures).
-constexpr int contract_waves(int cols) { return cols > 2 ? 12 : 16; }
+constexpr int contract_waves(int cols) { return cols > 1 ? 12 : 16; }
 template <int kCols>
 __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
     int N, int S, int kper, int n_pop, const int* __restrict__ tile_order,
@@ -644,10 +642,9 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
   const int t = tile_order[blockIdx.x];
   const int ta = tile_off[t], tb = tile_off[t + 1];
   const int s0 = tile_s0[t], s1 = tile_s0[t + 1];
-  int* Fq = acc;                          // [atom][3][kcs]
-  int* Wq = acc + (tb - ta) * 3 * kcs;    // [structure][9][kcs]
-  const int n_acc = ((tb - ta) * 3 + (s1 - s0) * 9) * kcs;
-  for (int x = threadIdx.x; x < n_acc; x += blockDim.x) acc[x] = 0;
+  const int n_acc = ((tb - ta) + (s1 - s0) * 3) * kcs;  // of each plane
+  for (int x = threadIdx.x; x < n_acc; x += blockDim.x)
+    acc[x] = acc[kPlane + x] = acc[2 * kPlane + x] = 0;
   if (threadIdx.x < KC) {
     const float2 tb2 = tbound[t];
     const float bk = dqbound[k0 + threadIdx.x];
@@ -677,24 +674,31 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
 
   // the pair block pb of atom i: radial tile v (rows: pairs) and, when the
   // block holds angular pairs, angular tiles ax, ay, az (same rows);
-  // F_j -= u_ij v + (ax, ay, az) for the receiver j of each row.  Rows past
-  // the atom's pairs have zero operands (their products are 0) and go to the
-  // tile's first accumulator, so no lane branches.
-  auto scatter_block = [&](const f32x4& v, const f32x4* va, bool ang, const float4 (&e)[4],
-                           int pb, int P, int kl) {
+  // F_j -= u_ij v + (ax, ay, az) for the receiver j of each row, at pxy[r] in
+  // planes x and y and pz[r] in plane z (an LDS address reaches 64 KB ahead).
+  // Rows past the atom's pairs have zero operands: they add 0, to 64 different
+  // banks, so no lane branches.
+  auto receivers = [&](const float4 (&e)[4], int pb, int P, int* (&pxy)[4], int* (&pz)[4]) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int dst = 16 * pb + 4 * h + r < P ? __mul24(__float_as_int(e[r].w), kcs) : 0;
-      int* fj = &Fq[dst + kl];
+      const int p = 16 * pb + 4 * h + r;
+      pxy[r] = acc + ((p < P ? __mul24(__float_as_int(e[r].w), kcs) : 16 * h) + col);
+      pz[r] = pxy[r] + 2 * kPlane;
+    }
+  };
+  auto scatter_block = [&](const f32x4& v, const f32x4* va, bool ang, const float4 (&e)[4],
+                           int* const (&pxy)[4], int* const (&pz)[4], int c) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
       float x = -e[r].x * v[r], y = -e[r].y * v[r], z = -e[r].z * v[r];
       if (ang) {
         x -= va[0][r];
         y -= va[1][r];
         z -= va[2][r];
       }
-      add_q(fj, x);
-      add_q(fj + kcs, y);
-      add_q(fj + 2 * kcs, z);
+      add_q(pxy[r] + 16 * c, x);
+      add_q(pxy[r] + kPlane + 16 * c, y);
+      add_q(pz[r] + 16 * c, z);
     }
   };
 
@@ -708,12 +712,13 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
       for (int q = 0; q < 8; ++q) o.b[c][q] *= sF[c];
     // the lane's rows 4 h + r of the own-force / virial tile: rows 0..2 the
     // own force, 3..11 the virial (row-major ab), 12..15 zero
-    int gdst[4];
+    int* gdst[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int row = 4 * h + r;
-      gdst[r] = row < 3 ? (il * 3 + row) * kcs
-                        : (row < 12 ? (int)(Wq - Fq) + (sl * 9 + row - 3) * kcs : il * 3 * kcs);
+      const int row = 4 * h + r, ab = row - 3;
+      const int unit = row < 3 || row > 11 ? il : (tb - ta) + 3 * sl + ab % 3;
+      const int plane = row < 3 ? row : (row > 11 ? 0 : ab / 3);
+      gdst[r] = acc + (plane * kPlane + unit * kcs + col);
     }
 #pragma unroll
     for (int c = 0; c < kCols; ++c) {
@@ -721,10 +726,9 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
 #pragma unroll
       for (int q = 0; q < kGSteps; ++q) g = mma(o.g[q], o.b[c][q], g);
       if (!valid[c]) continue;
-      const int kl = 16 * c + col;
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        add_q(&Fq[gdst[r] + kl], 4 * h + r < 3 ? g[r] : g[r] * rW[c]);
+        add_q(gdst[r] + 16 * c, 4 * h + r < 3 ? g[r] : g[r] * rW[c]);
     }
     if (fast_atom(m)) {
 #pragma unroll
@@ -734,6 +738,8 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
         float4 e[4];  // the rows' pair records, read while the products run
 #pragma unroll
         for (int r = 0; r < 4; ++r) e[r] = ppair[(size_t)m.y + 16 * pb + 4 * h + r];
+        int *pxy[4], *pz[4];
+        receivers(e, pb, P, pxy, pz);
 #pragma unroll
         for (int c = 0; c < kCols; ++c) {
           f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -748,7 +754,7 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
               for (int q = 0; q < kASteps; ++q) va[d] = mma(o.a[d][q], o.b[c][3 + q], va[d]);
             }
           }
-          if (valid[c]) scatter_block(v, va, ang, e, pb, P, 16 * c + col);
+          if (valid[c]) scatter_block(v, va, ang, e, pxy, pz, c);
         }
       }
       return;
@@ -772,6 +778,8 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
         const int p = 16 * pb + 4 * h + r;
         e[r] = ppair[(size_t)m.y + (p < P ? p : 0)];
       }
+      int *pxy[4], *pz[4];
+      receivers(e, pb, P, pxy, pz);
 #pragma unroll
       for (int c = 0; c < kCols; ++c) {
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
@@ -786,7 +794,7 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
             for (int q = 0; q < kASteps; ++q) va[x] = mma(da[x][q], o.b[c][3 + q], va[x]);
           }
         }
-        if (valid[c]) scatter_block(v, va, ang, e, pb, P, 16 * c + col);
+        if (valid[c]) scatter_block(v, va, ang, e, pxy, pz, c);
       }
     }
   };
@@ -795,64 +803,95 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
   // operands of an atom are requested before its first product (the other
   // waves on the SIMD cover the wait), its pair records just before the
   // products that use them
-  // (the atom records are read with vector loads, threadIdx.y being 0: a
+  // (the atom records are read one atom ahead, with vector loads, threadIdx.y being 0: a
   // scalar load would have to wait for every LDS addition in flight)
+  const int first = min(ta + w, tb - 1) + threadIdx.y;
+  int4 ahead = pmeta[first];
+  int s_ahead = struct_of[first];
   for (int i = ta + w; i < tb; i += contract_waves(kCols)) {
-    int4 m = pmeta[i + threadIdx.y];
-    m.x = __builtin_amdgcn_readfirstlane(m.x);
-    m.y = __builtin_amdgcn_readfirstlane(m.y);
-    m.z = __builtin_amdgcn_readfirstlane(m.z);
-    m.w = __builtin_amdgcn_readfirstlane(m.w);
-    const int sl = __builtin_amdgcn_readfirstlane(struct_of[i + threadIdx.y] - s0);
+    int4 m;
+    m.x = __builtin_amdgcn_readfirstlane(ahead.x);
+    m.y = __builtin_amdgcn_readfirstlane(ahead.y);
+    m.z = __builtin_amdgcn_readfirstlane(ahead.z);
+    m.w = __builtin_amdgcn_readfirstlane(ahead.w);
+    const int sl = __builtin_amdgcn_readfirstlane(s_ahead) - s0;
+    const int next = min(i + contract_waves(kCols), tb - 1) + threadIdx.y;
+    ahead = pmeta[next];
+    s_ahead = struct_of[next];
     AtomOps<kCols> o;
     fetch_atom(o, m, i, n_pop, dqk, pfrag, ppair, l, h);
     process(o, m, i, sl);
   }
   __syncthreads();
-  // Phase 2: unit (structure s, individual kl), lanes over atoms
-  const int n_units = (s1 - s0) * KC;
-  for (int u = w; u < n_units; u += contract_waves(kCols)) {
-    const int s = s0 + u / KC, kl = u % KC, k = k0 + kl;
+  // Phase 2: unit (structure s, kUnit individuals from kl0), lanes over atoms;
+  // kUnit individuals at a time share the targets and overlap their sums
+  constexpr int W = contract_waves(kCols), kUnit = (16 * kCols + W - 1) / W;
+  const int groups = (KC + kUnit - 1) / kUnit;
+  for (int u = w; u < (s1 - s0) * groups; u += W) {
+    const int s = s0 + u / groups, kl0 = u % groups * kUnit;
     const int i0 = off[s], i1 = off[s + 1];
-    const int eF = esc[0][kl], eW = esc[1][kl];
-    const double iF = eF == kBadScale ? 0.0 : ldexp(1.0, -eF);
-    const double iW = eW == kBadScale ? 0.0 : ldexp(1.0, -eW);
-    double eu = 0.0, ef = 0.0;
-    for (int i = i0 + l; i < i1; i += 64) {
-      eu += (double)U[(size_t)k * N + i];
-      const int il = i - ta;
+    int kl[kUnit];
+    double iF[kUnit], eu[kUnit], ef[kUnit];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const double d = (double)Fq[(il * 3 + c) * kcs + kl] * iF - f_tar[(size_t)c * N + i];
-        ef += d * d;
+    for (int q = 0; q < kUnit; ++q) {
+      kl[q] = min(kl0 + q, KC - 1);  // past KC: the last one again, not stored
+      const int eF = esc[0][kl[q]];
+      iF[q] = eF == kBadScale ? 0.0 : ldexp(1.0, -eF);
+      eu[q] = ef[q] = 0.0;
+    }
+    for (int i = i0 + l; i < i1; i += 64) {
+      const int il = i - ta;
+      double t[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) t[c] = f_tar[(size_t)c * N + i];
+#pragma unroll
+      for (int q = 0; q < kUnit; ++q) {
+        eu[q] += (double)U[(size_t)(k0 + kl[q]) * N + i];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const double d = (double)acc[c * kPlane + il * kcs + kl[q]] * iF[q] - t[c];
+          ef[q] += d * d;
+        }
       }
     }
     for (int d = 32; d > 0; d >>= 1) {
-      eu += __shfl_xor(eu, d, 64);
-      ef += __shfl_xor(ef, d, 64);
+#pragma unroll
+      for (int q = 0; q < kUnit; ++q) {
+        eu[q] += __shfl_xor(eu[q], d, 64);
+        ef[q] += __shfl_xor(ef[q], d, 64);
+      }
     }
-    if (l == 0) {
-      const double ns_inv = 1.0 / (double)(i1 - i0);
-      double ev = 0.0;
-      if (has_v[s]) {
-        // targets xx yy zz xy yz zx = row-major components 0, 4, 8, 1, 5, 6
-        const int comp[6] = {0, 4, 8, 1, 5, 6};
-        for (int c = 0; c < 6; ++c) {
-          const double d =
-              ((double)Wq[((s - s0) * 9 + comp[c]) * kcs + kl] * iW - w_tar[6 * (size_t)s + c]) *
-              ns_inv;
-          ev += d * d;
-        }
+    const int k = kl0 + l;  // lane q stores individual kl0 + q
+    if (l >= kUnit || k >= KC) continue;
+    double su = eu[0], sf = ef[0];
+#pragma unroll
+    for (int q = 1; q < kUnit; ++q) {
+      su = l == q ? eu[q] : su;
+      sf = l == q ? ef[q] : sf;
+    }
+    const int eF = esc[0][k], eW = esc[1][k];
+    const double iW = eW == kBadScale ? 0.0 : ldexp(1.0, -eW);
+    const double ns_inv = 1.0 / (double)(i1 - i0);
+    double ev = 0.0;
+    if (has_v[s]) {
+      // targets xx yy zz xy yz zx = components ab, plane a, row b
+      const int pl[6] = {0, 1, 2, 0, 1, 2}, pb[6] = {0, 1, 2, 1, 2, 0};
+      for (int c = 0; c < 6; ++c) {
+        const double d =
+            ((double)acc[pl[c] * kPlane + ((tb - ta) + 3 * (s - s0) + pb[c]) * kcs + k] * iW -
+             w_tar[6 * (size_t)s + c]) *
+            ns_inv;
+        ev += d * d;
       }
-      const double de = (eu - e_tar[s]) * ns_inv;
-      double* o = sq + ((size_t)k * S + s) * 3;
-      if (eF == kBadScale || eW == kBadScale) {
-        o[0] = o[1] = o[2] = __builtin_nan("");
-      } else {
-        o[0] = de * de;
-        o[1] = ef;
-        o[2] = ev;
-      }
+    }
+    const double de = (su - e_tar[s]) * ns_inv;
+    double* o = sq + ((size_t)(k0 + k) * S + s) * 3;
+    if (eF == kBadScale || eW == kBadScale) {
+      o[0] = o[1] = o[2] = __builtin_nan("");
+    } else {
+      o[0] = de * de;
+      o[1] = sf;
+      o[2] = ev;
     }
   }
 }
