@@ -419,6 +419,12 @@ nep_status nep_dataset_backward(nep_ctx ctx, nep_dataset ds, const float* z_dev,
                                 const float* forces_dev, double* grad_pos_dev,
                                 double* grad_z_dev, float* grad_z32_dev);
 
+/* The position gradient of nep_dataset_backward alone: grad_pos_dev
+ * [3][sum N] (float64) = -gE_s F_i, with gE_dev NULL for zero and forces_dev
+ * from nep_dataset_compute. */
+nep_status nep_dataset_position_gradient(nep_ctx ctx, nep_dataset ds, const double* gE_dev,
+                                         const float* forces_dev, double* grad_pos_dev);
+
 /* ----------------------------------------------------------- measurement */
 
 /* Kernel timing for benchmarks.  While enabled, every launch of the force

@@ -338,7 +338,26 @@ __global__ __launch_bounds__(1024) void k_grad_final(int nblocks, const float* _
   if (grad32) grad32[p] = (float)s;
 }
 
+// gpos[c][i] = -gE F of the atom's structure, 0 without gE.
+__global__ __launch_bounds__(kBlock) void k_position_gradient(
+    int n, const int* __restrict__ struct_of, const double* __restrict__ gE,
+    const float* __restrict__ F, double* __restrict__ gpos) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const double g = gE ? -gE[struct_of[i]] : 0.0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    gpos[(size_t)c * n + i] = gE ? g * (double)F[(size_t)c * n + i] : 0.0;
+}
+
 }  // namespace
+
+hipError_t launch_position_gradient(nep_ctx ctx, nep_dataset ds, const double* gE, const float* F,
+                                    double* gpos) {
+  launch_kernel(ctx, true, true, k_position_gradient, dim3(blocks_for(ds->N, kBlock)),
+                dim3(kBlock), ds->N, (const int*)ds->struct_of.ptr, gE, F, gpos);
+  return hipGetLastError();
+}
 
 hipError_t launch_backward(nep_ctx ctx, nep_dataset ds, const float* z, const double* gE,
                            const float* gF, const float* F, double* gpos, double* grad,

@@ -706,6 +706,8 @@ __global__ __launch_bounds__(64 * kImageWaves) void k_build_all_pairs(
 // j > i also writes the reverse slot of the entry it finds, and entries with
 // j < i are left to that thread; after an overflow every entry searches for
 // itself, so that every reverse slot still names a slot inside j's list.
+// Where totals is given it also receives the sums of n_in and n_ang (whole
+// numbers: any order).
 // One block per kReverseAtoms consecutive atoms (all their slots), blocks
 // spread over the XCDs in contiguous ranges: a pair's partner row is then
 // mostly a nearby atom's, already in the XCD's L2.
@@ -713,10 +715,24 @@ constexpr int kReverseAtoms = 32;
 __global__ __launch_bounds__(kBlock) void k_reverse(int n, int cap, const uint32_t* __restrict__ nl,
                           const uint32_t* __restrict__ nl_rm, const int* __restrict__ cnt_r,
                           const int* __restrict__ cnt_a, int* __restrict__ rev,
-                          int* __restrict__ flags) {
+                          int* __restrict__ flags, const int* __restrict__ n_in,
+                          const int* __restrict__ n_ang,
+                          unsigned long long* __restrict__ totals) {
   // thread (s0, i) handles slots s0, s0 + width, ... of atom i
   constexpr int width = kBlock / kReverseAtoms;
   const int i = (int)xcd_block(blockIdx.x, gridDim.x) * kReverseAtoms + threadIdx.x % kReverseAtoms;
+  if (totals && threadIdx.x < 64) {  // the block's atoms in the first kReverseAtoms lanes
+    const bool own = threadIdx.x < kReverseAtoms && i < n;
+    int in = own ? n_in[i] : 0, ang = own ? n_ang[i] : 0;
+    for (int d = kReverseAtoms / 2; d > 0; d >>= 1) {
+      in += __shfl_xor(in, d, 64);
+      ang += __shfl_xor(ang, d, 64);
+    }
+    if (threadIdx.x == 0) {
+      atomicAdd(&totals[0], (unsigned long long)in);
+      atomicAdd(&totals[1], (unsigned long long)ang);
+    }
+  }
   if (i >= n) return;
   const int cr = cnt_r[i], ca = cnt_a[i];
   const bool symmetric = flags[kFlagOverflow] == 0;
@@ -834,12 +850,13 @@ inline unsigned blocks_for(size_t work, int block) { return (unsigned)((work + b
 }  // namespace
 
 void launch_reverse(nep_ctx ctx, int n, int cap, const uint32_t* nl, const uint32_t* nl_rm,
-                    const int* cnt_r, const int* cnt_a, int* rev) {
+                    const int* cnt_r, const int* cnt_a, int* rev, const int* n_in,
+                    const int* n_ang, unsigned long long* totals) {
   const size_t ncap = (size_t)n * cap;
   if (ncap == 0) return;
   launch_kernel(ctx, false, false, k_reverse, dim3(blocks_for((size_t)n, kReverseAtoms)),
-                dim3(kBlock), n, cap, nl, nl_rm, cnt_r, cnt_a, rev,
-                ctx->flags.ptr);
+                dim3(kBlock), n, cap, nl, nl_rm, cnt_r, cnt_a, rev, ctx->flags.ptr, n_in, n_ang,
+                totals);
 }
 
 hipError_t unpack_neighbors(nep_ctx ctx, int* nbr, int* img, int* cnt_r, int* cnt_a, int* rev) {
@@ -1005,7 +1022,8 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const
   launch_kernel(ctx, false, true, k_reverse, dim3(blocks_for((size_t)n, kReverseAtoms)), blk, n,
                 s.cap, (const uint32_t*)s.nl.ptr,
                 (const uint32_t*)s.nl_rm.ptr,
-                (const int*)s.cnt_r.ptr, (const int*)s.cnt_a.ptr, s.rev.ptr, ctx->flags.ptr);
+                (const int*)s.cnt_r.ptr, (const int*)s.cnt_a.ptr, s.rev.ptr, ctx->flags.ptr, (const int*)nullptr, (const int*)nullptr,
+                (unsigned long long*)nullptr);
   return check_hip(ctx, hipGetLastError(), "launching neighbour kernels");
 }
 

@@ -75,9 +75,10 @@ hipError_t evaluate_internal(nep_ctx ctx, bool vel, int mode, double kick, doubl
 
 nep_status synchronize_flags(nep_ctx ctx, unsigned long long* pairs) {
   DeviceGuard guard(ctx->device);
-  int h[kFlagWords];
+  const int* h = ctx->flags_host;
   nep_status st = check_hip(ctx,
-                            hipMemcpyAsync(h, ctx->flags.ptr, sizeof(h), hipMemcpyDeviceToHost,
+                            hipMemcpyAsync(ctx->flags_host, ctx->flags.ptr,
+                                           sizeof(int) * kFlagWords, hipMemcpyDeviceToHost,
                                            ctx->stream),
                             "reading device flags");
   if (st != NEP_OK) return st;
@@ -134,7 +135,8 @@ nep_status nep_create(nep_ctx* out, int device, void* hip_stream) {
   ctx->stream = (hipStream_t)hip_stream;
   hipError_t e;
   if ((e = ctx->flags.ensure(kFlagWords)) != hipSuccess || (e = ctx->totals.ensure(16)) != hipSuccess ||
-      (e = hipMemset(ctx->flags.ptr, 0, sizeof(int) * kFlagWords)) != hipSuccess) {
+      (e = hipMemset(ctx->flags.ptr, 0, sizeof(int) * kFlagWords)) != hipSuccess ||
+      (e = hipHostMalloc((void**)&ctx->flags_host, sizeof(int) * kFlagWords)) != hipSuccess) {
     nep_destroy(ctx);
     return e == hipErrorOutOfMemory ? NEP_ENOMEM : NEP_EDEVICE;
   }
@@ -161,6 +163,7 @@ void nep_destroy(nep_ctx ctx) {
   ctx->partials.release();
   ctx->totals.release();
   ctx->flags.release();
+  if (ctx->flags_host) (void)hipHostFree(ctx->flags_host);
   ctx->snes_graph.release();
   ctx->gen_counter.release();
   delete ctx;

@@ -244,6 +244,7 @@ struct nep_ctx_s {
   nep::DevBuf<double> masses;     // [n] amu
   nep::DevBuf<double> totals;     // [16]
   nep::DevBuf<int> flags;         // [kFlagWords]: kNumFlags flags, two 64-bit pair totals
+  int* flags_host = nullptr;      // [kFlagWords], pinned: their copy at a synchronization
   // molecular dynamics state
   bool md_forces_valid = false;
   const double* md_pos = nullptr;
@@ -379,7 +380,8 @@ hipError_t unpack_neighbors(nep_ctx ctx, int* nbr, int* img, int* cnt_r, int* cn
 // Reverse slots of a list (any system, global atom indices).
 // nl_rm: the same entries per atom, [n][cap].
 void launch_reverse(nep_ctx ctx, int n, int cap, const uint32_t* nl, const uint32_t* nl_rm,
-                    const int* cnt_r, const int* cnt_a, int* rev);
+                    const int* cnt_r, const int* cnt_a, int* rev, const int* n_in = nullptr,
+                    const int* n_ang = nullptr, unsigned long long* totals = nullptr);
 
 // force.hip
 bool have_force_variant(const nep_hyper& h);
@@ -423,6 +425,8 @@ hipError_t launch_partials_population(nep_ctx ctx, nep_dataset ds, int n_pop, co
 hipError_t launch_backward(nep_ctx ctx, nep_dataset ds, const float* z, const double* gE,
                            const float* gF, const float* F, double* gpos, double* grad,
                            float* grad32);
+hipError_t launch_position_gradient(nep_ctx ctx, nep_dataset ds, const double* gE, const float* F,
+                                    double* gpos);
 
 // Launch a kernel on the context's stream.  When a timed kernel class is
 // being launched, its first kernel carries the start event and its last

@@ -29,16 +29,17 @@ constexpr int kLanes = 4;  // lanes per atom in the population gather (as in pas
 
 // ------------------------------------------------------- dataset lists
 
-// Wrap every position into its structure's cell; record the integer offsets
-// that remain after rounding (normally zero).
-__global__ void k_ds_wrap(int N, double* __restrict__ pos, const double* __restrict__ boxes,
+// pos = src (which may be pos) with every position wrapped into its structure's
+// cell; the integer offsets that remain after rounding (normally zero) go to
+// wrap.
+__global__ void k_ds_wrap(int N, const double* src, double* pos, const double* __restrict__ boxes,
                           const double* __restrict__ boxinv, const int* __restrict__ struct_of,
                           int* __restrict__ wrap) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= N) return;
   const double* H = boxes + 9 * (size_t)struct_of[i];
   const double* Hi = boxinv + 9 * (size_t)struct_of[i];
-  double r[3] = {pos[i], pos[N + i], pos[2 * N + i]};
+  double r[3] = {src[i], src[N + i], src[2 * N + i]};
   int w[3];
   for (int a = 0; a < 3; ++a) w[a] = (int)floor(r[0] * Hi[a] + r[1] * Hi[3 + a] + r[2] * Hi[6 + a]);
   for (int c = 0; c < 3; ++c) {
@@ -82,25 +83,6 @@ __global__ __launch_bounds__(64 * kImageWaves) void k_ds_build(
   }
   if (l.overflow) flags[kFlagOverflow] = 1;
   if (l.bad_image) flags[kFlagImage] = 1;
-}
-
-// totals += the sums of n_in and n_ang (whole numbers: any order).
-__global__ __launch_bounds__(kBlock) void k_ds_pair_totals(int N, const int* __restrict__ n_in,
-                                                           const int* __restrict__ n_ang,
-                                                           unsigned long long* __restrict__ totals) {
-  unsigned long long a = 0, b = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < N; i += gridDim.x * blockDim.x) {
-    a += (unsigned long long)n_in[i];
-    b += (unsigned long long)n_ang[i];
-  }
-  for (int d = 32; d > 0; d >>= 1) {
-    a += __shfl_xor(a, d, 64);
-    b += __shfl_xor(b, d, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    atomicAdd(&totals[0], a);
-    atomicAdd(&totals[1], b);
-  }
 }
 
 // ------------------------------------------------- population loss terms
@@ -385,7 +367,7 @@ void invert_box(const double* H, double* Hi) {
 // Wrap the dataset's positions and build its lists and reverse slots.  The
 // row-major list copy of the reverse search lies in pcidx, which the geometry
 // cache fills afterwards.
-hipError_t build_dataset_lists(nep_ctx ctx, nep_dataset ds) {
+hipError_t build_dataset_lists(nep_ctx ctx, nep_dataset ds, const double* pos) {
   const int N = ds->N;
   hipStream_t st = ctx->stream;
   hipError_t e = ds->pcidx.ensure((size_t)N * ds->cap);
@@ -394,7 +376,7 @@ hipError_t build_dataset_lists(nep_ctx ctx, nep_dataset ds) {
   if (e != hipSuccess) return e;
   const float rca = (float)ds->rc_a, rcr = (float)ds->rc_r;
   uint32_t* nl_rm = reinterpret_cast<uint32_t*>(ds->pcidx.ptr);
-  k_ds_wrap<<<blocks_for(N, kBlock), kBlock, 0, st>>>(N, ds->pos.ptr, ds->boxes.ptr,
+  k_ds_wrap<<<blocks_for(N, kBlock), kBlock, 0, st>>>(N, pos, ds->pos.ptr, ds->boxes.ptr,
                                                       ds->boxinv.ptr, ds->struct_of.ptr,
                                                       ds->wrap.ptr);
   const int waves = image_waves(N);
@@ -403,7 +385,8 @@ hipError_t build_dataset_lists(nep_ctx ctx, nep_dataset ds) {
       ds->kimg.ptr, ds->wrap.ptr, ds->rc_r * ds->rc_r, ds->rc_a * ds->rc_a, rcr * rcr, rca * rca,
       ds->nl.ptr, nl_rm, ds->cnt_r.ptr, ds->cnt_a.ptr, ds->pn_in.ptr, ds->pn_ang.ptr,
       pair_totals(ctx), ctx->flags.ptr);
-  launch_reverse(ctx, N, ds->cap, ds->nl.ptr, nl_rm, ds->cnt_r.ptr, ds->cnt_a.ptr, ds->rev.ptr);
+  launch_reverse(ctx, N, ds->cap, ds->nl.ptr, nl_rm, ds->cnt_r.ptr, ds->cnt_a.ptr, ds->rev.ptr,
+                 ds->pn_in.ptr, ds->pn_ang.ptr, pair_totals(ctx));
   ds->geometry_stale = true;
   return hipGetLastError();
 }
@@ -560,7 +543,7 @@ nep_status nep_dataset_create(nep_ctx ctx, int n_struct, const int* n_atoms_host
   up(ds->f_tar.ptr, ftT.data(), sizeof(double) * 3 * N);
   up(ds->w_tar.ptr, virial_host, sizeof(double) * 6 * S);
   up(ds->has_v.ptr, hv.data(), sizeof(int) * S);
-  if (e == hipSuccess) e = build_dataset_lists(ctx, ds);
+  if (e == hipSuccess) e = build_dataset_lists(ctx, ds, ds->pos.ptr);
   if (e == hipSuccess) e = ensure_geometry(ctx, ds);
   if (e != hipSuccess) {
     nep_dataset_destroy(ds);
@@ -622,9 +605,7 @@ nep_status nep_dataset_set_positions(nep_ctx ctx, nep_dataset ds, const double* 
   if (!ds || ds->ctx != ctx) return fail(ctx, NEP_EINVAL, "dataset belongs to another context");
   if (!pos_dev) return fail(ctx, NEP_EINVAL, "pos_dev is NULL");
   DeviceGuard guard(ctx->device);
-  hipError_t e = hipMemcpyAsync(ds->pos.ptr, pos_dev, sizeof(double) * 3 * ds->N,
-                                hipMemcpyDeviceToDevice, ctx->stream);
-  if (e == hipSuccess) e = build_dataset_lists(ctx, ds);
+  hipError_t e = build_dataset_lists(ctx, ds, pos_dev);
   if (e == hipSuccess && ds->population_used) {
     e = ensure_geometry(ctx, ds);
     if (e == hipSuccess) return nep_synchronize(ctx);
@@ -634,8 +615,6 @@ nep_status nep_dataset_set_positions(nep_ctx ctx, nep_dataset ds, const double* 
   // positions) needs the pair totals only: preparing the population operands
   // took 0.35 ms of the 1.1 ms of an energy-and-gradient call at new positions
   // of 64 structures.
-  k_ds_pair_totals<<<std::min(64u, blocks_for(ds->N, kBlock)), kBlock, 0, ctx->stream>>>(
-      ds->N, ds->pn_in.ptr, ds->pn_ang.ptr, pair_totals(ctx));
   unsigned long long pairs[2] = {0, 0};
   const nep_status st = synchronize_flags(ctx, pairs);
   if (st != NEP_EDEVICE) {
@@ -703,6 +682,17 @@ nep_status nep_dataset_backward(nep_ctx ctx, nep_dataset ds, const float* z_dev,
                            grad_z32_dev);
   });
   return check_hip(ctx, e, "launching the backward pass");
+}
+
+nep_status nep_dataset_position_gradient(nep_ctx ctx, nep_dataset ds, const double* gE_dev,
+                                         const float* forces_dev, double* grad_pos_dev) {
+  if (!ctx) return NEP_EINVAL;
+  nep_status chk = check_dataset(ctx, ds);
+  if (chk != NEP_OK) return chk;
+  if (!forces_dev || !grad_pos_dev) return fail(ctx, NEP_EINVAL, "NULL argument");
+  DeviceGuard guard(ctx->device);
+  return check_hip(ctx, launch_position_gradient(ctx, ds, gE_dev, forces_dev, grad_pos_dev),
+                   "launching the position gradient");
 }
 
 nep_status snes_eval_population(nep_ctx ctx, nep_dataset ds, int n_pop, const float* Z_dev,

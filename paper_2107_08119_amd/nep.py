@@ -27,7 +27,7 @@ EXPORTED = [
     "nep_get_neighbors", "nep_compute", "nep_md_step", "nep_set_timing", "nep_get_timing",
     "nep_time_partials", "nep_dataset_create", "nep_dataset_destroy", "snes_eval_population",
     "snes_sample", "snes_update", "nep_dataset_set_positions", "nep_dataset_get_positions",
-    "nep_dataset_compute", "nep_dataset_backward", "snes_autotune", "snes_run",
+    "nep_dataset_compute", "nep_dataset_backward", "nep_dataset_position_gradient", "snes_autotune", "snes_run",
     "snes_set_tile", "nep_dataset_pairs", "nep_autotune", "nep_set_tile", "nep_md_step_driven",
     "nep_set_species",
     "nep_vvcf_create", "nep_vvcf_destroy", "nep_vvcf_sample", "nep_vvcf_get", "nep_vvcf_spectrum",
@@ -108,6 +108,7 @@ def lib() -> C.CDLL:
         L.nep_dataset_get_positions.argtypes = [vp, vp, vp]
         L.nep_dataset_compute.argtypes = [vp, vp, vp, vp, vp, vp]
         L.nep_dataset_backward.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp]
+        L.nep_dataset_position_gradient.argtypes = [vp, vp, vp, vp, vp]
         L.nep_evaluate_static.argtypes = [vp, ip, vp, C.POINTER(C.c_double), dp, ip, vp, vp,
                                           vp, vp, vp, vp]
         L.nep_static_workspace_bytes.argtypes = []
@@ -445,6 +446,15 @@ class Context:
             _ptr(out["z"]), _ptr(out["z32"])))
         return out
 
+    def _position_gradient(self, ds: "Dataset", gE, F) -> torch.Tensor:
+        _require(F, torch.float32, (3, ds.n_atoms), "F")
+        if gE is not None:
+            _require(gE, torch.float64, (ds.n_struct,), "gE")
+        out = torch.empty((3, ds.n_atoms), dtype=torch.float64, device=F.device)
+        self._check(self._lib.nep_dataset_position_gradient(self._h, ds._h, _ptr(gE), _ptr(F),
+                                                            _ptr(out)))
+        return out
+
     def md_step(self, n_steps: int, dt: float, rebuild_every: int, mass: float,
                 pos: torch.Tensor, vel: torch.Tensor, thermo: torch.Tensor | None = None,
                 W: torch.Tensor | None = None, J: torch.Tensor | None = None,
@@ -562,6 +572,7 @@ class NEPEnergy(torch.autograd.Function):
         out = ctx.dataset_compute(ds, z.detach())
         actx.save_for_backward(z, out["F"])
         actx.nep = (ctx, ds)
+        actx.set_materialize_grads(False)
         actx.pos_needs_grad = pos.requires_grad
         return out["E"], out["F"]
 
@@ -569,10 +580,15 @@ class NEPEnergy(torch.autograd.Function):
     def backward(actx, gE, gF):
         z, F = actx.saved_tensors
         ctx, ds = actx.nep
+        # an output that the objective does not use has no gradient here (None):
+        # filling one with zeros and reading back whether it is zero took a
+        # quarter of an energy-and-gradient call on 64 structures
         gE = None if gE is None else gE.detach().contiguous()
         gF = None if gF is None else gF.detach().contiguous()
         if gF is not None and actx.pos_needs_grad and bool(gF.abs().max() > 0):
             raise NotImplementedError("position gradient of the force part needs the Hessian")
+        if not actx.needs_input_grad[1]:  # only the positions' gradient is asked for
+            return ctx._position_gradient(ds, gE, F), None, None, None
         g = ctx.dataset_backward(ds, z.detach(), gE, gF, F, want_pos=actx.pos_needs_grad)
         return g.get("pos"), g["z32"], None, None
 
