@@ -19,7 +19,7 @@
 // k_grad_final adds the blocks in order and applies the factors w2.
 #include <algorithm>
 
-#include "nep_device.h"
+#include "nep_terms.h"
 
 namespace nep {
 namespace {
@@ -39,13 +39,49 @@ struct GradLayout {
                        G = 3 * NNEU + 2 * NDES, FIELDS = 3 * NNEU + 2 * NDES + 1;
 };
 
-template <int idx>
-constexpr int l_of() {
-  return idx < 3 ? 1 : (idx < 8 ? 2 : (idx < 15 ? 3 : 4));
+// The derivatives of the 24 harmonics at the unit vector (x, y, z) along
+// (tx, ty, tz), and the harmonics: Yhat_lm = Q_lm(z) Re or Im (x + i y)^m.
+__device__ __forceinline__ void harmonics_along(float x, float y, float z, float tx, float ty,
+                                                float tz, float (&yh)[24], float (&dy)[24]) {
+  const float zz = z * z;
+  const PlanePowers p = plane_powers(x, y);
+  const ZFactors q = z_factors(z, zz);
+  harmonics(x, y, z, yh);
+  // of Re and Im (x + i y)^m: m (x + i y)^(m-1) (tx + i ty)
+  const float a2 = 2.f * (x * tx - y * ty), b2 = 2.f * (x * ty + y * tx);
+  const float a3 = 3.f * (p.a2 * tx - p.b2 * ty), b3 = 3.f * (p.a2 * ty + p.b2 * tx);
+  const float a4 = 4.f * (p.a3 * tx - p.b3 * ty), b4 = 4.f * (p.a3 * ty + p.b3 * tx);
+  dy[0] = tx, dy[1] = ty, dy[2] = tz;
+  dy[5] = 3.f * z * tz, dy[11] = (7.5f * zz - 1.5f) * tz;
+  dy[19] = z * (17.5f * zz - 7.5f) * tz;
+  auto pair = [&](int re, int im, float q0, float dq, float pa, float pb, float da, float db) {
+    dy[re] = dq * pa + q0 * da;
+    dy[im] = dq * pb + q0 * db;
+  };
+  pair(6, 4, q.q21, NEP_S3 * tz, p.a1, p.b1, tx, ty);
+  pair(12, 10, q.q31, 2.5f * NEP_S6 * z * tz, p.a1, p.b1, tx, ty);
+  pair(20, 18, q.q41, (5.25f * NEP_S10 * zz - 0.75f * NEP_S10) * tz, p.a1, p.b1, tx, ty);
+  pair(13, 9, q.q32, 0.5f * NEP_S15 * tz, p.a2, p.b2, a2, b2);
+  pair(21, 17, q.q42, 3.5f * NEP_S5 * z * tz, p.a2, p.b2, a2, b2);
+  pair(22, 16, q.q43, 0.25f * NEP_S70 * tz, p.a3, p.b3, a3, b3);
+  dy[7] = q.q22 * a2, dy[3] = q.q22 * b2;
+  dy[14] = q.q33 * a3, dy[8] = q.q33 * b3;
+  dy[23] = q.q44 * a4, dy[15] = q.q44 * b4;
 }
 
+// Per atom: L lanes split the neighbour slots.  The displacements of the first
+// kStage slots are formed once, several loads in flight, and kept in LDS for
+// both passes.  Bound: the arithmetic of the two passes, latency below 8,000
+// atoms.  The angular part of delta q, per pair and (n, l), is
+//   2 g_n'(r) (u.D) sum_m c_nlm Yhat_lm + 2 g_n(r) sum_m c_nlm dYhat_lm
+// with dYhat_lm the derivative along (D - u (u.D)) / r: 2 multiply-adds per
+// (n, l, m) and one set of directional derivatives, where all three gradient
+// components per harmonic and 3 per (n, l, m) took 54 us on 36,863 atoms, now 50
+// (256 registers: two waves per SIMD, the last 64 of 576 blocks after the rest).
+// Eight lanes per atom take as long (49 us; 21 against 23 on 7,700 atoms).
+constexpr int kStage = 40;
 template <int NR, int NA, int LMAX, int NNEU, int L>
-__global__ __launch_bounds__(kBlock) void k_grad_atoms(
+__global__ __launch_bounds__(kBlock, 2) void k_grad_atoms(
     int n, const double* __restrict__ pos, const uint32_t* __restrict__ nl,
     const int* __restrict__ cnt_r, const int* __restrict__ cnt_a,
     const double* __restrict__ boxes, const int* __restrict__ struct_of,
@@ -70,6 +106,44 @@ __global__ __launch_bounds__(kBlock) void k_grad_atoms(
   const double* H = boxes + 9 * (size_t)struct_of[ii];
   const float rcr_inv = 1.f / rc_r, rca_inv = 1.f / rc_a;
 
+  constexpr int KS = kStage, kBatch = 5;
+  __shared__ float4 sd[KS][kBlock / L];  // displacement and, in .w, the neighbour
+  const int la = threadIdx.x / L;
+  const int staged = min(cr, KS);
+  for (int s0 = lane; s0 < staged; s0 += L * kBatch) {
+    uint32_t e[kBatch];
+    double pj[kBatch][3];
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) e[b] = nl[(size_t)min(s0 + b * L, staged - 1) * n + i];
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      const int j = (int)(e[b] & kAtomMask);
+      pj[b][0] = pos[j];
+      pj[b][1] = pos[n + j];
+      pj[b][2] = pos[2 * n + j];
+    }
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      if (s0 + b * L >= staged) break;
+      float dx, dy, dz;
+      image_displacement(e[b], pj[b][0], pj[b][1], pj[b][2], xi, yi, zi, H, dx, dy, dz);
+      sd[s0 + b * L][la] = make_float4(dx, dy, dz, __int_as_float((int)(e[b] & kAtomMask)));
+    }
+  }
+  // a lane reads back only the entries it wrote
+  auto pair = [&](int s, int& j, float& dx, float& dy, float& dz) {
+    if (s < KS) {
+      const float4 v = sd[s][la];
+      dx = v.x;
+      dy = v.y;
+      dz = v.z;
+      j = __float_as_int(v.w);
+    } else {
+      displacement(nl[(size_t)s * n + i], pos, n, xi, yi, zi, H, j, dx, dy, dz);
+    }
+  };
+
+  const float rcr2 = rc_r * rc_r, rca2 = rc_a * rc_a;
   float q[NDES];
   float c[NA][NLM];
 #pragma unroll
@@ -81,47 +155,19 @@ __global__ __launch_bounds__(kBlock) void k_grad_atoms(
   for (int s = lane; s < cr; s += L) {
     int j;
     float dx, dy, dz;
-    displacement(nl[(size_t)s * n + i], pos, n, xi, yi, zi, H, j, dx, dy, dz);
-    const float r2 = dx * dx + dy * dy + dz * dz;
-    const float rinv = __builtin_amdgcn_rsqf(r2);
-    const float r = r2 * rinv;
-    if (r < rc_r) {
-      float g[NR];
-      radial_basis<NR, false>(r, rcr_inv, g, nullptr);
-#pragma unroll
-      for (int a = 0; a < NR; ++a) q[a] += g[a];
-    }
-    if (s < ca && r < rc_a) {
-      float g[NA];
-      radial_basis<NA, false>(r, rca_inv, g, nullptr);
-      const float x = dx * rinv, y = dy * rinv, z = dz * rinv;
-      const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
-      const float xyz = xy * z;
-      (void)xyz;
-#define NEP_ACC(idx, YV, GX, GY, GZ)                                         \
-  if constexpr ((idx) < NLM) {                                               \
-    const float yv = (YV);                                                   \
-    _Pragma("unroll") for (int a = 0; a < NA; ++a) c[a][idx] += g[a] * yv;   \
-  }
-      NEP_YLM_TABLE(NEP_ACC)
-#undef NEP_ACC
-    }
+    pair(s, j, dx, dy, dz);
+    const float r2 = pair_r2(dx, dy, dz);
+    pair_descriptor<NR, NA, LMAX>(dx, dy, dz, r2 < rcr2, s < ca && r2 < rca2, rcr_inv, rca_inv, q,
+                                  c);
   }
 #pragma unroll
   for (int a = 0; a < NR; ++a) q[a] = group_sum<L>(q[a]);
+  radial_finish<NR>(q);
 #pragma unroll
   for (int a = 0; a < NA; ++a)
 #pragma unroll
     for (int m = 0; m < NLM; ++m) c[a][m] = group_sum<L>(c[a][m]);
-#pragma unroll
-  for (int a = 0; a < NA; ++a)
-#pragma unroll
-    for (int l = 1; l <= LMAX; ++l) {
-      float s2 = 0.f;
-#pragma unroll
-      for (int m = 0; m < 2 * l + 1; ++m) s2 += c[a][l * l - 1 + m] * c[a][l * l - 1 + m];
-      q[NR + a * LMAX + (l - 1)] = s2;
-    }
+  angular_invariants<NR, NA, LMAX>(c, q);
 
   // delta q: directional derivative of the descriptor along gF
   float dq[NDES];
@@ -129,39 +175,48 @@ __global__ __launch_bounds__(kBlock) void k_grad_atoms(
   for (int v = 0; v < NDES; ++v) dq[v] = 0.f;
   if (gF) {
     const float gxi = gF[ii], gyi = gF[n + ii], gzi = gF[2 * n + ii];
+    int j = 0;
+    float dx = 1.f, dy = 0.f, dz = 0.f, ax = 0.f, ay = 0.f, az = 0.f;
+    auto fetch = [&](int s) {  // pair s and gF of its neighbour, one slot ahead
+      pair(s, j, dx, dy, dz);
+      ax = gF[j];
+      ay = gF[n + j];
+      az = gF[2 * n + j];
+    };
+    if (lane < cr) fetch(lane);
     for (int s = lane; s < cr; s += L) {
-      int j;
-      float dx, dy, dz;
-      displacement(nl[(size_t)s * n + i], pos, n, xi, yi, zi, H, j, dx, dy, dz);
-      const float r2 = dx * dx + dy * dy + dz * dz;
+      const float r2 = pair_r2(dx, dy, dz);
       const float rinv = __builtin_amdgcn_rsqf(r2);
       const float r = r2 * rinv;
       const float x = dx * rinv, y = dy * rinv, z = dz * rinv;
-      const float Dx = gF[j] - gxi, Dy = gF[n + j] - gyi, Dz = gF[2 * n + j] - gzi;
+      const float Dx = ax - gxi, Dy = ay - gyi, Dz = az - gzi;
+      if (s + L < cr) fetch(s + L);
       const float uD = x * Dx + y * Dy + z * Dz;
-      if (r < rc_r) {
+      if (r2 < rcr2) {
         float g[NR], dg[NR];
         radial_basis<NR, true>(r, rcr_inv, g, dg);
 #pragma unroll
         for (int a = 0; a < NR; ++a) dq[a] += dg[a] * uD;
       }
-      if (s < ca && r < rc_a) {
-        float g[NA], dg[NA];
+      if (s < ca && r2 < rca2) {
+        float g[NA], dg[NA], yh[24], dyh[24];
         radial_basis<NA, true>(r, rca_inv, g, dg);
-        const float xx = x * x, yy = y * y, zz = z * z, xy = x * y, xz = x * z, yz = y * z;
-        const float xyz = xy * z;
-        (void)xyz;
-        // d q_nl = sum_m 2 c_nlm [g_n' Y_lm (u.D) + g_n (grad Y_lm . D - (u.grad Y_lm)(u.D)) / r]
-#define NEP_JVP(idx, YV, GX, GY, GZ)                                                     \
-  if constexpr ((idx) < NLM) {                                                           \
-    const float gxv = (GX), gyv = (GY), gzv = (GZ);                                      \
-    const float yd = (YV) * uD;                                                          \
-    const float gd = (gxv * Dx + gyv * Dy + gzv * Dz - (x * gxv + y * gyv + z * gzv) * uD) * rinv; \
-    _Pragma("unroll") for (int a = 0; a < NA; ++a)                                       \
-      dq[NR + a * LMAX + (l_of<idx>() - 1)] += 2.f * c[a][idx] * (dg[a] * yd + g[a] * gd); \
-  }
-        NEP_YLM_TABLE(NEP_JVP)
-#undef NEP_JVP
+        harmonics_along(x, y, z, (Dx - x * uD) * rinv, (Dy - y * uD) * rinv, (Dz - z * uD) * rinv,
+                        yh, dyh);
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+          const float gy = 2.f * dg[a] * uD, gd = 2.f * g[a];
+#pragma unroll
+          for (int l = 1; l <= LMAX; ++l) {
+            float sy = 0.f, sd2 = 0.f;
+#pragma unroll
+            for (int m = l * l - 1; m < (l + 1) * (l + 1) - 1; ++m) {
+              sy += c[a][m] * yh[m];
+              sd2 += c[a][m] * dyh[m];
+            }
+            dq[NR + a * LMAX + (l - 1)] += gy * sy + gd * sd2;
+          }
+        }
       }
     }
 #pragma unroll
