@@ -322,7 +322,7 @@ void nep_dataset_destroy(nep_dataset ds);
  * their order.  The squared errors are float64 sums in a fixed order.  The
  * result of an individual does not depend on the rest of the population, and
  * a non-finite bound gives NaN losses.  The network kernel uses the shape
- * chosen by snes_autotune (32 atoms per wave until then).  The dataset must
+ * chosen by snes_autotune (by the number of atoms until then).  The dataset must
  * belong to ctx and match its hyperparameters.  NEP_EINVAL if a structure has
  * more than 13,312 atoms (the forces of one individual on one structure must
  * fit in 160 KB of LDS); more than 52 individuals per 256-atom structure

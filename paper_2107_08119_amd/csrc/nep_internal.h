@@ -306,7 +306,7 @@ struct nep_dataset_s {
   bool population_used = false;  // a population call has run: set_positions prepares the cache
   long long pairs_r = 0, pairs_a = 0;  // pairs inside r_c^R, inside r_c^A (geometry cache)
   int tile_kc = 0;               // individuals per contraction launch the tiles were sized for
-  int pop_variant = 1;         // network kernel shape: 0, 1, 2 = 16, 32, 64 atoms per wave
+  int pop_variant = -1;        // network kernel shape: 0, 1, 2 = 16, 32, 64 atoms per wave, -1 by size
   unsigned long long serial = 0;  // unique per dataset created by the process
   bool pop_tuned = false;
   // population workspace
@@ -354,6 +354,8 @@ int population_variants();
 int population_atoms(int variant);
 // Largest structure snes_eval_population handles (its forces for one
 // individual must fit the contraction kernel's LDS).
+// atom rows of dU/dq and U in a population evaluation: whole network tiles
+inline size_t population_rows(int n) { return ((size_t)n + 63) / 64 * 64; }
 int population_max_structure();
 
 // neighbours.hip

@@ -211,11 +211,17 @@ __host__ __device__ constexpr int dq_kappa(int col, int nt) {
   return 8 * (col / 4) + col % 4 + 4 * nt;
 }
 
-__global__ void k_pop_qpad(int N, const float* __restrict__ desc, float* __restrict__ qpad) {
+// Descriptors in padded order, zero for the rows past N.
+__global__ void k_pop_qpad(int N, size_t rows, const float* __restrict__ desc,
+                           float* __restrict__ qpad) {
   const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (size_t)N * kQ) return;
+  if (t >= rows * kQ) return;
   const int i = (int)(t / kQ), v = (int)(t % kQ);
   float q = 0.f;
+  if (i >= N) {
+    qpad[t] = q;
+    return;
+  }
   if (v < NR)
     q = desc[(size_t)i * kDescRow + v];
   else if (v >= kAng0)
@@ -334,7 +340,7 @@ __device__ __forceinline__ float max_nan(float a, float b) { return (b > a || b 
 // lane (col, h) = (lane % 16, lane / 16)
 //   q 0..3:  W1[16 mt + col][nu(4 s + h)], the first product's A (mt, s),
 //   q 4..7:  W1[16 (s / 4) + 4 h + s % 4][nu(16 nt + col)], the second's B,
-//   q 8..11: b1 and w2 of the lane's neurons 16 mt + 4 h + r,
+//   q 8..11: -b1 and 4 w2 of the lane's neurons 16 mt + 4 h + r,
 // with nu(kappa) the descriptor component of padded index kappa and zeros for
 // padding; wb2[k] = b2; dqbound[k] bounds |dU/dq| of individual k.
 __global__ __launch_bounds__(64) void k_pop_wfrag(int n_par, const float* __restrict__ Z,
@@ -370,8 +376,8 @@ __global__ __launch_bounds__(64) void k_pop_wfrag(int n_par, const float* __rest
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int mu = 16 * mt + 4 * h + r;
-      f[32 + 4 * mt + r] = mu < NNEU ? z[NNEU * NDES + mu] : 0.f;
-      f[40 + 4 * mt + r] = mu < NNEU ? z[NNEU * (NDES + 1) + mu] : 0.f;
+      f[32 + 4 * mt + r] = mu < NNEU ? -z[NNEU * NDES + mu] : 0.f;
+      f[40 + 4 * mt + r] = mu < NNEU ? 4.f * z[NNEU * (NDES + 1) + mu] : 0.f;
     }
 #pragma unroll
   for (int q = 0; q < 12; ++q)
@@ -383,99 +389,108 @@ __global__ __launch_bounds__(64) void k_pop_wfrag(int n_par, const float* __rest
 // act^T = W1_k Q^T (rows: neurons in two tiles of 16; columns: atoms), the
 // neurons' tanh, U_i, and dU/dq_i = sum_mu w2_mu sech^2(act_mu) W1_k[mu] as
 // a product whose K order (neurons) follows what each lane already holds,
-// so G = w2 sech^2 never moves between lanes.  Each individual's weight
-// fragments are loaded while the previous individual is multiplied.
-// dq [N][n_pop][32] (padded order, zeros at 9..11), U [n_pop][N].
+// so G = w2 sech^2 never moves between lanes.  The next individual's weight
+// fragments are requested as soon as their registers are free (W1 after the
+// last tile's first product, b1 and w2 after its tanh, W1 again after its
+// second product), before the stores, so that no load waits behind one.
+// dq in blocks of kDqAtoms atoms: [block][n_pop][kDqAtoms][32] (padded order,
+// zeros at 9..11), 2 KB written in one piece per tile and individual;
+// U [n_pop][rows].  Both have whole tiles of rows (population_rows): rows past
+// the atoms are computed from zero descriptors and written, which keeps
+// branches, and with them waits for the stores, out of the loop.
 // Individuals per wave of the network kernel (`chunk`, at most kNetChunk): the
 // population is split into chunks over blockIdx.y, so that the grid has many
 // more waves than the machine holds at once (whole waves of all individuals
 // left the last round of waves mostly empty).
-// Bound: the matrix cores (85 us of 16x16x4 steps per 50 individuals of 65,600
-// atoms) and the store of dU/dq (128 bytes per individual and atom), overlapped
-// by the waves of a SIMD: with three of them 32 atoms per wave take 440 us per
-// evaluation with the contraction, with two 455 us.
+// Bound: the float32 matrix steps (86 us per 50 individuals of 64,400 atoms) and
+// the vector instructions (54 us), which do not run beside each other; measured
+// 172 us.  b1 as the start of the sums and w2 times 4 save 16 of 130 vector
+// instructions per tile and individual.
 constexpr int kNetChunk = 10;
 constexpr int kNetWaves = 4096;  // four per SIMD
 
+constexpr int kDqAtoms = 16;
 template <int CT>
 __global__ __launch_bounds__(kBlock)
-    __attribute__((amdgpu_waves_per_eu(CT == 1 ? 4 : (CT == 2 ? 3 : 2)))) void k_pop_net(
-    int N, int n_pop, int chunk, const float* __restrict__ qpad, const float4* __restrict__ wf,
+    __attribute__((amdgpu_waves_per_eu(CT == 1 ? 6 : (CT == 2 ? 3 : 4)))) void k_pop_net(
+    int rows, int n_pop, int chunk, const float* __restrict__ qpad, const float4* __restrict__ wf,
     const float* __restrict__ wb2, float* __restrict__ dq, float* __restrict__ U) {
   const int l = threadIdx.x & 63, col = l & 15, h = l >> 4;
   const int a0 = (blockIdx.x * (kBlock / 64) + threadIdx.x / 64) * 16 * CT;
-  if (a0 >= N) return;  // whole waves leave together
+  if (a0 >= rows) return;  // whole waves leave together
   // Q^T fragments: B[kappa = 4 s + h][atom = col]
   float qb[CT][8];
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const int a = a0 + 16 * ct + col;
+  for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-    for (int s = 0; s < 8; ++s) qb[ct][s] = a < N ? qpad[(size_t)a * kQ + 4 * s + h] : 0.f;
-  }
+    for (int s = 0; s < 8; ++s) qb[ct][s] = qpad[(size_t)(a0 + 16 * ct + col) * kQ + 4 * s + h];
   // the individuals k_begin .. k_end - 1 of this wave (blockIdx.y chunk)
   const int k_begin = blockIdx.y * chunk;
   const int k_end = min(n_pop, k_begin + chunk);
-  float4 nxt[12];
+  // fragments 0..3: W1 of the first product, 4..7: of the second, 8..9: -b1, 10..11: 4 w2
+  float f[48];
+  auto load = [&](int k, int first, int last) {
 #pragma unroll
-  for (int q = 0; q < 12; ++q) nxt[q] = wf[((size_t)k_begin * 12 + q) * 64 + l];
-  for (int k = k_begin; k < k_end; ++k) {
-    float f[48];
-#pragma unroll
-    for (int q = 0; q < 12; ++q) {
-      f[4 * q] = nxt[q].x;
-      f[4 * q + 1] = nxt[q].y;
-      f[4 * q + 2] = nxt[q].z;
-      f[4 * q + 3] = nxt[q].w;
+    for (int q = first; q < last; ++q) {
+      const float4 v = wf[((size_t)k * 12 + q) * 64 + l];
+      f[4 * q] = v.x;
+      f[4 * q + 1] = v.y;
+      f[4 * q + 2] = v.z;
+      f[4 * q + 3] = v.w;
     }
-    const float b2 = wb2[k];
+  };
+  load(k_begin, 0, 12);
+  float b2 = wb2[k_begin];
+  for (int k = k_begin; k < k_end; ++k) {
     const int kn = k + 1 < k_end ? k + 1 : k;
-#pragma unroll
-    for (int q = 0; q < 12; ++q) nxt[q] = wf[((size_t)kn * 12 + q) * 64 + l];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       f32x4 act[2];
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        act[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int mt = 0; mt < 2; ++mt)  // the sums start from -b1
+        act[mt] = f32x4{f[32 + 4 * mt], f[33 + 4 * mt], f[34 + 4 * mt], f[35 + 4 * mt]};
 #pragma unroll
-        for (int s = 0; s < 8; ++s) act[mt] = mma(f[8 * mt + s], qb[ct][s], act[mt]);
-      }
+      for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) act[mt] = mma(f[8 * mt + s], qb[ct][s], act[mt]);
+      if (ct == CT - 1) load(kn, 0, 4);
       float gm[2][4];
       float u = 0.f;
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float x = act[mt][r] - f[32 + 4 * mt + r];
-          const float w2 = f[40 + 4 * mt + r];
+          const float x = act[mt][r], w2 = f[40 + 4 * mt + r];  // 4 w2
           // tanh and 1 - tanh^2 from e = exp(-2|x|) (no cancellation)
           const float ea = __expf(-2.f * fabsf(x));
           const float inv = __builtin_amdgcn_rcpf(1.f + ea);
           const float th = copysignf((1.f - ea) * inv, x);
           u += w2 * th;
-          gm[mt][r] = w2 * (4.f * ea * inv * inv);
+          gm[mt][r] = w2 * (ea * inv * inv);
         }
       u += __shfl_xor(u, 16, 64);
       u += __shfl_xor(u, 32, 64);
-      const int a = a0 + 16 * ct + col;
-      if (h == 0 && a < N) U[(size_t)k * N + a] = u - b2;
+      u = 0.25f * u - b2;
+      if (ct == CT - 1) {
+        load(kn, 8, 12);
+        b2 = wb2[kn];
+      }
       f32x4 o[2];
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        o[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int nt = 0; nt < 2; ++nt) o[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < 8; ++s) o[nt] = mma(gm[s / 4][s % 4], f[16 + 8 * nt + s], o[nt]);
-      }
+      for (int s = 0; s < 8; ++s)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int ar = a0 + 16 * ct + 4 * h + r;
-        if (ar < N) {
-          // kappa = dq_kappa(col, 0) and dq_kappa(col, 1) = that + 4: adjacent slots
-          float* d = dq + ((size_t)ar * n_pop + k) * kQ + dq_slot(dq_kappa(col, 0));
-          *reinterpret_cast<float2*>(d) = make_float2(o[0][r], o[1][r]);
-        }
-      }
+        for (int nt = 0; nt < 2; ++nt)
+          o[nt] = mma(gm[s / 4][s % 4], f[16 + 8 * nt + s], o[nt]);
+      if (ct == CT - 1) load(kn, 4, 8);
+      U[(size_t)k * rows + a0 + 16 * ct + col] = u;  // the same from the four groups
+      // kappa = dq_kappa(col, 0) and dq_kappa(col, 1) = that + 4: adjacent slots
+      float* d = dq + (((size_t)(a0 / 16 + ct) * n_pop + k) * kDqAtoms + 4 * h) * kQ +
+                 dq_slot(dq_kappa(col, 0));
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<float2*>(d + r * kQ) = make_float2(o[0][r], o[1][r]);
     }
   }
 }
@@ -577,7 +592,7 @@ __device__ __forceinline__ void fetch_atom(AtomOps<kCols>& o, int4 m, int i, int
                                            const float* const (&dqk)[kCols],
                                            const float* pfrag, const float4* ppair, int l,
                                            int h) {
-  const size_t row = (size_t)i * n_pop * kQ;
+  const size_t row = ((size_t)(i / kDqAtoms) * n_pop * kDqAtoms + i % kDqAtoms) * kQ;
 #pragma unroll
   for (int c = 0; c < kCols; ++c) {  // kappa = 4 q + h at slots 8 h + q
     const float4 lo = *reinterpret_cast<const float4*>(dqk[c] + row);
@@ -627,7 +642,7 @@ __device__ __forceinline__ void fetch_atom(AtomOps<kCols>& o, int4 m, int i, int
 constexpr int contract_waves(int cols) { return cols > 1 ? 12 : 16; }
 template <int kCols>
 __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
-    int N, int S, int kper, int n_pop, const int* __restrict__ tile_order,
+    int N, int rows, int S, int kper, int n_pop, const int* __restrict__ tile_order,
     const int* __restrict__ tile_off, const int* __restrict__ tile_s0,
     const int* __restrict__ off, const int* __restrict__ struct_of,
     const int4* __restrict__ pmeta, const float* __restrict__ pfrag,
@@ -661,7 +676,7 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
     const int kl = 16 * c + col;
     valid[c] = kl < KC;
     const int k = k0 + (valid[c] ? kl : 0);
-    dqk[c] = dq + (size_t)k * kQ + 8 * h;  // K index 4 q + h at slot 8 h + q
+    dqk[c] = dq + (size_t)k * kDqAtoms * kQ + 8 * h;  // K index 4 q + h at slot 8 h + q
     const int eF = valid[c] ? esc[0][kl] : kBadScale, eW = valid[c] ? esc[1][kl] : kBadScale;
     // the force scale goes into dU/dq, so the products come out scaled; the
     // virial rows are rescaled by 2^(eW - eF).  A non-finite bound: every
@@ -846,7 +861,7 @@ __global__ __launch_bounds__(64 * contract_waves(kCols)) void k_pop_contract(
       for (int c = 0; c < 3; ++c) t[c] = f_tar[(size_t)c * N + i];
 #pragma unroll
       for (int q = 0; q < kUnit; ++q) {
-        eu[q] += (double)U[(size_t)(k0 + kl[q]) * N + i];
+        eu[q] += (double)U[(size_t)(k0 + kl[q]) * rows + i];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           const double d = (double)acc[c * kPlane + il * kcs + kl[q]] * iF[q] - t[c];
@@ -906,7 +921,7 @@ void launch_net(nep_ctx ctx, nep_dataset ds, int n_pop, const float* Z, bool fir
   const int chunk = std::max(1, std::min(kNetChunk, (int)((long long)tiles * n_pop / kNetWaves)));
   launch_kernel(ctx, false, false, k_pop_net<CT>,
                 dim3(blocks_for(ds->N, 16 * CT * (kBlock / 64)), (n_pop + chunk - 1) / chunk),
-                dim3(kBlock), ds->N, n_pop, chunk, (const float*)ds->qpad.ptr,
+                dim3(kBlock), (int)population_rows(ds->N), n_pop, chunk, (const float*)ds->qpad.ptr,
                 (const float4*)ds->wfrag.ptr, (const float*)ds->wb2.ptr, ds->dq.ptr, ds->U.ptr);
 }
 
@@ -914,7 +929,7 @@ template <int kCols>
 void launch_contract(nep_ctx ctx, nep_dataset ds, int n_pop, int kper) {
   launch_kernel(ctx, false, false, k_pop_contract<kCols>,
                 dim3(ds->n_tiles, (n_pop + kper - 1) / kper), dim3(64 * contract_waves(kCols)), ds->N,
-                ds->S, kper, n_pop, (const int*)ds->tile_order.ptr, (const int*)ds->tile_off.ptr,
+                (int)population_rows(ds->N), ds->S, kper, n_pop, (const int*)ds->tile_order.ptr, (const int*)ds->tile_off.ptr,
                 (const int*)ds->tile_s0.ptr, (const int*)ds->off.ptr,
                 (const int*)ds->struct_of.ptr, (const int4*)ds->pmeta.ptr,
                 (const float*)ds->pfrag.ptr, (const float4*)ds->ppair.ptr,
@@ -936,7 +951,7 @@ hipError_t prepare_dataset_geometry(nep_ctx ctx, nep_dataset ds) {
   if (e == hipSuccess) e = ds->pn_ang.ensure(N);
   if (e == hipSuccess) e = ds->pn_in.ensure(N);
   if (e == hipSuccess) e = ds->desc.ensure((size_t)kDescRow * N);
-  if (e == hipSuccess) e = ds->qpad.ensure((size_t)kQ * N);
+  if (e == hipSuccess) e = ds->qpad.ensure(kQ * population_rows(N));
   if (e == hipSuccess) e = ds->pmeta.ensure(N);
   if (e == hipSuccess) e = ds->stile0.ensure(S);
   if (e != hipSuccess) return e;
@@ -950,7 +965,8 @@ hipError_t prepare_dataset_geometry(nep_ctx ctx, nep_dataset ds) {
       ds->rev.ptr, ds->pcidx.ptr, ds->prec.ptr, ctx->flags.ptr);
   k_ds_descriptors<4><<<blocks_for((size_t)N * 4, kBlock), kBlock, 0, st>>>(
       N, ds->prec.ptr, ds->pn_ang.ptr, ds->pn_in.ptr, rcr, rca, ds->desc.ptr);
-  k_pop_qpad<<<blocks_for((size_t)N * kQ, kBlock), kBlock, 0, st>>>(N, ds->desc.ptr, ds->qpad.ptr);
+  k_pop_qpad<<<blocks_for(population_rows(N) * kQ, kBlock), kBlock, 0, st>>>(
+      N, population_rows(N), ds->desc.ptr, ds->qpad.ptr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // Layout of the contraction operands from the pair counts (host side).
   std::vector<int> n_in(N), n_ang(N);
@@ -1072,6 +1088,11 @@ hipError_t launch_population(nep_ctx ctx, nep_dataset ds, int n_pop, const float
   if (ds->N == 0 || n_pop == 0) return hipSuccess;
   const int KC = ds->tile_kc;
   if (KC < 1 || ds->n_tiles < 1) return hipErrorInvalidConfiguration;
+  // Atoms per wave of the network kernel unless the caller has chosen: 64 read an
+  // individual's weights for four tiles (414 against 422 us per evaluation for 50
+  // individuals on 64k atoms, 824 against 835 on 131k); on small sets 32 leave
+  // more waves (115 against 120 us on 8.3k atoms, 171 both on 15k).
+  if (variant < 0) variant = ds->N >= 12288 ? 2 : 1;
   switch (variant) {
     case 0:
       launch_net<1>(ctx, ds, n_pop, Z, first);
@@ -1086,8 +1107,8 @@ hipError_t launch_population(nep_ctx ctx, nep_dataset ds, int n_pop, const float
   // when the tiles alone fill the chip, since a block reads its tile's fragments
   // once for all of them; at most 32 or 16 while there are so few tiles that the
   // smaller blocks still run in two rounds or one over the 256 compute units.
-  // 50 individuals, tiles x (blocks of 50 / 25 / 16), us per evaluation: 60 x 233 /
-  // 153 / 119, 120 x 256 / 173 / 181, 250 x 311 / 249 / 303, 500 x 446 / 511 / 660.
+  // 50 individuals, tiles x (blocks of 50 / 25 / 17), us per evaluation: 60 x 222 /
+  // 151 / 115, 120 x 243 / 171 / 176, 250 x 290 / 243 / 299, 500 x 414 / 496 / 651.
   auto blocks = [&](int per) { return (long long)ds->n_tiles * ((n_pop + per - 1) / per); };
   int per = std::min(KC, 64);
   if (blocks(16) <= 256)

@@ -413,11 +413,11 @@ nep_status check_dataset(nep_ctx ctx, nep_dataset ds) {
 // per atom and individual), site energies and per-structure squared errors.
 hipError_t ensure_population(nep_dataset ds, int n_pop) {
   const int N = ds->N, S = ds->S;
-  hipError_t e = ds->dq.ensure((size_t)n_pop * N * 32);
+  hipError_t e = ds->dq.ensure((size_t)n_pop * population_rows(N) * 32);
   if (e == hipSuccess) e = ds->dqbound.ensure((size_t)n_pop);
   if (e == hipSuccess) e = ds->wfrag.ensure((size_t)n_pop * 12 * 64);
   if (e == hipSuccess) e = ds->wb2.ensure((size_t)n_pop);
-  if (e == hipSuccess) e = ds->U.ensure((size_t)n_pop * N);
+  if (e == hipSuccess) e = ds->U.ensure((size_t)n_pop * population_rows(N));
   if (e == hipSuccess) e = ds->struct_sq.ensure((size_t)n_pop * 3 * S);
   return e;
 }
