@@ -685,7 +685,7 @@ __global__ __launch_bounds__(64 * kImageWaves) void k_build_all_pairs(
     uint32_t* __restrict__ nl_rm, int* __restrict__ cnt_r, int* __restrict__ cnt_a,
     int* __restrict__ flags) {
   __shared__ uint32_t stash[kImageWaves][kImageStash];
-  const int w = (int)threadIdx.x / 64;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);  // uniform in the wave
   const int i = (int)(blockIdx.x * (blockDim.x / 64)) + w;
   if (i >= n) return;  // whole waves leave together
   const ImageList l = scan_images(n, cap, i, 0, n, pos, wrap, box.h, box.hinv, k0, k1, k2, rc2_r,

@@ -311,8 +311,10 @@ __device__ __forceinline__ double list_r2_shifted(double xj, double yj, double z
 // (only atoms within three cells of each other make entries), so the exact
 // test sees every image it would keep.  Testing all
 // (2K+1)^3 images in two passes, one per list part, took 97 us on the 216-atom
-// cell (now 9.6 us), 419 us on 64 structures of 8-256 atoms (now 36 us) and
-// 3.2 ms on 128 structures of 64-512 atoms (now 0.18 ms).
+// cell (now 8.8 us), 419 us on 64 structures of 8-256 atoms (now 28 us) and
+// 3.2 ms on 128 structures of 64-512 atoms (now 0.13 ms).  The atom is uniform
+// in the wave, so that the callers pass i and the cell in scalar registers (95
+// vector registers instead of 154; 33 us on the 64 structures).
 //
 // stash: kImageStash words of LDS of this wave, where radial-only entries wait
 // for the number of angular ones; an atom with more of them scans once more.
@@ -353,22 +355,22 @@ __device__ __forceinline__ ImageList scan_images(
   auto scan = [&](int radial) {
     int na = 0, nr = 0;
     double nx, ny, nz;
-    int nw[3];
+    int nw0, nw1, nw2;
     auto request = [&](int t) {  // the positions of the lane's next atom
       const int j = j0 + (t < nj ? t : 0);
       nx = pos[j];
       ny = pos[n + j];
       nz = pos[2 * n + j];
-      nw[0] = wrap[j];
-      nw[1] = wrap[n + j];
-      nw[2] = wrap[2 * n + j];
+      nw0 = wrap[j];
+      nw1 = wrap[n + j];
+      nw2 = wrap[2 * n + j];
     };
     request(lane);
     for (int base = 0; base < nj; base += 64) {
       const int t = base + lane;
       const int j = j0 + t;
       const double xj = nx, yj = ny, zj = nz;
-      const int wj[3] = {nw[0], nw[1], nw[2]};
+      const int wj[3] = {nw0, nw1, nw2};
       if (base + 64 < nj) request(t + 64);
       int lo[3], hi3[3];
 #pragma unroll
@@ -396,7 +398,9 @@ __device__ __forceinline__ ImageList scan_images(
             }
       };
       int ca = 0, cr = 0;  // the lane's entries of each part
+      uint32_t last = 0u;  // and the last of them
       images([&](uint32_t e, bool in_a) {
+        last = e;
         ca += in_a ? 1 : 0;
         cr += in_a ? 0 : 1;
         if (rcr2 > 0.f && radial == 0) {
@@ -418,30 +422,35 @@ __device__ __forceinline__ ImageList scan_images(
       }
       const int total = __shfl(sum, 63, 64);
       int sa = na + ((sum - own) & 0xFFFF), sr = nr + ((sum - own) >> 16);
-      if (own)
-        images([&](uint32_t e, bool in_a) {
-          if (in_a) {
-            if (radial == 0) {
-              if (sa < cap) {
-                nl[(size_t)sa * n + i] = e;
-                if (nl_rm) nl_rm[(size_t)i * cap + sa] = e;
-              } else {
-                out.overflow = true;
-              }
-            }
-            ++sa;
-          } else {
-            if (radial == 0) {
-              if (sr < kImageStash) stash[sr] = e;
-            } else if (out.na + sr < cap) {
-              nl[(size_t)(out.na + sr) * n + i] = e;
-              if (nl_rm) nl_rm[(size_t)i * cap + out.na + sr] = e;
+      auto emit = [&](uint32_t e, bool in_a) {
+        if (in_a) {
+          if (radial == 0) {
+            if (sa < cap) {
+              nl[(size_t)sa * n + i] = e;
+              if (nl_rm) nl_rm[(size_t)i * cap + sa] = e;
             } else {
               out.overflow = true;
             }
-            ++sr;
           }
-        });
+        } else {
+          if (radial == 0) {
+            if (sr < kImageStash) stash[sr] = e;
+          } else if (out.na + sr < cap) {
+            nl[(size_t)(out.na + sr) * n + i] = e;
+            if (nl_rm) nl_rm[(size_t)i * cap + out.na + sr] = e;
+          } else {
+            out.overflow = true;
+          }
+        }
+        sa += in_a ? 1 : 0;
+        sr += in_a ? 0 : 1;
+      };
+      // one image inside the cutoff (all there are in cells wider than two
+      // cutoffs) needs no second look at the images
+      if (ca + cr == 1)
+        emit(last, ca == 1);
+      else if (own)
+        images(emit);
       na += total & 0xFFFF;
       nr += total >> 16;
     }

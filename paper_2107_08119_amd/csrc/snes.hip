@@ -62,7 +62,8 @@ __global__ __launch_bounds__(64 * kImageWaves) void k_ds_build(
     int* __restrict__ n_in, int* __restrict__ n_ang, unsigned long long* __restrict__ totals,
     int* __restrict__ flags) {
   __shared__ uint32_t stash[kImageWaves][kImageStash];
-  const int w = (int)threadIdx.x / 64;
+  // uniform in the wave: the cell and the atom's own values stay in scalar registers
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int i = (int)(blockIdx.x * (blockDim.x / 64)) + w;
   if (blockIdx.x == 0 && threadIdx.x < 2) totals[threadIdx.x] = 0;
   if (i >= N) return;  // whole waves leave together
