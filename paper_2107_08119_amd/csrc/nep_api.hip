@@ -78,13 +78,19 @@ nep_status synchronize_flags(nep_ctx ctx, unsigned long long* pairs) {
   const int* h = ctx->flags_host;
   nep_status st = check_hip(ctx,
                             hipMemcpyAsync(ctx->flags_host, ctx->flags.ptr,
-                                           sizeof(int) * kFlagWords, hipMemcpyDeviceToHost,
+                                           sizeof(int) * (pairs ? kFlagWords : kPairTotals),
+                                           hipMemcpyDeviceToHost,
                                            ctx->stream),
                             "reading device flags");
   if (st != NEP_OK) return st;
   st = check_hip(ctx, hipStreamSynchronize(ctx->stream), "synchronizing");
   if (st != NEP_OK) return st;
-  if (pairs) std::memcpy(pairs, h + kPairTotals, 2 * sizeof(*pairs));
+  for (int k = 0; pairs && k < kPairSlots; ++k) {
+    unsigned long long part[2];
+    std::memcpy(part, h + kPairTotals + 16 * k, sizeof(part));
+    pairs[0] += part[0];
+    pairs[1] += part[1];
+  }
   int any = 0;
   for (int k = 0; k < kNumFlags; ++k) any |= h[k];
   if (any) {

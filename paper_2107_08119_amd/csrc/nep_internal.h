@@ -100,9 +100,11 @@ enum Flag {
   kFlagSkin = 4,  // an evaluation saw an atom more than skin/2 from its list-build position
   kNumFlags = 5
 };
-// Words of the flag buffer; the 64-bit totals of a dataset's pairs lie at word
-// kPairTotals, so that one copy brings both to the host.
-constexpr int kPairTotals = 8, kFlagWords = 12;
+// Words of the flag buffer.  The totals of a dataset's pairs follow the flags,
+// so that one copy brings both to the host: kPairSlots places of one cache line,
+// each two 64-bit partial totals, so that the additions of many blocks do not
+// wait for each other (240 blocks on one place took 6 us).
+constexpr int kPairTotals = 16, kPairSlots = 32, kFlagWords = kPairTotals + 16 * kPairSlots;
 
 // 1 eV/A acting on 1 amu, in A/fs^2; and 1 amu A^2/fs^2 in eV.
 constexpr double kAccel = 1.602176634e-19 / 1.66053906660e-27 * 1.0e-10;
@@ -243,7 +245,7 @@ struct nep_ctx_s {
   nep::DevBuf<double> species_wd;  // [n] sqrt(atomic number)
   nep::DevBuf<double> masses;     // [n] amu
   nep::DevBuf<double> totals;     // [16]
-  nep::DevBuf<int> flags;         // [kFlagWords]: kNumFlags flags, two 64-bit pair totals
+  nep::DevBuf<int> flags;         // [kFlagWords]: kNumFlags flags, partial pair totals
   int* flags_host = nullptr;      // [kFlagWords], pinned: their copy at a synchronization
   // molecular dynamics state
   bool md_forces_valid = false;
@@ -383,7 +385,8 @@ hipError_t unpack_neighbors(nep_ctx ctx, int* nbr, int* img, int* cnt_r, int* cn
 // nl_rm: the same entries per atom, [n][cap].
 void launch_reverse(nep_ctx ctx, int n, int cap, const uint32_t* nl, const uint32_t* nl_rm,
                     const int* cnt_r, const int* cnt_a, int* rev, const int* n_in = nullptr,
-                    const int* n_ang = nullptr, unsigned long long* totals = nullptr);
+                    const int* n_ang = nullptr, unsigned long long* totals = nullptr,
+                    bool last = false);
 
 // force.hip
 bool have_force_variant(const nep_hyper& h);

@@ -52,7 +52,7 @@ __global__ void k_ds_wrap(int N, const double* src, double* pos, const double* _
 
 // One wave per atom over the atoms of its structure and their lattice images
 // (scan_images), with the pairs inside the cutoffs counted per atom as
-// k_pair_classes does.  Also clears the two pair totals.
+// k_pair_classes does.  Also clears the pair totals.
 __global__ __launch_bounds__(64 * kImageWaves) void k_ds_build(
     int N, int cap, const double* __restrict__ pos, const double* __restrict__ boxes,
     const double* __restrict__ boxinv, const int* __restrict__ struct_of,
@@ -65,7 +65,8 @@ __global__ __launch_bounds__(64 * kImageWaves) void k_ds_build(
   // uniform in the wave: the cell and the atom's own values stay in scalar registers
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int i = (int)(blockIdx.x * (blockDim.x / 64)) + w;
-  if (blockIdx.x == 0 && threadIdx.x < 2) totals[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < kPairSlots)
+    totals[8 * threadIdx.x] = totals[8 * threadIdx.x + 1] = 0;
   if (i >= N) return;  // whole waves leave together
   const int s = struct_of[i];
   ImageList l = scan_images(N, cap, i, off[s], off[s + 1] - off[s], pos, wrap,
