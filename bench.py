@@ -60,11 +60,11 @@ BYTE_ATOM, BYTE_SLOT = 36, 28
 # tile shape (lanes per atom: FETCH_SIZE, WRITE_SIZE).  They hold only for the
 # kernel sources they were taken with (hash below); otherwise, or for a tile
 # without an entry, the bench reports traffic null.
-COUNTERS = {"sources_sha256": "bb68c64c1c1252629b018d61938ea9669370a28693b87a7445000bca64b64e45",
+COUNTERS = {"sources_sha256": "bf695d50f641166aefc4c9a541f1d1e82c5011be1e840a81d87eb50fca95d777",
             "kib": {
-                    "2": [12099.1, 81810.2],
-                    "4": [10776.8, 76409.1],
-                    "8": [10932.5, 76255.0]}}
+                    "2": [12109.9, 83825.9],
+                    "4": [10802.8, 75784.1],
+                    "8": [10915.6, 76234.3]}}
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 KERNEL_SOURCES = ["force.hip", "nep_terms.h", "nep_device.h", "nep_internal.h"]
 
@@ -232,7 +232,7 @@ def paper_model_rate(nep, I, torch, steps=100):
     cases.append(("pbte_41_40_1_8000", nep.hyper(8.0, 4.0, 12, 6, 4, 40), pos, box, (Z, masses),
                   150.0, 0.05))
     out = {"workload": "the paper's speed test in kind: %d NVE steps, dt 1 fs, rebuild every 10 "
-                       "steps, for the three models of Table I (one-wave-per-atom kernel with "
+                       "steps, for the three models of Table I (general kernel with "
                        "each model's sizes compiled in)" % steps,
            "paper_v100_atom_steps_per_s": ">1e7 for each (context: another GPU)"}
     for name, h, pos, box, species, mass, std in cases:
