@@ -256,12 +256,17 @@ __global__ void k_snes_sample(int n_par, const float* __restrict__ m, const floa
 }
 
 // Every block ranks the population itself (P <= 1024), then updates its
-// share of the parameters.
+// share of the parameters.  With a counter, the first block also closes the
+// generation g = counter[0]: best[(g - counter[1]) 6 + q] (unless NULL) are the
+// loss terms of the first rank (NaN ranks last, ties by index), and counter[0]
+// becomes g + 1 (a launch of its own took 4 us of a generation).
 __global__ __launch_bounds__(kBlock) void k_snes_update(int n_par, int n_pop, float* __restrict__ m,
                                                         float* __restrict__ s,
                                                         const float* __restrict__ r,
                                                         const double* __restrict__ loss,
-                                                        double eta_m, double eta_s) {
+                                                        double eta_m, double eta_s,
+                                                        int* __restrict__ counter,
+                                                        double* __restrict__ best) {
 #pragma clang fp contract(off)
   __shared__ int order[1024];
   __shared__ double util[1024];
@@ -293,6 +298,11 @@ __global__ __launch_bounds__(kBlock) void k_snes_update(int n_par, int n_pop, fl
   __syncthreads();
   for (int k = threadIdx.x; k < n_pop; k += blockDim.x) util[k] = util[k] / tot_s - 1.0 / n_pop;
   __syncthreads();
+  if (counter && blockIdx.x == 0 && threadIdx.x < 64) {  // one wave: it reads, then writes
+    const int g = counter[0], l = threadIdx.x;
+    if (best && l < 6) best[(size_t)(g - counter[1]) * 6 + l] = loss[6 * order[0] + l];
+    if (l == 0) counter[0] = g + 1;
+  }
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n_par) return;
   double gm = 0.0, gs = 0.0;
@@ -307,41 +317,6 @@ __global__ __launch_bounds__(kBlock) void k_snes_update(int n_par, int n_pop, fl
   const double sv = (double)s[v];
   m[v] = (float)((double)m[v] + eta_m * sv * gm);
   s[v] = (float)(sv * exp(0.5 * eta_s * gs));
-}
-
-// One wave: best[(g - g0) 6 + q] = loss terms of the best individual of
-// generation g = counter[0] (NaN ranks last, ties by index), g0 = counter[1];
-// then counter[0] = g + 1.
-__global__ __launch_bounds__(64) void k_snes_record(int n_pop, const double* __restrict__ loss,
-                                                    int* __restrict__ counter,
-                                                    double* __restrict__ best) {
-  if (blockIdx.x != 0) return;
-  const int l = threadIdx.x;
-  const int g = counter[0];
-  if (best) {
-    // lane minima over k = l, l + 64, ..., then the wave's (loss, index) minimum
-    double lb = INFINITY;
-    int b = n_pop;
-    for (int k = l; k < n_pop; k += 64) {
-      const double lk = loss[6 * k] != loss[6 * k] ? INFINITY : loss[6 * k];
-      if (lk < lb || (lk == lb && k < b)) {
-        lb = lk;
-        b = k;
-      }
-    }
-    for (int d = 32; d > 0; d >>= 1) {
-      const double lo = __shfl_xor(lb, d, 64);
-      const int bo = __shfl_xor(b, d, 64);
-      if (lo < lb || (lo == lb && bo < b)) {
-        lb = lo;
-        b = bo;
-      }
-    }
-    if (b >= n_pop) b = 0;  // every loss NaN: the first individual
-    if (l < 6) best[(size_t)(g - counter[1]) * 6 + l] = loss[6 * b + l];
-  }
-  __syncthreads();  // every lane has read the counter
-  if (l == 0) counter[0] = g + 1;
 }
 
 __global__ void k_set_counter(int* __restrict__ counter, int g) {
@@ -748,7 +723,8 @@ nep_status snes_update(nep_ctx ctx, int n_par, int n_pop, float* m_dev, float* s
   hipError_t e = hipSuccess;
   {
     launch_kernel(ctx, true, true, k_snes_update, dim3(blocks_for(n_par, kBlock)), dim3(kBlock),
-                  n_par, n_pop, m_dev, s_dev, r_dev, loss_dev, eta_m, eta_s);
+                  n_par, n_pop, m_dev, s_dev, r_dev, loss_dev, eta_m, eta_s, (int*)nullptr,
+                  (double*)nullptr);
     e = hipGetLastError();
   }
   return check_hip(ctx, e, "launching the SNES update");
@@ -871,9 +847,7 @@ nep_status snes_run(nep_ctx ctx, nep_dataset ds, int n_par, int n_pop, float* m_
                                               ds->pop_variant);
       launch_kernel(ctx, false, false, k_snes_update, dim3(blocks_for(n_par, kBlock)),
                     dim3(kBlock), n_par, n_pop, m_dev, s_dev, (const float*)r_dev,
-                    (const double*)loss_dev, eta_m, eta_s);
-      launch_kernel(ctx, false, false, k_snes_record, dim3(1), dim3(64), n_pop,
-                    (const double*)loss_dev, ctx->gen_counter.ptr, best_dev);
+                    (const double*)loss_dev, eta_m, eta_s, ctx->gen_counter.ptr, best_dev);
       if (le == hipSuccess) le = hipGetLastError();
       hipGraph_t graph = nullptr;
       e = hipStreamEndCapture(cap, &graph);
