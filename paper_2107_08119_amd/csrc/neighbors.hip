@@ -950,13 +950,20 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const
   const dim3 blk(kBlock);
   if (s.use_cells) {
     const int ncell = s.nc[0] * s.nc[1] * s.nc[2];
-    const int* cnt_before = s.cell_cnt.ptr;
+    const bool one_block = n <= kSortAtoms && ncell <= kSortCells;
+    // The counters of the multi-kernel sort are clear for cells_zeroed_for cells.
+    // They are grown only here, where growing them takes that back (memory just
+    // allocated holds anything): k_sort_small leaves them alone.
+    if (!one_block) {
+      if ((size_t)ncell > s.cell_cnt.size) s.cells_zeroed_for = -1;
+      if ((e = s.cell_cnt.ensure(ncell)) != hipSuccess ||
+          (e = s.scan_part.ensure(1024)) != hipSuccess ||
+          (e = s.cell_fill.ensure(ncell)) != hipSuccess ||
+          (e = s.cell_atoms.ensure(n)) != hipSuccess)
+        return check_hip(ctx, e, "allocating cell lists");
+    }
     if ((e = s.nl_rm.ensure(ncap)) != hipSuccess || (e = s.cell_of.ensure(n)) != hipSuccess ||
-        (e = s.cell_cnt.ensure(ncell)) != hipSuccess ||
-        (e = s.scan_part.ensure(1024)) != hipSuccess ||
         (e = s.cell_start.ensure((size_t)ncell + 1)) != hipSuccess ||
-        (e = s.cell_fill.ensure(ncell)) != hipSuccess ||
-        (e = s.cell_atoms.ensure(n)) != hipSuccess ||
         (e = s.cell_rec.ensure(n)) != hipSuccess ||
         (e = s.pos_t.ensure((size_t)3 * n)) != hipSuccess ||
         (e = s.vel_t.ensure((size_t)3 * n)) != hipSuccess ||
@@ -968,13 +975,13 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const
                         s.iperm.ptr,  s.cell_t.ptr,
                         s.cell_rec.ptr, s.pos_ref.ptr,
                         ctx->flags.ptr};
-    if (n <= kSortAtoms && ncell <= kSortCells) {
+    if (one_block) {
       launch_kernel(ctx, true, false, k_sort_small, dim3(1), dim3(kSortThreads), n, ncell, src,
                     vel_src, (const double*)s.pos_s.ptr, (const double*)s.vel_s.ptr,
                     (const int*)s.perm.ptr, s.box, s.nc[0], s.nc[1], s.nc[2],
                     wrap_in_place ? 1 : 0, s.cell_start.ptr, sorted);
     } else {
-      const bool zero = s.cell_cnt.ptr != cnt_before || s.cells_zeroed_for != ncell;
+      const bool zero = s.cells_zeroed_for != ncell;
       if (zero)
         launch_kernel(ctx, true, false, k_zero, dim3(blocks_for(ncell, kBlock)), blk,
                       s.cell_cnt.ptr, ncell);
@@ -995,7 +1002,7 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const
         launch_kernel(ctx, false, false, k_scan, dim3(1), dim3(1024), ncell, s.cell_cnt.ptr,
                       s.cell_start.ptr, s.cell_fill.ptr);
       }
-      s.cells_zeroed_for = ncell;
+      s.cells_zeroed_for = ncell;  // the scan cleared what k_bin counted
       launch_kernel(ctx, false, false, k_fill, dim3(blocks_for(n, kBlock)), blk, n,
                     (const int*)s.cell_of.ptr, (const int*)s.cell_start.ptr, s.cell_fill.ptr,
                     s.cell_atoms.ptr);
@@ -1034,7 +1041,9 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const
   }
   launch_reverse(ctx, n, s.cap, s.nl.ptr, s.nl_rm.ptr, s.cnt_r.ptr, s.cnt_a.ptr, s.rev.ptr,
                  nullptr, nullptr, nullptr, true);
-  return check_hip(ctx, hipGetLastError(), "launching neighbour kernels");
+  e = hipGetLastError();
+  if (e != hipSuccess) s.cells_zeroed_for = -1;  // a scan that did not run cleared nothing
+  return check_hip(ctx, e, "launching neighbour kernels");
 }
 
 }  // namespace nep
