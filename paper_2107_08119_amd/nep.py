@@ -412,6 +412,7 @@ class Context:
 
     def dataset_set_positions(self, ds: "Dataset", pos: torch.Tensor) -> None:
         _require(pos, torch.float64, (3, ds.n_atoms), "pos")
+        ds._held = None  # whatever it held is replaced, also where the call fails
         self._check(self._lib.nep_dataset_set_positions(self._h, ds._h, _ptr(pos)))
 
     def dataset_compute(self, ds: "Dataset", z: torch.Tensor, virial: bool = False) -> dict:
@@ -488,7 +489,19 @@ class Dataset:
 
     def __init__(self, ctx: Context, handle, n_struct: int, n_atoms: int):
         self.ctx, self._h, self.n_struct, self.n_atoms = ctx, handle, n_struct, n_atoms
-        self._pos_key = None  # (data pointer, version) of the positions last uploaded
+        self._held = None  # positions that NEPEnergy uploaded last and their version then
+
+    def _holds(self, pos: torch.Tensor) -> bool:
+        """Whether the dataset's positions are those of `pos` as it is now.  The
+        uploaded tensor is kept alive, so that another one cannot come to lie
+        at its address, and both version counters are compared, so that a
+        change in place of either is seen."""
+        if self._held is None:
+            return False
+        held, version = self._held
+        return (held.data_ptr() == pos.data_ptr() and held.dtype == pos.dtype
+                and held.shape == pos.shape and held.stride() == pos.stride()
+                and held._version == version == pos._version)
 
     def pairs(self) -> tuple[int, int]:
         """Ordered pairs inside the radial and inside the angular cutoff."""
@@ -500,6 +513,7 @@ class Dataset:
         if getattr(self, "_h", None):
             self.ctx._lib.nep_dataset_destroy(self._h)
             self._h = None
+            self._held = None
 
     def __del__(self):
         try:
@@ -562,13 +576,19 @@ class NEPEnergy(torch.autograd.Function):
     hand-written gradient: dG/dz for G = sum gE.E + sum gF.F, and the position
     gradient of the energy part, -gE F.  The position gradient of the force
     part would need second derivatives of U and raises NotImplementedError.
+
+    Positions are uploaded when they are new: another tensor than in the last
+    call, or changed in place since then as the tensor's version counter tells.
+    A change that the counter does not see (through ``pos.data``, or by a kernel
+    of another library) has to be followed by ``ctx.dataset_set_positions``.
     """
 
     @staticmethod
     def forward(actx, pos, z, ctx, ds):
-        if ds._pos_key != (pos.data_ptr(), pos._version):
-            ctx.dataset_set_positions(ds, pos.detach())
-            ds._pos_key = (pos.data_ptr(), pos._version)
+        if not ds._holds(pos):
+            alias = pos.detach()  # the same memory and version counter, no graph
+            ctx.dataset_set_positions(ds, alias)
+            ds._held = (alias, alias._version)
         out = ctx.dataset_compute(ds, z.detach())
         actx.save_for_backward(z, out["F"])
         actx.nep = (ctx, ds)
