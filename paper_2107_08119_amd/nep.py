@@ -481,6 +481,9 @@ class Context:
             self._check(self._lib.nep_md_step_driven(
                 self._h, n_steps, dt, rebuild_every, mass, f.ctypes.data, _ptr(pos), _ptr(vel),
                 _ptr(thermo), _ptr(W), _ptr(J)))
+        # torch does not see the library's writes: without this, NEPEnergy would
+        # take the moved positions for the ones it has
+        torch.autograd.graph.increment_version((pos, vel))
         return thermo
 
 

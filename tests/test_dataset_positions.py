@@ -27,6 +27,10 @@ class _Lib:
         F.copy_(-self.pos)
         return 0
 
+    def nep_md_step(self, h, steps, dt, every, mass, pos, vel, thermo, W, J):
+        pos.numpy()[:] += 1.0  # unseen by the version counter, as a kernel's writes
+        return 0
+
     def nep_last_error(self, h):
         return b"list overflow"
 
@@ -67,6 +71,15 @@ def test_positions_set_directly_or_in_place(held):
     with torch.no_grad():
         p.add_(2.0)
     assert energy(p, z, ctx, ds) == float(p.detach().sum())
+
+
+def test_positions_moved_by_md(held):
+    ctx, ds, z = held
+    ctx.n = N
+    p = base()
+    energy(p, z, ctx, ds)
+    ctx.md_step(2, 1.0, 10, 28.0, p, torch.zeros_like(p))
+    assert energy(p, z, ctx, ds) == float(p.sum())
 
 
 def test_failed_upload_is_not_taken_for_the_one_before(held):
