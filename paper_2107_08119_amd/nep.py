@@ -7,6 +7,7 @@ or ``python -m paper_2107_08119_amd.build``); nothing falls back to the CPU.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import os
 
@@ -506,6 +507,28 @@ class Dataset:
                 and held.shape == pos.shape and held.stride() == pos.stride()
                 and held._version == version == pos._version)
 
+    @contextlib.contextmanager
+    def _at(self, held):
+        """The dataset at the positions `held` = (tensor, version) of an earlier
+        call: as they are where no other positions have come since, else the
+        earlier ones are uploaded again for the time being."""
+        now = self._held
+        if now is held or (now is not None and now[0].data_ptr() == held[0].data_ptr()
+                           and now[1] == held[1]):
+            yield
+            return
+        if held[0]._version != held[1]:
+            raise RuntimeError("positions of an earlier NEPEnergy call were changed in place and "
+                               "the dataset has other ones: its parameter gradient is lost")
+        same = now is not None and now[0]._version == now[1]
+        back = now[0] if same else self.ctx.dataset_positions(self)
+        self.ctx.dataset_set_positions(self, held[0])
+        try:
+            yield
+        finally:
+            self.ctx.dataset_set_positions(self, back)
+            self._held = now
+
     def pairs(self) -> tuple[int, int]:
         """Ordered pairs inside the radial and inside the angular cutoff."""
         r, a = C.c_longlong(), C.c_longlong()
@@ -594,7 +617,7 @@ class NEPEnergy(torch.autograd.Function):
             ds._held = (alias, alias._version)
         out = ctx.dataset_compute(ds, z.detach())
         actx.save_for_backward(z, out["F"])
-        actx.nep = (ctx, ds)
+        actx.nep = (ctx, ds, ds._held)
         actx.set_materialize_grads(False)
         actx.pos_needs_grad = pos.requires_grad
         return out["E"], out["F"]
@@ -602,7 +625,7 @@ class NEPEnergy(torch.autograd.Function):
     @staticmethod
     def backward(actx, gE, gF):
         z, F = actx.saved_tensors
-        ctx, ds = actx.nep
+        ctx, ds, held = actx.nep
         # an output that the objective does not use has no gradient here (None):
         # filling one with zeros and reading back whether it is zero took a
         # quarter of an energy-and-gradient call on 64 structures
@@ -612,7 +635,8 @@ class NEPEnergy(torch.autograd.Function):
             raise NotImplementedError("position gradient of the force part needs the Hessian")
         if not actx.needs_input_grad[1]:  # only the positions' gradient is asked for
             return ctx._position_gradient(ds, gE, F), None, None, None
-        g = ctx.dataset_backward(ds, z.detach(), gE, gF, F, want_pos=actx.pos_needs_grad)
+        with ds._at(held):
+            g = ctx.dataset_backward(ds, z.detach(), gE, gF, F, want_pos=actx.pos_needs_grad)
         return g.get("pos"), g["z32"], None, None
 
 

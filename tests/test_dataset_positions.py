@@ -27,6 +27,13 @@ class _Lib:
         F.copy_(-self.pos)
         return 0
 
+    def nep_dataset_backward(self, h, d, z, gE, gF, F, gpos, gz, gz32):
+        gz.fill_(self.pos.sum() * gE.sum())
+        gz32.copy_(gz)
+        if gpos is not None:
+            gpos.copy_(-gE.sum() * F)
+        return 0
+
     def nep_md_step(self, h, steps, dt, every, mass, pos, vel, thermo, W, J):
         pos.numpy()[:] += 1.0  # unseen by the version counter, as a kernel's writes
         return 0
@@ -41,6 +48,7 @@ def held(monkeypatch):
     ctx = nep.Context.__new__(nep.Context)
     ctx._lib, ctx._h, ctx.device, ctx.hyper = _Lib(), None, "cpu", nep.hyper()
     ds = nep.Dataset(ctx, None, 2, N)
+    monkeypatch.setattr(ctx, "dataset_positions", lambda ds: ctx._lib.pos.clone(), raising=False)
     z = torch.zeros(nep.num_params(ctx.hyper))
     yield ctx, ds, z
 
@@ -100,3 +108,34 @@ def test_unchanged_positions_are_uploaded_once(held):
     assert ctx._lib.uploads == 1
     with pytest.raises(ValueError):
         energy(p.detach().view(N, 3), z, ctx, ds)
+
+
+@pytest.mark.parametrize("later", ["frame", "set", "back"])
+def test_parameter_gradient_at_the_positions_of_its_call(held, later):
+    ctx, ds, z = held
+    z.requires_grad_()
+    p, q = base(), base() + 2.0
+    E = nep.NEPEnergy.apply(p, z, ctx, ds)[0]
+    if later == "set":
+        ctx.dataset_set_positions(ds, q)
+    else:  # "back": another frame and the first one again
+        for frame in ((q,) if later == "frame" else (q, p)):
+            nep.NEPEnergy.apply(frame, z, ctx, ds)
+    now = ctx._lib.pos.clone()
+    E.sum().backward()
+    assert float(z.grad[0]) == float((p.sum() * len(E)).float())
+    assert torch.equal(ctx._lib.pos, now)  # the dataset is left as it was
+
+
+def test_parameter_gradient_of_positions_that_are_gone(held):
+    ctx, ds, z = held
+    z.requires_grad_()
+    p = base()
+    E = nep.NEPEnergy.apply(p, z, ctx, ds)[0]
+    want = float((p.sum() * len(E)).float())
+    p.add_(1.0)
+    E.sum().backward(retain_graph=True)  # the dataset still has the first ones
+    assert float(z.grad[0]) == want
+    nep.NEPEnergy.apply(p, z, ctx, ds)
+    with pytest.raises(RuntimeError, match="in place"):
+        E.sum().backward()
