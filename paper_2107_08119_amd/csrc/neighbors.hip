@@ -17,6 +17,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "cell_grid.h"
 #include "nep_device.h"
 
 namespace nep {
@@ -149,7 +150,8 @@ __global__ __launch_bounds__(1024) void k_scan(int m, int* __restrict__ cnt,
 // The same scan for many cells in three launches: block b scans counts
 // [1024 b, 1024 b + 1024) (k_scan_blocks), one block scans the block totals
 // (k_scan_totals), every block adds its offset and clears the counters
-// (k_scan_add).
+// (k_scan_add).  At most 1,024 block totals (kMaxCells).
+static_assert(kMaxCells <= 1024 * 1024, "one block scans the block totals");
 __device__ __forceinline__ int block_exclusive_scan_1024(int v, int* part, int& total) {
   const int t = threadIdx.x;
   part[t] = v;
@@ -923,15 +925,12 @@ void prepare_system_geometry(System& s, const double* H, double rc_r, double rc_
     return std::sqrt(x * x + y * y + z * z);
   };
   const double width[3] = {vol / cross_norm(B, C), vol / cross_norm(C, A), vol / cross_norm(A, B)};
-  s.use_cells = true;
+  s.use_cells = cell_counts(width, s.rc_list_r, s.nc);
   for (int ax = 0; ax < 3; ++ax) {
-    s.nc[ax] = (int)std::floor(width[ax] / (s.rc_list_r * (1.0 + 1e-9)));
-    if (s.nc[ax] < 3) s.use_cells = false;
     // wrapped fractional differences lie in (-1, 1); a neighbour needs
     // |ds + m| <= rc/width
     s.kimg[ax] = (int)std::floor(1.0 + s.rc_list_r / width[ax] * (1.0 + 1e-12) + 1e-12);
   }
-  if (!s.use_cells) s.nc[0] = s.nc[1] = s.nc[2] = 1;
 }
 
 nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const double* src,
@@ -990,7 +989,7 @@ nep_status build_neighbors(nep_ctx ctx, bool wrap_in_place, bool have_vel, const
                     s.nc[2], 1, wrap_in_place ? 1 : 0, s.wrap.ptr, s.cell_of.ptr, s.cell_cnt.ptr,
                     (float*)nullptr);
       const int nsb = (ncell + 1023) / 1024;
-      if (ncell > 1024 * kScanChunks && nsb <= 1024) {
+      if (ncell > 1024 * kScanChunks) {  // nsb <= 1024 (kMaxCells)
         launch_kernel(ctx, false, false, k_scan_blocks, dim3(nsb), dim3(1024), ncell,
                       (const int*)s.cell_cnt.ptr, s.cell_start.ptr, s.scan_part.ptr);
         launch_kernel(ctx, false, false, k_scan_totals, dim3(1), dim3(1024), nsb, ncell,
