@@ -452,10 +452,13 @@ nep_status nep_time_partials(nep_ctx ctx, const double* pos_dev, int reps, doubl
  * HIP events on the context's stream in three interleaved rounds of `reps`
  * launches per shape (1..10000), so that a clock that settles during the
  * calls weighs on every shape alike, and keeps the shape with the fastest
- * round for later nep_compute / nep_md_step calls.  Host outputs (either may
- * be NULL): *lanes_out = chosen lanes per atom; ms_out[3] = mean ms per
- * launch of each shape's fastest round, in the order above.  Needs loaded
- * parameters and a neighbour list; waits for the stream. */
+ * round for later nep_compute / nep_md_step calls.  In small systems (up to
+ * 4,096 atoms) the kernel of every model size is timed beside them, and where
+ * it is faster than each the context keeps its choice by system size.  Host
+ * outputs (either may be NULL): *lanes_out = lanes per atom of the fastest of
+ * the three shapes; ms_out[3] = mean ms per launch of each shape's fastest
+ * round, in the order above.  Needs loaded parameters and a neighbour list;
+ * waits for the stream. */
 nep_status nep_autotune(nep_ctx ctx, const double* pos_dev, int reps, int* lanes_out,
                         double* ms_out);
 

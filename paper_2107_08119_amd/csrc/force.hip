@@ -591,7 +591,7 @@ void launch_partials_shape(nep_ctx ctx, const double* pos, bool first, bool last
 // 8.9 with the kernel of every model size (one atom per wave), 14.6 with 8
 // lanes, 18.5 with 4; 4,096 atoms 13.5, 15.0 and 19.0; 8,000 atoms 16.6, 15.7
 // and 19.7; 17,576 atoms 39.4, 31.2 and 27.6.
-inline int default_variant(int n) { return n <= 16 * 256 ? 3 : (n <= 32 * 256 ? 2 : 1); }
+int default_variant(int n) { return n <= 16 * 256 ? 3 : (n <= 32 * 256 ? 2 : 1); }
 
 hipError_t launch_partials(nep_ctx ctx, const double* pos, int variant) {
   const System& s = ctx->sys;

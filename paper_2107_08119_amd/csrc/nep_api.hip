@@ -517,11 +517,13 @@ nep_status nep_autotune(nep_ctx ctx, const double* pos_dev, int reps, int* lanes
   int best = ctx->md_variant;
   // other model sizes have one kernel only
   const int nv = have_training_variant(ctx->hyper) && !ctx->species_on() ? 3 : 1;
+  // where the choice by size is the kernel of every model size, that one too
+  const bool general = nv == 3 && default_variant(ctx->sys.n) == 3;
   // shapes timed in interleaved rounds; each keeps its fastest round
   constexpr int kRounds = 3;
-  double per[3] = {0.0, 0.0, 0.0};
+  double per[4] = {0.0, 0.0, 0.0, 0.0};
   for (int round = 0; round < kRounds && e == hipSuccess; ++round)
-    for (int v = 0; v < nv && e == hipSuccess; ++v) {
+    for (int v = 0; v < nv + (general ? 1 : 0) && e == hipSuccess; ++v) {
       if (round == 0) e = launch_partials(ctx, ctx->sys.pos_s.ptr, v);  // warm-up
       if (e == hipSuccess) e = hipEventRecord(a, ctx->stream);
       for (int r = 0; r < reps && e == hipSuccess; ++r)
@@ -544,7 +546,9 @@ nep_status nep_autotune(nep_ctx ctx, const double* pos_dev, int reps, int* lanes
   ctx->timer.on = timing;
   ctx->md_forces_valid = false;  // the partial forces were recomputed
   if (e != hipSuccess) return check_hip(ctx, e, "timing the partial-force kernel");
-  ctx->md_variant = nv == 3 ? best : 3;
+  // (-1, the choice by size, rather than that kernel: later systems on the
+  // context may be larger)
+  ctx->md_variant = nv != 3 ? 3 : (general && per[3] < per[best] ? -1 : best);
   if (lanes_out) *lanes_out = nv == 3 ? 2 << best : 64;
   return NEP_OK;
 }

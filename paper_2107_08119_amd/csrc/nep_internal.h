@@ -401,6 +401,8 @@ hipError_t launch_partials_generic(nep_ctx ctx, const double* pos);
 // lanes per atom, 3 = the kernel of every model size; -1 = the context's
 // choice).  Models other than the default sizes always use the latter.
 hipError_t launch_partials(nep_ctx ctx, const double* pos, int variant = -1);
+// The shape that the default model takes for n atoms without a choice.
+int default_variant(int n);
 // mode 0: plain evaluation (totals = E, W(9), J(3)); mode 1: velocity-Verlet
 // second half-kick fused (vel updated, thermo row written).
 // Pass 2 (k_gather, modes as documented there) writing per-block sums to

@@ -290,8 +290,9 @@ class Context:
 
     def autotune(self, pos: torch.Tensor, reps: int = 20):
         """Time the pass-1 tile shapes on the current system and keep the
-        fastest; returns (lanes per atom chosen, ms per launch of the 2-, 4-
-        and 8-lane shapes)."""
+        fastest (in small systems the choice by size where that is faster);
+        returns (lanes per atom of the fastest shape, ms per launch of the 2-,
+        4- and 8-lane shapes)."""
         _require(pos, torch.float64, (3, self.n), "pos")
         lanes = C.c_int(0)
         ms = (C.c_double * 3)()
