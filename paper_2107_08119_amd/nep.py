@@ -184,9 +184,28 @@ class Context:
         self.hyper = None
 
     def close(self):
+        """Free the context and, first, what was made on it and is still there."""
         if getattr(self, "_h", None):
+            for handle in list(self._owned()):
+                self._free(handle)
             self._lib.nep_destroy(self._h)
             self._h = None
+
+    # Handles made on the context (datasets, correlations) and the names of the
+    # calls that free them.  They are freed through the context, so that none outlives it:
+    # in a reference cycle the finalizers run in any order, and the context may
+    # be closed first.
+    def _owned(self) -> dict:
+        return self.__dict__.setdefault("_owned_handles", {})
+
+    def _own(self, handle, destroy):
+        if handle:
+            self._owned()[handle.value] = (handle, destroy)
+
+    def _free(self, value):
+        handle, destroy = self._owned().pop(value, (None, None))
+        if handle:
+            getattr(self._lib, destroy)(handle)
 
     def __del__(self):
         try:
@@ -495,6 +514,7 @@ class Dataset:
     def __init__(self, ctx: Context, handle, n_struct: int, n_atoms: int):
         self.ctx, self._h, self.n_struct, self.n_atoms = ctx, handle, n_struct, n_atoms
         self._held = None  # positions that NEPEnergy uploaded last and their version then
+        ctx._own(handle, "nep_dataset_destroy")
 
     def _holds(self, pos: torch.Tensor) -> bool:
         """Whether the dataset's positions are those of `pos` as it is now.  The
@@ -538,7 +558,7 @@ class Dataset:
 
     def close(self):
         if getattr(self, "_h", None):
-            self.ctx._lib.nep_dataset_destroy(self._h)
+            self.ctx._free(self._h.value)
             self._h = None
             self._held = None
 
@@ -557,6 +577,7 @@ class Correlation:
         h = C.c_void_p()
         ctx._check(ctx._lib.nep_vvcf_create(ctx._h, n_atoms, n_lags, C.byref(h)))
         self.ctx, self._h, self.n_atoms, self.n_lags = ctx, h, n_atoms, n_lags
+        ctx._own(h, "nep_vvcf_destroy")
 
     def sample(self, W: torch.Tensor, vel: torch.Tensor) -> None:
         """W [9][N] float32 and vel [3][N] float64 device tensors (caller order)."""
@@ -584,7 +605,7 @@ class Correlation:
 
     def close(self):
         if getattr(self, "_h", None):
-            self.ctx._lib.nep_vvcf_destroy(self._h)
+            self.ctx._free(self._h.value)
             self._h = None
 
     def __del__(self):
