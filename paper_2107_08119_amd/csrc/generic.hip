@@ -200,16 +200,12 @@ __device__ __forceinline__ void harmonics_d(double x, double y, double z, double
 #pragma pop_macro("NEP_S5")
 #pragma pop_macro("NEP_S3")
 
-// Radial basis g_n, n < nb (<= MB), and optionally g_n'.
+// Radial basis g_n, n < nb (<= MB), zero beyond.
 template <int MB>
-__device__ __forceinline__ void radial_basis_n(float r, float rc_inv, int nb, float* g, float* dg) {
-  float gg[MB], dd[MB];
-  radial_basis<MB, true>(r, rc_inv, gg, dd);
+__device__ __forceinline__ void radial_basis_n(float r, float rc_inv, int nb, float* g) {
+  radial_basis<MB, false>(r, rc_inv, g, nullptr);
 #pragma unroll
-  for (int n = 0; n < MB; ++n) {
-    g[n] = n < nb ? gg[n] : 0.f;
-    if (dg) dg[n] = n < nb ? dd[n] : 0.f;
-  }
+  for (int n = 0; n < MB; ++n) g[n] = n < nb ? g[n] : 0.f;
 }
 
 // F64: the float64 descriptor and hidden-layer input of multicomponent
@@ -451,7 +447,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(F64
           for (int a = 0; a < MA; ++a) gn[a] *= w;
           harmonics_d(x * rinv, y * rinv, zz * rinv, yh);
         } else {
-          radial_basis_n<MA>(r, rca_inv, NA, gn, nullptr);
+          radial_basis_n<MA>(r, rca_inv, NA, gn);
           harmonics(x * rinv, y * rinv, zz * rinv, yh);
         }
       }
