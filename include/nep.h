@@ -312,9 +312,9 @@ void nep_dataset_destroy(nep_dataset ds);
  * where U_s and W_s = sum_i W_i are the NEP energy and virial of structure s.
  * All individuals are evaluated by the same two launches, on the matrix
  * cores: the network and dU/dq of every (individual, atom), then one block
- * per tile of whole structures that contracts the descriptor derivatives
- * cached when the dataset's positions were set (Sec. II D) with every
- * individual's dU/dq, gathers the forces in LDS and forms the squared errors.
+ * per tile of whole structures and group of individuals that contracts the
+ * descriptor derivatives cached for the dataset's positions (Sec. II D) with
+ * their dU/dq, gathers the forces in LDS and forms the squared errors.
  * Forces and structure virials are summed as 32-bit fixed point, round(x 2^e)
  * with e per (tile of structures, individual) chosen from a bound on
  * |dU/dq| so that no sum reaches 2^30 (each term then carries an absolute
@@ -324,9 +324,10 @@ void nep_dataset_destroy(nep_dataset ds);
  * a non-finite bound gives NaN losses.  The network kernel uses the shape
  * chosen by snes_autotune (by the number of atoms until then).  The dataset must
  * belong to ctx and match its hyperparameters.  NEP_EINVAL if a structure has
- * more than 13,312 atoms (the forces of one individual on one structure must
- * fit in 160 KB of LDS); more than 52 individuals per 256-atom structure
- * take one more contraction launch per 52. */
+ * more than 13,565 atoms (the forces of one individual on one structure must
+ * fit in 160 KB of LDS).  A group holds as many individuals as fit beside the
+ * largest structure, at most 64 (52 beside 256 atoms), and 32 or 16 where the
+ * tiles are few. */
 nep_status snes_eval_population(nep_ctx ctx, nep_dataset ds, int n_pop, const float* Z_dev,
                                 const double* lambda_host, double* loss_dev);
 

@@ -77,7 +77,8 @@ __device__ __forceinline__ void harmonics_along(float x, float y, float z, float
 // with dYhat_lm the derivative along (D - u (u.D)) / r: 2 multiply-adds per
 // (n, l, m) and one set of directional derivatives, where all three gradient
 // components per harmonic and 3 per (n, l, m) took 54 us on 36,863 atoms, now 50
-// (256 registers: two waves per SIMD, the last 64 of 576 blocks after the rest).
+// (256 registers and 11 spilled, 48 bytes of scratch per lane: two waves per SIMD,
+// the last 64 of 576 blocks after the rest).
 // Eight lanes per atom take as long (49 us; 21 against 23 on 7,700 atoms).
 constexpr int kStage = 40;
 template <int NR, int NA, int LMAX, int NNEU, int L>

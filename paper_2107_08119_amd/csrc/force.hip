@@ -39,10 +39,12 @@ constexpr int stage_slots(int atoms_per_block) {
 // MULTI: every atom has its own cell (struct_of[i] indexes boxes[][9]).
 // Bound: VALU issue (about 5,000 instructions per wave of 16 atoms with L = 4:
 // 830 for staging, 780 per atom between the loops, 265 per radial and angular
-// pair in the first loop and 450 in the second), two waves per SIMD.  With the
-// combined harmonic sums and Clenshaw's recurrence 49.5 us on 64,000 and 331 us
-// on 512,000 diamond atoms (L = 4), 51.9 and 338 us with every harmonic and
-// Chebyshev term written out.
+// pair in the first loop and 450 in the second), two waves per SIMD: 231 registers
+// and 59,624 bytes of LDS (L = 4; 215 and 69,864 with 2 lanes, 237 and 50,920 with
+// 8), none spilled.  With the combined harmonic sums and Clenshaw's recurrence
+// 49.5 us on 64,000 and 331 us on 512,000 diamond atoms (L = 4), 51.9 and 338 us
+// with every harmonic and Chebyshev term written out.  A third wave needs 32 staged
+// slots instead of 40 (51,432 bytes) and 168 registers: 44 spilled, 90.5 and 612 us.
 // Population: blockIdx.y selects parameter vector k at zpar + k*zstride and
 // its outputs at pin + k*pstride, fown + 3nk, U + nk.
 template <int NR, int NA, int LMAX, int NNEU, int L, bool MULTI>
@@ -587,10 +589,11 @@ void launch_partials_shape(nep_ctx ctx, const double* pos, bool first, bool last
 
 // Tile shape of the default model by the system's size: the most lanes per atom
 // whose blocks still find a compute unit each (256 of them), since below that a
-// wave's own chain sets the time.  Measured on diamond cells (us): 1,000 atoms
-// 8.9 with the kernel of every model size (one atom per wave), 14.6 with 8
-// lanes, 18.5 with 4; 4,096 atoms 13.5, 15.0 and 19.0; 8,000 atoms 16.6, 15.7
-// and 19.7; 17,576 atoms 39.4, 31.2 and 27.6.
+// wave's own chain sets the time; beyond, blocks that share a unit share its
+// vector units.  Measured on diamond cells (us), with the kernel of every model
+// size, 8 lanes and 4: 1,000 atoms 8.7, 14.2, 17.6; 4,096 atoms 13.4, 14.6, 18.2;
+// 5,832 atoms 16.2, 15.0, 18.6; 8,000 atoms 16.6, 15.4, 18.9; 10,648 atoms 26.6,
+// 20.8, 19.5; 13,824 atoms 29.2, 20.8, 19.8; 17,576 atoms 38.6, 30.4, 26.2.
 int default_variant(int n) { return n <= 16 * 256 ? 3 : (n <= 32 * 256 ? 2 : 1); }
 
 hipError_t launch_partials(nep_ctx ctx, const double* pos, int variant) {

@@ -6,9 +6,10 @@
 // The terms are those of nep_terms.h (factorised angular descriptor, network,
 // partial force of Sec. II D):
 //   * staging: the block reads the list and reverse slots of its atoms, 48
-//     (64) slots at a time with atoms fastest, classifies the pairs and packs those inside a cutoff per atom in LDS, angular ones first; the
-//     pair vectors r_ij go to the atom's own slots for pass 2 (systems of up
-//     to kPairVectorMaxAtoms atoms);
+//     (with one atom per wave 64) slots at a time with atoms fastest, classifies
+//     the pairs and packs those inside a cutoff per atom in LDS, angular ones
+//     first; the pair vectors r_ij go to the atom's own slots for pass 2 (systems
+//     of up to kPairVectorMaxAtoms atoms);
 //   * radial q_n: each lane adds f_c T_n of its pairs, the atom's lanes are
 //     summed in a fixed order, q_n = (R_n + R_0)/2 (g_n = f_c (T_n + 1)/2);
 //   * angular moments c_nlm = sum_j g_n(r_ij) Yhat_lm(u_ij): per atom the
@@ -27,7 +28,11 @@
 // wave per atom, with the contractions on the VALU from LDS, left most lanes
 // idle where an atom has fewer than 64 pairs (6 angular ones in PbTe): 63.0
 // against 27.4 us for 80-50-1 on 8,000 atoms, 527 against 213 us for PbTe on
-// 64,000 atoms.
+// 64,000 atoms.  Two blocks fit a compute unit: 76,160 bytes of LDS and 187
+// registers for 80-50-1, 70,848 bytes and 256 registers (4 spilled) for PbTe; the
+// runtime-sized float64 kernel with four atoms per wave takes 86,208 bytes, one
+// block per unit (34-24-1 with two species on 64,000 atoms 414 us, with one wave
+// per atom 1,538 us).
 //
 // Multicomponent systems take the descriptor and the hidden layer's input in
 // float64 (pair geometry, basis, harmonics, the sums q and c_nlm, and the
@@ -821,8 +826,9 @@ void launch_atoms(nep_ctx ctx, const double* pos) {
 // Atoms per wave: one while two blocks per compute unit hold every atom (256
 // units x 2 blocks x 4 waves): the chip is then not full and the shorter chain
 // of a wave counts (12.9 against 20.5 us for 80-50-1 on 1,000 atoms, 8.9
-// against 13.0 us for 29-30-1, 16.9 against 23.5 us for PbTe), else four (20.9
-// against 26.4 us for 80-50-1 on 2,744 atoms; two per wave lie between).
+// against 13.0 us for 29-30-1, 16.9 against 23.5 us for PbTe), else four (20.7
+// against 25.9 us for 80-50-1 on 2,744 atoms, 13.3 against 16.3 us for 29-30-1,
+// 24.5 against 32.4 us for PbTe; two per wave lie between).
 constexpr int kOneAtomWaves = 2048;
 
 template <int TR, int TA, int TL, int TNEU, bool F64>

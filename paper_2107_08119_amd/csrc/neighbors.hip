@@ -9,7 +9,7 @@
 // atoms are binned by fractional coordinate, each cell's members are sorted
 // by index (so the list order does not depend on atomic arrival order) and
 // each atom scans its 27 surrounding cells.  Thin boxes: every atom is tested
-// against every atom and every image in a bounded range.
+// against every atom, in those images that its cutoff can reach (scan_images).
 //
 // The membership test is evaluated in float64 exactly as documented in
 // nep.h (no fused multiply-add), so the list is reproducible bit for bit.

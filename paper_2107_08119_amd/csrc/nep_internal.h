@@ -109,13 +109,13 @@ constexpr int kPairTotals = 16, kPairSlots = 32, kFlagWords = kPairTotals + 16 *
 // 1 eV/A acting on 1 amu, in A/fs^2; and 1 amu A^2/fs^2 in eV.
 constexpr double kAccel = 1.602176634e-19 / 1.66053906660e-27 * 1.0e-10;
 
-// An atom as a neighbour candidate, stored in cell order: float64 position,
-// index, and integer cell offsets of the raw position packed as 3 x int8.
 // One stored partial force dU_i/dr_ij: 12 bytes (one dwordx3 access).
 struct Partial3 {
   float x, y, z;
 };
 
+// An atom as a neighbour candidate, stored in cell order: float64 position,
+// index, and integer cell offsets of the raw position packed as 3 x int8.
 struct alignas(32) CellRec {
   double x, y, z;
   int j;
@@ -354,10 +354,10 @@ hipError_t launch_population(nep_ctx ctx, nep_dataset ds, int n_pop, const float
                              bool first);
 int population_variants();
 int population_atoms(int variant);
-// Largest structure snes_eval_population handles (its forces for one
-// individual must fit the contraction kernel's LDS).
 // atom rows of dU/dq and U in a population evaluation: whole network tiles
 inline size_t population_rows(int n) { return ((size_t)n + 63) / 64 * 64; }
+// Largest structure snes_eval_population handles (its forces for one
+// individual must fit the contraction kernel's LDS).
 int population_max_structure();
 
 // neighbours.hip

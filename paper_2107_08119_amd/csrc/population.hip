@@ -26,16 +26,17 @@
 //   * the network kernel: per individual k, act^T = W1_k Q^T (rows neurons,
 //     columns atoms), tanh, U_i, and dU/dq = (w2 sech^2(act)) W1_k as two
 //     products on the matrix cores (Eqs. nn1, nn2 and their input gradient);
-//   * the contraction kernel: one block per tile of whole structures keeps
-//     the forces of every atom of the tile for every individual in LDS.  Wave
-//     w owns the individuals k = w mod 4, sixteen per matrix tile, and for
-//     each atom i multiplies D_i (rows: pair components) by dU/dq_i (columns:
-//     individuals); each product element p_ij goes to F_j with an LDS add
-//     (F_i = sum_j p_ij - sum_j p_ji, Sec. II A), G_i and V_i give the own
-//     force and the virial.  No partial force goes to memory.  At the end of
-//     each structure the wave forms its energy, force and virial errors in
-//     float64 in a fixed order (Sec. II E).  Only wave w touches the forces
-//     of its individuals, so the sums do not depend on scheduling.
+//   * the contraction kernel: one block per tile of whole structures and group
+//     of up to 64 individuals keeps the forces of every atom of the tile for
+//     every individual of the group in LDS.  The waves take the tile's atoms in
+//     turn and for each atom i multiply D_i (rows: pair components) by dU/dq_i
+//     (columns: individuals, sixteen per matrix tile); each product element
+//     p_ij is added to F_j in LDS (F_i = sum_j p_ij - sum_j p_ji, Sec. II A),
+//     G_i and V_i give the own force and the virial.  No partial force goes to
+//     memory.  The accumulators are 32-bit integers, whose sums do not depend
+//     on the order of the waves' additions, and the energy, force and virial
+//     errors of each structure are then formed in float64 in a fixed order
+//     (Sec. II E), so the losses do not depend on scheduling.
 #include <algorithm>
 #include <vector>
 

@@ -4,11 +4,12 @@
 // update steps.
 //
 // Structures are concatenated into one system (as the paper does, Sec. II F)
-// with a cell per structure.  Their neighbour lists are built once, when the
-// dataset is created.  One launch of the partial-force kernel evaluates every
-// (atom, individual) pair; a population gather turns the partials into per-
-// atom loss terms; float64 sums over each structure and then over structures
-// give the loss components of each individual, in a fixed order.
+// with a cell per structure.  Their neighbour lists are built when the dataset
+// is created or its positions are set.  The population kernels (population.hip)
+// give every individual's squared errors per structure; float64 sums over the
+// structures in a fixed order give the loss components.  One parameter vector
+// (nep_dataset_compute) runs the partial-force kernel and a gather of per-atom
+// terms, and the gradients follow in backward.hip.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -25,7 +26,7 @@ namespace {
 
 inline unsigned blocks_for(size_t work, int block) { return (unsigned)((work + block - 1) / block); }
 
-constexpr int kLanes = 4;  // lanes per atom in the population gather (as in pass 1)
+constexpr int kLanes = 4;  // lanes per atom in the gather (as in pass 1)
 
 // ------------------------------------------------------- dataset lists
 
