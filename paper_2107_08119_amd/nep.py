@@ -524,20 +524,22 @@ class Dataset:
         if self._held is None:
             return False
         held, version = self._held
-        return (held.data_ptr() == pos.data_ptr() and held.dtype == pos.dtype
-                and held.shape == pos.shape and held.stride() == pos.stride()
-                and held._version == version == pos._version)
+        return (pos._version == version and held._version == version
+                and pos.data_ptr() == held.data_ptr() and pos.dtype == torch.float64
+                and pos.is_contiguous() and pos.shape == held.shape)
+
+    def _still(self, held) -> bool:
+        """Whether the dataset's positions are `held` = (tensor, version) of an
+        earlier call."""
+        now = self._held
+        return now is held or (now is not None and now[1] == held[1]
+                               and now[0].data_ptr() == held[0].data_ptr())
 
     @contextlib.contextmanager
-    def _at(self, held):
-        """The dataset at the positions `held` = (tensor, version) of an earlier
-        call: as they are where no other positions have come since, else the
-        earlier ones are uploaded again for the time being."""
+    def _back_at(self, held):
+        """The dataset back at the positions `held` of an earlier call for the
+        time being."""
         now = self._held
-        if now is held or (now is not None and now[0].data_ptr() == held[0].data_ptr()
-                           and now[1] == held[1]):
-            yield
-            return
         if held[0]._version != held[1]:
             raise RuntimeError("positions of an earlier NEPEnergy call were changed in place and "
                                "the dataset has other ones: its parameter gradient is lost")
@@ -657,8 +659,12 @@ class NEPEnergy(torch.autograd.Function):
             raise NotImplementedError("position gradient of the force part needs the Hessian")
         if not actx.needs_input_grad[1]:  # only the positions' gradient is asked for
             return ctx._position_gradient(ds, gE, F), None, None, None
-        with ds._at(held):
-            g = ctx.dataset_backward(ds, z.detach(), gE, gF, F, want_pos=actx.pos_needs_grad)
+        want_pos = actx.pos_needs_grad
+        if ds._still(held):
+            g = ctx.dataset_backward(ds, z.detach(), gE, gF, F, want_pos=want_pos)
+        else:  # other positions have come since
+            with ds._back_at(held):
+                g = ctx.dataset_backward(ds, z.detach(), gE, gF, F, want_pos=want_pos)
         return g.get("pos"), g["z32"], None, None
 
 
