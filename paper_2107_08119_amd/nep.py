@@ -10,6 +10,7 @@ from __future__ import annotations
 import contextlib
 import ctypes as C
 import os
+import weakref
 
 import numpy as np
 import torch
@@ -513,27 +514,32 @@ class Dataset:
 
     def __init__(self, ctx: Context, handle, n_struct: int, n_atoms: int):
         self.ctx, self._h, self.n_struct, self.n_atoms = ctx, handle, n_struct, n_atoms
-        self._held = None  # positions that NEPEnergy uploaded last and their version then
+        # positions that NEPEnergy uploaded last: an alias that keeps them alive,
+        # their version and address then, the tensor itself (weakly)
+        self._held = None
         ctx._own(handle, "nep_dataset_destroy")
+
+    def _hold(self, pos: torch.Tensor, alias: torch.Tensor) -> None:
+        self._held = (alias, pos._version, pos.data_ptr(), weakref.ref(pos))
 
     def _holds(self, pos: torch.Tensor) -> bool:
         """Whether the dataset's positions are those of `pos` as it is now.  The
-        uploaded tensor is kept alive, so that another one cannot come to lie
-        at its address, and both version counters are compared, so that a
-        change in place of either is seen."""
-        if self._held is None:
+        uploaded memory is kept alive, so that another tensor cannot come to lie
+        at its address; for another tensor that shares it, both version counters
+        and the layout are compared."""
+        held = self._held
+        if held is None or pos._version != held[1] or pos.data_ptr() != held[2]:
             return False
-        held, version = self._held
-        return (pos._version == version and held._version == version
-                and pos.data_ptr() == held.data_ptr() and pos.dtype == torch.float64
-                and pos.is_contiguous() and pos.shape == held.shape)
+        if held[3]() is pos:
+            return True
+        alias = held[0]
+        return (alias._version == held[1] and pos.dtype == alias.dtype
+                and pos.shape == alias.shape and pos.is_contiguous())
 
     def _still(self, held) -> bool:
-        """Whether the dataset's positions are `held` = (tensor, version) of an
-        earlier call."""
+        """Whether the dataset's positions are those that an earlier call held."""
         now = self._held
-        return now is held or (now is not None and now[1] == held[1]
-                               and now[0].data_ptr() == held[0].data_ptr())
+        return now is held or (now is not None and now[1:3] == held[1:3])
 
     @contextlib.contextmanager
     def _back_at(self, held):
@@ -638,7 +644,7 @@ class NEPEnergy(torch.autograd.Function):
         if not ds._holds(pos):
             alias = pos.detach()  # the same memory and version counter, no graph
             ctx.dataset_set_positions(ds, alias)
-            ds._held = (alias, alias._version)
+            ds._hold(pos, alias)
         out = ctx.dataset_compute(ds, z.detach())
         actx.save_for_backward(z, out["F"])
         actx.nep = (ctx, ds, ds._held)
@@ -660,7 +666,7 @@ class NEPEnergy(torch.autograd.Function):
         if not actx.needs_input_grad[1]:  # only the positions' gradient is asked for
             return ctx._position_gradient(ds, gE, F), None, None, None
         want_pos = actx.pos_needs_grad
-        if ds._still(held):
+        if ds._held is held or ds._still(held):
             g = ctx.dataset_backward(ds, z.detach(), gE, gF, F, want_pos=want_pos)
         else:  # other positions have come since
             with ds._back_at(held):
