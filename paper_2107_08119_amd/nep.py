@@ -191,6 +191,7 @@ class Context:
                 self._free(handle)
             self._lib.nep_destroy(self._h)
             self._h = None
+            self._md_buffers = None
 
     # Handles made on the context (datasets, correlations) and the names of the
     # calls that free them.  They are freed through the context, so that none outlives it:
@@ -232,6 +233,7 @@ class Context:
         n = pos.shape[1] if pos.dim() == 2 else 0
         _require(pos, torch.float64, (3, n), "pos")
         b = np.ascontiguousarray(box, dtype=np.float64).reshape(9)
+        self._md_buffers = None
         self._check(self._lib.nep_build_neighbors(
             self._h, n, _ptr(pos), b.ctypes.data_as(C.POINTER(C.c_double)), skin, max_neighbors))
         self.n, self.cap = n, max_neighbors  # cap > 0 marks a built list
@@ -483,7 +485,11 @@ class Context:
                 W: torch.Tensor | None = None, J: torch.Tensor | None = None,
                 fe=None) -> torch.Tensor:
         """Velocity-Verlet steps; with fe = (Fx, Fy, Fz) in 1/Angstrom the HNEMD
-        driving force F_e . W_i acts on every atom (nep_md_step_driven)."""
+        driving force F_e . W_i acts on every atom (nep_md_step_driven).  A call
+        on the tensors of the call before continues it with the forces kept from
+        there (velocities may be changed in between, positions by whole lattice
+        vectors); after other changes of the positions build_neighbors or compute
+        has to come first.  The context keeps both tensors alive until then."""
         n = self.n
         _require(pos, torch.float64, (3, n), "pos")
         _require(vel, torch.float64, (3, n), "vel")
@@ -506,6 +512,8 @@ class Context:
         # torch does not see the library's writes: without this, NEPEnergy would
         # take the moved positions for the ones it has
         torch.autograd.graph.increment_version((pos, vel))
+        # the library takes the next call on these addresses for a continuation
+        self._md_buffers = (pos, vel)
         return thermo
 
 

@@ -1,10 +1,12 @@
-"""Datasets and correlations are freed before their context, whatever the order
-in which Python gives them up (no GPU needed): a stand-in library records the
-calls that free them."""
+"""What the binding keeps alive, and in which order it lets go (no GPU needed, a
+stand-in library): datasets and correlations are freed before their context,
+whatever the order in which Python gives them up, and the tensors of an MD call
+stay while the library knows their addresses."""
 import ctypes
 import gc
 
 import pytest
+import torch
 
 from paper_2107_08119_amd import nep
 
@@ -57,3 +59,29 @@ def test_context_closed_first_or_last():
     for x in (corr, *sets, ctx):
         x.close()
     assert sorted(lib.freed[:-1]) == WANT and lib.freed[-1] == ("nep_destroy", 1)
+
+
+def test_md_tensors_stay_while_their_addresses_count(monkeypatch):
+    monkeypatch.setattr(nep, "_ptr", lambda t: t)
+    ctx = nep.Context.__new__(nep.Context)
+    ctx.device, ctx.n, ctx.cap, ctx._h = 0, 20000, 16, None
+
+    class Lib:
+        def __getattr__(self, name):
+            return lambda *a: 0
+
+    ctx._lib = Lib()
+
+    def state():
+        return torch.zeros((3, ctx.n), dtype=torch.float64)
+
+    taken = set()
+    for _ in range(20):  # each call on new tensors: none may lie where one before it did
+        p, v = state(), state()
+        here = {p.data_ptr(), v.data_ptr()}
+        assert not here & taken
+        ctx.md_step(1, 1.0, 10, 28.0, p, v)
+        taken = here
+        del p, v
+    ctx.build_neighbors(state(), torch.eye(3).numpy(), 0.5, 16)
+    assert ctx._md_buffers is None
