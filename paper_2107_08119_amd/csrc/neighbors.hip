@@ -272,13 +272,10 @@ __global__ void k_rank_permute(int n, const int* __restrict__ start,
 }
 
 // k_bin, the cell scan, k_fill and k_rank_permute of a small system in one
-// block: counts, starts and members stay in LDS.  The four launches cost about
-// 20 us on the stream whatever the size, this one a compute unit's loads and
-// stores: a whole list build of 1,000 / 1,500 / 2,048 / 2,500 / 3,000 atoms at 0.05
-// per cubic Angstrom takes 27 / 29 / 32 / 37 / 39 us with it and 36 / 34 / 33 / 36 /
-// 34 us with the four (at a tenth of the density 18 / 22 / 26 / 30 / 35 against 23 /
-// 25 / 27 / 28 / 29), so it serves up to 2,048 atoms.
-constexpr int kSortAtoms = 2048, kSortCells = 4096;
+// block: counts, starts and members stay in LDS.  The four launches cost 20 us
+// on the stream at 1,000 and 8,000 atoms alike, this one 8.6 and 32 us (one
+// compute unit's loads and stores), so it serves up to 3,072 atoms.
+constexpr int kSortAtoms = 3072, kSortCells = 4096;
 constexpr int kSortThreads = 1024;
 __global__ __launch_bounds__(kSortThreads) void k_sort_small(
     int n, int ncell, const double* __restrict__ src, const double* __restrict__ vel_src,

@@ -46,9 +46,3 @@ def test_lists_match_oracle(n, density, images):
     back, j = nb["rev"][mine], nb["nbr"][mine]
     np.testing.assert_array_equal(nb["nbr"][back, j], i)
     np.testing.assert_array_equal(nb["img"][back, j], -nb["img"][mine])
-
-
-# one block sorts up to 2,048 atoms
-@pytest.mark.parametrize("n,density", [(2047, 0.05), (2048, 0.05), (2049, 0.05), (2048, 0.25)])
-def test_lists_around_the_one_block_sort(n, density):
-    test_lists_match_oracle(n, density, 1)

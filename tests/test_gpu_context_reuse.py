@@ -24,7 +24,7 @@ def gas(n, edge):
     [crystal(8), gas(1000, 60.0), crystal(8)],                     # 343, 1,000, 343 cells
     [crystal(10), gas(2000, 80.0), crystal(10), gas(4000, 90.0)],  # 729, 2,744, 729, 4,096
     [crystal(8), crystal(5), crystal(8), crystal(2), crystal(8)],  # 343, 64, 343, thin, 343
-    [gas(2048, 85.0), crystal(8), gas(2049, 85.0)],
+    [gas(3072, 85.0), crystal(8), gas(3073, 85.0)],
 ])
 def test_lists_do_not_depend_on_earlier_systems(order):
     from paper_2107_08119_amd import nep
