@@ -272,9 +272,13 @@ __global__ void k_rank_permute(int n, const int* __restrict__ start,
 }
 
 // k_bin, the cell scan, k_fill and k_rank_permute of a small system in one
-// block: counts, starts and members stay in LDS.  The four launches cost 20 us
-// on the stream at 1,000 and 8,000 atoms alike, this one 8.6 and 32 us (one
-// compute unit's loads and stores), so it serves up to 3,072 atoms.
+// block: counts, starts and members stay in LDS.  The four launches cost about
+// 20 us on the stream whatever the size, this one a compute unit's loads and
+// stores, which depend on the order the atoms come in.  A whole list build of
+// 1,000 / 2,016 / 2,352 / 2,744 diamond atoms in cell order, as at every rebuild of a
+// run, takes 25 / 27 / 29 / 30 us with it and 36 / - / 38 / 38 us with the four; in
+// random order 26 / 32 / 35 / 38 and - / - / 34 / 35 us (3,000 atoms of a tenth of the
+// density 35 and 29 us).  It serves up to 3,072 atoms for the former.
 constexpr int kSortAtoms = 3072, kSortCells = 4096;
 constexpr int kSortThreads = 1024;
 __global__ __launch_bounds__(kSortThreads) void k_sort_small(
