@@ -208,6 +208,7 @@ class Context:
         handle, destroy = self._owned().pop(value, (None, None))
         if handle:
             getattr(self._lib, destroy)(handle)
+            handle.value = None  # its owner's too: NULL, which the library refuses
 
     def __del__(self):
         try:

@@ -52,6 +52,7 @@ def test_context_closed_first_or_last():
     lib, ctx, sets, corr = things()
     sets[0].close()
     ctx.close()
+    assert not sets[1]._h and not corr._h  # no dangling handles
     for x in (*sets, corr, ctx):
         x.close()
     assert sorted(lib.freed[:-1]) == WANT and lib.freed[-1] == ("nep_destroy", 1)
